@@ -96,76 +96,138 @@ __device__ __forceinline__ void two_sum(double a, double b, double &s, double &e
 }
 
 // Row partial sums over one column chunk: mode 0 -> compensated sum of
-// A_ij x_j (hi, lo), mode 1 -> sum |A_ij|.
+// A_ij x_j (hi, lo), mode 1 -> sum |A_ij|, mode 2 -> sum A_ij x_j.
+// Bound by the one read of the matrix.  kCols independent sums over
+// j = jb + kCols k + u keep that many loads of a thread in flight (a wave
+// reads 512 contiguous bytes of each column), combined in fixed order at the
+// end; about kRowsWorkgroups workgroups, all resident at once, cover the HBM
+// latency also for matrices of few rows.  At 7,464 cells (445 MB) a product
+// takes 78 us (5.8 TB/s); the library gemv, whose grid is one workgroup per 64
+// rows, took 418 us (1.07 TB/s).
+constexpr int kCols = 8;
+constexpr int kRowsWorkgroups = 1024;
+
 template <int MODE>
 __global__ __launch_bounds__(256) void k_rows_chunk(int N, const double *__restrict__ A, const double *__restrict__ x,
                                                     int chunk, double *hi_out, double *lo_out) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= N) return;
   const int jb = blockIdx.y * chunk, je = min(N, jb + chunk);
-  // four independent compensated sums over j = jb + 4k + u (more loads in
-  // flight per thread), combined in fixed order at the end
-  double s[4] = {0.0, 0.0, 0.0, 0.0}, c[4] = {0.0, 0.0, 0.0, 0.0};
-  int j = jb;
-  for (; j + 4 <= je; j += 4) {
-    double a[4];
+  double s[kCols], c[kCols];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) a[u] = A[(size_t)(j + u) * N + i];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (MODE == 0) {
-        const double xj = x[j + u];
-        const double p = a[u] * xj;
-        const double pe = fma(a[u], xj, -p);
-        double t, e;
-        two_sum(s[u], p, t, e);
-        s[u] = t;
-        c[u] += e + pe;
-      } else {
-        s[u] += fabs(a[u]);
-      }
-    }
-  }
-  for (; j < je; ++j) {
-    const double a = A[(size_t)j * N + i];
-    if (MODE == 0) {
+  for (int u = 0; u < kCols; ++u) s[u] = c[u] = 0.0;
+  auto add = [&](int u, double a, int j) {
+    if (MODE == 1) {
+      s[u] += fabs(a);
+    } else if (MODE == 2) {
+      s[u] = fma(a, x[j], s[u]);
+    } else {
       const double xj = x[j];
       const double p = a * xj;
       const double pe = fma(a, xj, -p);
       double t, e;
-      two_sum(s[0], p, t, e);
-      s[0] = t;
-      c[0] += e + pe;
-    } else {
-      s[0] += fabs(a);
+      two_sum(s[u], p, t, e);
+      s[u] = t;
+      c[u] += e + pe;
     }
+  };
+  const double *col = A + (size_t)jb * N + i;
+  int j = jb;
+  for (; j + kCols <= je; j += kCols, col += (size_t)kCols * N) {
+    double a[kCols];
+#pragma unroll
+    for (int u = 0; u < kCols; ++u) a[u] = __builtin_nontemporal_load(col + (size_t)u * N);
+#pragma unroll
+    for (int u = 0; u < kCols; ++u) add(u, a[u], j + u);
   }
+  for (; j < je; ++j, col += N) add(0, *col, j);
   double S = s[0], C = c[0];
 #pragma unroll
-  for (int u = 1; u < 4; ++u) {
-    double t, e;
-    two_sum(S, s[u], t, e);
-    S = t;
-    C += e + c[u];
+  for (int u = 1; u < kCols; ++u) {
+    if (MODE == 0) {
+      double t, e;
+      two_sum(S, s[u], t, e);
+      S = t;
+      C += e + c[u];
+    } else {
+      S += s[u];
+    }
   }
   hi_out[(size_t)blockIdx.y * N + i] = S;
-  lo_out[(size_t)blockIdx.y * N + i] = C;
+  if (MODE == 0) lo_out[(size_t)blockIdx.y * N + i] = C;
 }
 
-// r_i = b_i - sum over chunks (fixed order), compensated; also max |r|.
-__global__ __launch_bounds__(256) void k_residual_final(int N, int nch, const double *__restrict__ hi,
-                                                        const double *__restrict__ lo, const double *__restrict__ b,
-                                                        double *r) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= N) return;
-  double s = b[i], c = 0.0;
-  for (int k = 0; k < nch; ++k) {
-    double t, e;
-    two_sum(s, -hi[(size_t)k * N + i], t, e);
-    s = t;
-    c += e - lo[(size_t)k * N + i];
+// r_i = b_i - sum over chunks (fixed order), compensated; with mx, the
+// workgroup's max |r|, |x|, |b| go to mx[3 blockIdx.x + 0..2] (x = the
+// product's operand).  One wave per workgroup and eight chunks' loads in
+// flight: at a few thousand rows the launch is bound by that latency.
+constexpr int kFin = 64;
+
+__global__ __launch_bounds__(kFin) void k_residual_final(int N, int nch, const double *__restrict__ hi,
+                                                         const double *__restrict__ lo, const double *__restrict__ b,
+                                                         const double *__restrict__ x, double *r, double *mx) {
+  const int i = blockIdx.x * kFin + threadIdx.x;
+  double ar = 0.0, ax = 0.0, ab = 0.0;
+  if (i < N) {
+    double s = b[i], c = 0.0;
+    int k = 0;
+    for (; k + 8 <= nch; k += 8) {
+      double h[8], l[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        h[u] = hi[(size_t)(k + u) * N + i];
+        l[u] = lo[(size_t)(k + u) * N + i];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        double t, e;
+        two_sum(s, -h[u], t, e);
+        s = t;
+        c += e - l[u];
+      }
+    }
+    for (; k < nch; ++k) {
+      double t, e;
+      two_sum(s, -hi[(size_t)k * N + i], t, e);
+      s = t;
+      c += e - lo[(size_t)k * N + i];
+    }
+    r[i] = s + c;
+    ar = fmax(ar, fabs(s + c));
+    ax = fmax(ax, fabs(x[i]));
+    ab = fmax(ab, fabs(b[i]));
   }
-  r[i] = s + c;
+  if (mx) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      ar = fmax(ar, __shfl_xor(ar, o));
+      ax = fmax(ax, __shfl_xor(ax, o));
+      ab = fmax(ab, __shfl_xor(ab, o));
+    }
+    if (threadIdx.x == 0) {
+      mx[3 * (size_t)blockIdx.x] = ar;
+      mx[3 * (size_t)blockIdx.x + 1] = ax;
+      mx[3 * (size_t)blockIdx.x + 2] = ab;
+    }
+  }
+}
+
+// out_i = (add ? out_i : 0) + sum over chunks, in chunk order
+__global__ __launch_bounds__(kFin) void k_rows_final(int N, int nch, const double *__restrict__ hi, int add,
+                                                     double *out) {
+  const int i = blockIdx.x * kFin + threadIdx.x;
+  if (i >= N) return;
+  double s = 0.0;
+  int k = 0;
+  for (; k + 8 <= nch; k += 8) {
+    double h[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) h[u] = hi[(size_t)(k + u) * N + i];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += h[u];
+  }
+  for (; k < nch; ++k) s += hi[(size_t)k * N + i];
+  out[i] = add ? out[i] + s : s;
 }
 
 // Transposed compensated residual r_j = g_j - sum_i A_ij l_i: one wave per
@@ -200,14 +262,6 @@ __global__ __launch_bounds__(256) void k_residual_t(int N, const double *__restr
     two_sum(g[j], -s, t, e);
     r[j] = t + (e - c);
   }
-}
-
-__global__ __launch_bounds__(256) void k_rowsum_final(int N, int nch, const double *__restrict__ hi, double *out) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= N) return;
-  double s = 0.0;
-  for (int k = 0; k < nch; ++k) s += hi[(size_t)k * N + i];
-  out[i] = s;
 }
 
 // max |v| over up to three vectors of length N -> out[0..2] (single block, fixed order)
@@ -262,12 +316,13 @@ __global__ __launch_bounds__(256) void k_axpy1(int N, const double *__restrict__
 }
 
 static inline int nb(int n) { return (n + 255) / 256; }
+static inline int nfin(int n) { return (n + kFin - 1) / kFin; }
 
+// Column chunks of the matrix passes: about kRowsWorkgroups workgroups, at
+// least 32 columns each.
 static int n_chunks(int N) {
-  // enough workgroups for 256 CUs, >= 512 columns per chunk
-  int rb = nb(N);
-  int c = std::max(1, std::min((2048 + rb - 1) / rb, N / 512));
-  return std::min(c, 64);
+  const int rb = nb(N);
+  return std::max(1, std::min((kRowsWorkgroups + rb - 1) / rb, N / 32));
 }
 
 static obem_status handle(obem_ctx *ctx, rocblas_handle *h) {
@@ -313,8 +368,10 @@ __global__ __launch_bounds__(256) void k_identity(int N, double *B) {
   for (int j = blockIdx.y; j < N; j += gridDim.y) B[(size_t)j * N + i] = (i == j) ? 1.0 : 0.0;
 }
 
-// Compensated residual r = b - A x (device), chunked over columns.
-static obem_status residual(obem_ctx *ctx, const obem_meshh *m, const double *x, const double *b, double *r) {
+// Compensated residual r = b - A x (device), chunked over columns; with mx,
+// also per-workgroup maxima of |r|, |x|, |b| (k_residual_final).
+static obem_status residual(obem_ctx *ctx, const obem_meshh *m, const double *x, const double *b, double *r,
+                            double *mx) {
   const int N = (int)m->n;
   const int nch = n_chunks(N);
   const int chunk = (N + nch - 1) / nch;
@@ -322,7 +379,7 @@ static obem_status residual(obem_ctx *ctx, const obem_meshh *m, const double *x,
   double *lo = (double *)ws_get(ctx, WS_SOLVE2, sizeof(double) * (size_t)nch * N);
   if (!hi || !lo) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
   hipLaunchKernelGGL(k_rows_chunk<0>, dim3(nb(N), nch), dim3(256), 0, ctx->stream, N, m->A, x, chunk, hi, lo);
-  hipLaunchKernelGGL(k_residual_final, dim3(nb(N)), dim3(256), 0, ctx->stream, N, nch, hi, lo, b, r);
+  hipLaunchKernelGGL(k_residual_final, dim3(nfin(N)), dim3(kFin), 0, ctx->stream, N, nch, hi, lo, b, x, r, mx);
   OBEM_HIP(ctx, hipGetLastError());
   return OBEM_OK;
 }
@@ -359,7 +416,7 @@ obem_status bem_factor(obem_ctx *ctx, obem_meshh *m) {
     double *rs = (double *)ws_get(ctx, WS_SOLVE0, sizeof(double) * (size_t)(3 * N + 8));
     if (!hi || !lo || !rs) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
     hipLaunchKernelGGL(k_rows_chunk<1>, dim3(nb(N), nch), dim3(256), 0, ctx->stream, N, m->A, nullptr, chunk, hi, lo);
-    hipLaunchKernelGGL(k_rowsum_final, dim3(nb(N)), dim3(256), 0, ctx->stream, N, nch, hi, rs);
+    hipLaunchKernelGGL(k_rows_final, dim3(nfin(N)), dim3(kFin), 0, ctx->stream, N, nch, hi, 0, rs);
     hipLaunchKernelGGL(k_absmax3, dim3(1), dim3(256), 0, ctx->stream, N, rs, nullptr, nullptr, rs + 3 * N);
     OBEM_HIP(ctx, hipGetLastError());
     OBEM_HIP(ctx, hipMemcpyAsync(&m->anorm_inf, rs + 3 * N, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
@@ -437,14 +494,26 @@ obem_status bem_factor(obem_ctx *ctx, obem_meshh *m) {
   return OBEM_OK;
 }
 
-// out = A^{-1} in, or A^{-T} in when trans (in and out distinct)
-static obem_status inv_apply(obem_ctx *ctx, obem_meshh *m, const double *in, double *out, bool trans = false) {
+// out = A^{-1} in (added to out when add), or A^{-T} in when trans (then not
+// added; in and out distinct).  The plain product is k_rows_chunk<2>, the
+// transposed one the library's.
+static obem_status inv_apply(obem_ctx *ctx, obem_meshh *m, const double *in, double *out, bool trans, bool add) {
+  const int N = (int)m->n;
+  if (!trans) {
+    const int nch = n_chunks(N);
+    const int chunk = (N + nch - 1) / nch;
+    double *hi = (double *)ws_get(ctx, WS_SOLVE1, sizeof(double) * (size_t)nch * N);
+    if (!hi) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
+    hipLaunchKernelGGL(k_rows_chunk<2>, dim3(nb(N), nch), dim3(256), 0, ctx->stream, N, m->LU, in, chunk, hi, nullptr);
+    hipLaunchKernelGGL(k_rows_final, dim3(nfin(N)), dim3(kFin), 0, ctx->stream, N, nch, hi, add ? 1 : 0, out);
+    OBEM_HIP(ctx, hipGetLastError());
+    return OBEM_OK;
+  }
   rocblas_handle h;
   obem_status st = handle(ctx, &h);
   if (st) return st;
-  const int N = (int)m->n;
   const double one = 1.0, zero = 0.0;
-  const rocblas_operation op = trans ? rocblas_operation_transpose : rocblas_operation_none;
+  const rocblas_operation op = rocblas_operation_transpose;
   if (rocblas_set_pointer_mode(h, rocblas_pointer_mode_host) != rocblas_status_success)
     return fail(ctx, OBEM_EDEVICE, "rocblas_set_pointer_mode failed");
   const rocblas_status rs = large_matrix(N) ? rocblas_dgemv_64(h, op, N, N, &one, m->LU, N, in, 1, &zero, out, 1)
@@ -459,31 +528,33 @@ obem_status bem_solve(obem_ctx *ctx, obem_meshh *m, const double *rhs, double *s
   if (st) return st;
   OBEM_PROF(ctx, "solve");
   const int N = (int)m->n;
-  double *w = (double *)ws_get(ctx, WS_SOLVE0, sizeof(double) * (size_t)(3 * N + 8));
+  const int nmx = trans ? 1 : nfin(N);  // triples of maxima: r, sigma, b
+  double *w = (double *)ws_get(ctx, WS_SOLVE0, sizeof(double) * (size_t)(3 * N + 3 * nmx + 8));
   if (!w) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
   double *b = w, *r = w + N, *d = w + 2 * N, *stats = w + 3 * N;
   // keep b (rhs may alias sigma)
   OBEM_HIP(ctx, hipMemcpyAsync(b, rhs, sizeof(double) * N, hipMemcpyDeviceToDevice, ctx->stream));
-  st = inv_apply(ctx, m, b, sigma, trans);
+  st = inv_apply(ctx, m, b, sigma, trans, false);
   if (st) return st;
   double best_err = INFINITY;
   int it = 0;
-  double h[3] = {0, 0, 0};
+  std::vector<double> hm(info ? 3 * (size_t)nmx : 0);
   for (;;) {
     // without info nobody reads the residual after the last correction
     if (!info && it >= max_refine) break;
     if (trans) {
       hipLaunchKernelGGL(k_residual_t, dim3((N + 3) / 4), dim3(256), 0, ctx->stream, N, m->A, sigma, b, r);
+      if (info) hipLaunchKernelGGL(k_absmax3, dim3(1), dim3(256), 0, ctx->stream, N, r, sigma, b, stats);
       OBEM_HIP(ctx, hipGetLastError());
     } else {
-      st = residual(ctx, m, sigma, b, r);
+      st = residual(ctx, m, sigma, b, r, info ? stats : nullptr);
       if (st) return st;
     }
     if (info) {
-      hipLaunchKernelGGL(k_absmax3, dim3(1), dim3(256), 0, ctx->stream, N, r, sigma, b, stats);
-      OBEM_HIP(ctx, hipGetLastError());
-      OBEM_HIP(ctx, hipMemcpyAsync(h, stats, 3 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+      OBEM_HIP(ctx, hipMemcpyAsync(hm.data(), stats, sizeof(double) * hm.size(), hipMemcpyDeviceToHost, ctx->stream));
       OBEM_HIP(ctx, hipStreamSynchronize(ctx->stream));
+      double h[3] = {0, 0, 0};
+      for (size_t k = 0; k < hm.size(); ++k) h[k % 3] = std::fmax(h[k % 3], hm[k]);
       const double berr = h[0] / (m->anorm_inf * h[1] + h[2] + 1e-300);
       info->iterations = it;
       info->backward_error = berr;
@@ -492,10 +563,15 @@ obem_status bem_solve(obem_ctx *ctx, obem_meshh *m, const double *rhs, double *s
       if (!(berr < 0.5 * best_err) || it >= max_refine) break;
       best_err = berr;
     }
-    st = inv_apply(ctx, m, r, d, trans);
-    if (st) return st;
-    hipLaunchKernelGGL(k_axpy1, dim3(nb(N)), dim3(256), 0, ctx->stream, N, d, sigma);
-    OBEM_HIP(ctx, hipGetLastError());
+    if (trans) {
+      st = inv_apply(ctx, m, r, d, true, false);
+      if (st) return st;
+      hipLaunchKernelGGL(k_axpy1, dim3(nb(N)), dim3(256), 0, ctx->stream, N, d, sigma);
+      OBEM_HIP(ctx, hipGetLastError());
+    } else {
+      st = inv_apply(ctx, m, r, sigma, false, true);
+      if (st) return st;
+    }
     ++it;
   }
   if (info && info->backward_error > 1e-14)
