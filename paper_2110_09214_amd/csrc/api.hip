@@ -594,18 +594,21 @@ static obem_status field_eval_impl(obem_ctx *ctx, const obem_meshh *mesh, const 
   }
   double *acc = (double *)ws_get(ctx, WS_ACC, sizeof(double) * 4 * (size_t)n_tgt);
   if (!acc) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
-  if (mesh) {
-    st = launch_panel_field(ctx, mesh, sigma, to, precision, want_v, acc);
-  } else {
+  // the pair-once evaluation adds to the accumulator; otherwise the partial
+  // sums of cells and charges are added and scattered in one pass
+  Slots cells, pairs;
+  if (mesh)
+    st = launch_panel_field(ctx, mesh, sigma, to, precision, want_v, acc, once ? nullptr : &cells);
+  else if (once)
     st = launch_fill(ctx, acc, 4 * (size_t)n_tgt, 0.0);
-  }
   if (st) return st;
   if (n_src > 0) {
     st = launch_pair_field(ctx, n_src, so.x, so.y, so.z, so.q, to, soft, precision, tis, want_v, nullptr, nullptr,
-                           acc, nullptr, nullptr, so.tbox, 0.0, tis ? so.inv : nullptr, once);
+                           acc, nullptr, nullptr, so.tbox, 0.0, tis ? so.inv : nullptr, once, once ? nullptr : &pairs);
     if (st) return st;
   }
-  return launch_scatter(ctx, to, acc, kKe, Ex, Ey, Ez, want_v ? V : nullptr);
+  if (once) return launch_scatter(ctx, to, acc, kKe, Ex, Ey, Ez, nullptr);
+  return launch_finish(ctx, to, cells, pairs, kKe, Ex, Ey, Ez, want_v ? V : nullptr);
 }
 
 obem_status field_eval(obem_ctx *ctx, const obem_meshh *mesh, const double *sigma, int64_t n_src,

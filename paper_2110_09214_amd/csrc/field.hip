@@ -828,21 +828,55 @@ __global__ __launch_bounds__(kThreads) void k_panel_fp64_near(int n_t, const dou
   }
 }
 
-// acc = sum of the cell-split partials, in split order.
-__global__ __launch_bounds__(256) void k_panel_reduce(int n_t, int ns, const double *__restrict__ part, double *acc) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= n_t) return;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    double s = 0.0;
-    for (int y = 0; y < ns; ++y) s += part[((size_t)y * 4 + c) * n_t + i];
-    acc[(size_t)c * n_t + i] = s;
-  }
+// Slot sums: acc[c][i] = (has_base ? acc[c][i] : 0) + the slots' entries
+// part[s][c][i] in slot order, one thread per (component, point).  Bound by
+// the latency of the loads for few points and by HBM for many: 16 loads of a
+// thread in flight and one component per thread (97 points, 64 slots: one
+// workgroup that walked the slots one by one took 58 us).
+__global__ __launch_bounds__(kSlotThreads) void k_slot_sum(int n, int ns, size_t stride,
+                                                           const double *__restrict__ part, int has_base,
+                                                           double *acc) {
+  const int i = blockIdx.x * kSlotThreads + threadIdx.x;
+  if (i >= n) return;
+  const size_t o = (size_t)blockIdx.y * n + i;
+  acc[o] = slot_sum(has_base ? acc[o] : 0.0, part + o, stride, ns);
+}
+
+void launch_slot_sum(obem_ctx *ctx, int n, int comps, const Slots &s, bool has_base, double *acc) {
+  hipLaunchKernelGGL(k_slot_sum, dim3((n + kSlotThreads - 1) / kSlotThreads, comps), dim3(kSlotThreads), 0, ctx->stream,
+                     n, s.n, (size_t)comps * n, s.p, has_base ? 1 : 0, acc);
+}
+
+// The field at the caller's targets from the cell slots and the source-chunk
+// slots in one pass: scale * (cells in split order, then chunks in order),
+// scattered to caller order.
+__global__ __launch_bounds__(kSlotThreads) void k_slot_finish(int n, const int32_t *__restrict__ perm, Slots cells,
+                                                              Slots pairs, double scale, double *Ex, double *Ey,
+                                                              double *Ez, double *V) {
+  const int i = blockIdx.x * kSlotThreads + threadIdx.x;
+  if (i >= n) return;
+  const int c = blockIdx.y;
+  const size_t o = (size_t)c * n + i;
+  double v = slot_sum(0.0, cells.p + o, 4 * (size_t)n, cells.n);
+  v = slot_sum(v, pairs.p + o, 4 * (size_t)n, pairs.n);
+  double *out = c == 0 ? Ex : (c == 1 ? Ey : (c == 2 ? Ez : V));
+  out[perm[i]] = scale * v;
+}
+
+obem_status launch_finish(obem_ctx *ctx, const TargetOrder &to, const Slots &cells, const Slots &pairs, double scale,
+                          double *Ex, double *Ey, double *Ez, double *V) {
+  if (to.n == 0) return OBEM_OK;
+  OBEM_PROF(ctx, "scatter");
+  hipLaunchKernelGGL(k_slot_finish, dim3((to.n + kSlotThreads - 1) / kSlotThreads, V ? 4 : 3), dim3(kSlotThreads), 0,
+                     ctx->stream, to.n, to.perm, cells, pairs, scale, Ex, Ey, Ez, V);
+  OBEM_HIP(ctx, hipGetLastError());
+  return OBEM_OK;
 }
 
 obem_status launch_panel_field(obem_ctx *ctx, const obem_meshh *m, const double *sigma, const TargetOrder &to,
-                               obem_precision prec, bool want_v, double *acc) {
+                               obem_precision prec, bool want_v, double *acc, Slots *slots) {
   const int n_t = to.n;
+  if (slots) *slots = Slots{acc, 0};
   if (n_t == 0) return OBEM_OK;
   const int N = (int)m->n;
   const int bt = nblk(n_t);
@@ -879,7 +913,10 @@ obem_status launch_panel_field(obem_ctx *ctx, const obem_meshh *m, const double 
   }
 #undef PANEL_NEAR
 #undef PANEL_FAR
-  if (ns > 1) hipLaunchKernelGGL(k_panel_reduce, dim3(nblk(n_t)), dim3(256), 0, ctx->stream, n_t, ns, part, acc);
+  if (slots)
+    *slots = Slots{part, ns};
+  else if (ns > 1)
+    launch_slot_sum(ctx, n_t, 4, Slots{part, ns}, false, acc);
   OBEM_HIP(ctx, hipGetLastError());
   return OBEM_OK;
 }
@@ -890,7 +927,7 @@ obem_status launch_panel_field(obem_ctx *ctx, const obem_meshh *m, const double 
 // Each workgroup takes 256 consecutive (sorted) targets and one chunk of the
 // sources (gridDim.y chunks, so small target sets still fill the chip), and
 // writes per-chunk partial sums part[chunk][4][n_t] (Ex, Ey, Ez, V) plus the
-// nearest opposite-species source; k_pair_reduce then sums the chunks in
+// nearest opposite-species source; the chunks are then summed in
 // order.  Source tiles of 256 are staged in LDS (recentred FP32 position and
 // charge, read as broadcasts).
 // Species keys: electron 0 looks for cation 1 and vice versa.
@@ -1586,34 +1623,26 @@ __global__ __launch_bounds__(kThreads) void k_pair_fp64(int n_t, const double *_
   }
 }
 
-// acc[c][i] = (has_base ? acc[c][i] : 0) + sum over chunks in order; nearest
-// partner = smallest distance, ties to the earlier chunk (lower source index).
+// Nearest partner over the source chunks: smallest distance, ties to the
+// earlier chunk (lower source index).
 template <typename DT>
-__global__ __launch_bounds__(256) void k_pair_reduce(int n_t, int nsplit, const double *__restrict__ part,
-                                                     int has_base, double *acc, const DT *__restrict__ nn_d2p,
-                                                     const int32_t *__restrict__ nn_ip, double *nn_d2,
-                                                     int32_t *nn_idx) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
+__global__ __launch_bounds__(kSlotThreads) void k_nn_reduce(int n_t, int nsplit, const DT *__restrict__ nn_d2p,
+                                                            const int32_t *__restrict__ nn_ip, double *nn_d2,
+                                                            int32_t *nn_idx) {
+  const int i = blockIdx.x * kSlotThreads + threadIdx.x;
   if (i >= n_t) return;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    double s = has_base ? acc[(size_t)c * n_t + i] : 0.0;
-    for (int k = 0; k < nsplit; ++k) s += part[(size_t)k * 4 * n_t + (size_t)c * n_t + i];
-    acc[(size_t)c * n_t + i] = s;
-  }
-  if (nn_idx) {
-    DT best = INFINITY;
-    int32_t bi = -1;
-    for (int k = 0; k < nsplit; ++k) {
-      DT d = nn_d2p[(size_t)k * n_t + i];
-      if (d < best) {
-        best = d;
-        bi = nn_ip[(size_t)k * n_t + i];
-      }
+  DT best = INFINITY;
+  int kb = -1;
+#pragma unroll 8
+  for (int k = 0; k < nsplit; ++k) {
+    const DT d = nn_d2p[(size_t)k * n_t + i];
+    if (d < best) {
+      best = d;
+      kb = k;
     }
-    nn_d2[i] = (double)best;
-    nn_idx[i] = bi;
   }
+  nn_d2[i] = (double)best;
+  nn_idx[i] = kb < 0 ? -1 : nn_ip[(size_t)kb * n_t + i];
 }
 
 // Terms of the tile pairs kept by the directed kernel (mask bits weighted
@@ -1667,10 +1696,12 @@ obem_status launch_pair_field(obem_ctx *ctx, int64_t n_src, const double *sx, co
                               const double *sq, const TargetOrder &to, double soft, obem_precision prec,
                               bool tgt_is_src, bool want_v, const int8_t *species, const int8_t *species_s,
                               double *acc, int32_t *nn_idx, double *nn_d2, const double *tbox, double nn_cut,
-                              const int32_t *self_map, bool once) {
+                              const int32_t *self_map, bool once, Slots *slots) {
   const int n_t = to.n;
   const int n_s = (int)n_src;
+  if (slots) *slots = Slots{acc, 0};
   if (n_t == 0 || n_s == 0) return OBEM_OK;
+  if (once && slots) return fail(ctx, OBEM_EINVAL, "the pair-once evaluation adds its sums itself");
   if (once && !(tgt_is_src && n_s == n_t && tbox && pair_once_applies(n_t, prec, soft, want_v)))
     return fail(ctx, OBEM_EINVAL, "pair-once evaluation needs targets = sources in one order");
   const int bt = nblk(n_t);
@@ -1747,12 +1778,17 @@ obem_status launch_pair_field(obem_ctx *ctx, int64_t n_src, const double *sx, co
   // the accumulator already holds the cell field when the panel kernel ran
   {
     OBEM_PROF(ctx, "pair_reduce");
-    if (prec == OBEM_MIXED)
-      hipLaunchKernelGGL(k_pair_reduce<float>, dim3(nblk(n_t)), dim3(256), 0, ctx->stream, n_t, nsplit, part, 1,
-                         acc, (const float *)nnd, nni, nn_d2, nn_idx);
+    if (slots)
+      *slots = Slots{part, nsplit};
     else
-      hipLaunchKernelGGL(k_pair_reduce<double>, dim3(nblk(n_t)), dim3(256), 0, ctx->stream, n_t, nsplit, part, 1,
-                         acc, (const double *)nnd, nni, nn_d2, nn_idx);
+      launch_slot_sum(ctx, n_t, 4, Slots{part, nsplit}, true, acc);
+    const dim3 gn((n_t + kSlotThreads - 1) / kSlotThreads);
+    if (nn && prec == OBEM_MIXED)
+      hipLaunchKernelGGL(k_nn_reduce<float>, gn, dim3(kSlotThreads), 0, ctx->stream, n_t, nsplit, (const float *)nnd,
+                         nni, nn_d2, nn_idx);
+    else if (nn)
+      hipLaunchKernelGGL(k_nn_reduce<double>, gn, dim3(kSlotThreads), 0, ctx->stream, n_t, nsplit, (const double *)nnd,
+                         nni, nn_d2, nn_idx);
   }
   OBEM_HIP(ctx, hipGetLastError());
   if (once) {

@@ -134,9 +134,10 @@ obem_status field_map_build(obem_ctx *ctx, const obem_meshh *mesh, const double 
   TargetOrder to;
   obem_status st = order_targets(ctx, M, xs, xs + M, xs + 2 * M, &to);
   if (st) return st;
-  st = launch_panel_field(ctx, mesh, sigma, to, precision, false, acc);
+  Slots cells;
+  st = launch_panel_field(ctx, mesh, sigma, to, precision, false, acc, &cells);
   if (st) return st;
-  return launch_scatter(ctx, to, acc, kKe, map->ex, map->ey, map->ez, nullptr);
+  return launch_finish(ctx, to, cells, Slots{}, kKe, map->ex, map->ey, map->ez, nullptr);
 }
 
 obem_status field_map_eval(obem_ctx *ctx, const obem_field_map *map, int64_t n, const double *x, const double *y,
@@ -191,9 +192,10 @@ obem_status induced_current(obem_ctx *ctx, const obem_meshh *mesh, const double 
     if (st) return st;
     double *acc = (double *)ws_get(ctx, WS_ACC, sizeof(double) * 4 * (size_t)n);
     if (!acc) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
-    st = launch_panel_field(ctx, mesh, sigma_w, to, precision, false, acc);
+    Slots cells;
+    st = launch_panel_field(ctx, mesh, sigma_w, to, precision, false, acc, &cells);
     if (st) return st;
-    st = launch_scatter(ctx, to, acc, kKe, Ew, Ew + n, Ew + 2 * n, nullptr);
+    st = launch_finish(ctx, to, cells, Slots{}, kKe, Ew, Ew + n, Ew + 2 * n, nullptr);
     if (st) return st;
   }
   hipLaunchKernelGGL(k_ramo_terms, dim3(nb), dim3(256), 0, ctx->stream, (int)n, Ew, vx, vy, vz, species, terms, part);

@@ -372,10 +372,9 @@ __global__ __launch_bounds__(256) void k_influence_rhs(int N, int nch, const dou
   const int k = blockIdx.x * 256 + threadIdx.x;  // sorted position
   if (k >= N) return;
   const int i = ord[k];
-  double s[4] = {0, 0, 0, 0};
-  for (int c = 0; c < nch; ++c)
+  double s[4];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) s[m] += part[(size_t)c * 4 * N + (size_t)m * N + k];
+  for (int m = 0; m < 4; ++m) s[m] = slot_sum(0.0, part + (size_t)m * N + k, 4 * (size_t)N, nch);
   const double area = f[(size_t)MF_AREA * N + i];
   const double vb = kKe * s[0] / area;
   const double eb[3] = {-kKe * s[1] / area, -kKe * s[2] / area, -kKe * s[3] / area};

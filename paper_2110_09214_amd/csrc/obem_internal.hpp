@@ -202,23 +202,60 @@ struct TargetOrder {
 obem_status order_targets(obem_ctx *ctx, int64_t n, const double *tx, const double *ty,
                           const double *tz, TargetOrder *out);
 
+// Partial sums in n slots, each [components][points] FP64.
+struct Slots {
+  const double *p = nullptr;
+  int n = 0;
+};
+constexpr int kSlotThreads = 64;
+
+// s + p[0] + p[stride] + ... (ns terms, in order), 16 loads in flight.
+__device__ __forceinline__ double slot_sum(double s, const double *__restrict__ p, size_t stride, int ns) {
+  int k = 0;
+  for (; k + 16 <= ns; k += 16) {
+    double v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = p[(size_t)(k + u) * stride];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) s += v[u];
+  }
+  for (; k + 4 <= ns; k += 4) {
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = p[(size_t)(k + u) * stride];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) s += v[u];
+  }
+  for (; k < ns; ++k) s += p[(size_t)k * stride];
+  return s;
+}
+
+// acc (+)= the slots of comps x n, in slot order (field.hip).
+void launch_slot_sum(obem_ctx *ctx, int n, int comps, const Slots &s, bool has_base, double *acc);
+
 // Field kernels (field.hip).  acc: 4 x n FP64 accumulator in sorted order
-// (Ex, Ey, Ez, V) in units of 1/k_e.
+// (Ex, Ey, Ez, V) in units of 1/k_e.  With slots, the partial sums are left
+// in their slots (acc itself where there is one) for launch_finish.
 obem_status launch_panel_field(obem_ctx *ctx, const obem_meshh *m, const double *sigma,
-                               const TargetOrder &to, obem_precision prec, bool want_v, double *acc);
+                               const TargetOrder &to, obem_precision prec, bool want_v, double *acc,
+                               Slots *slots = nullptr);
 // species_t (caller order of the targets) and species_s (source order) are
 // needed only for the nearest opposite-species search (nn_idx != NULL).
 // With tbox (per 256-source tile: lo xyz, hi xyz; mixed precision only) the
 // search is limited to partners within nn_cut (a target with none gets
 // index -1), and source tiles far from a workgroup's targets take the
 // expanded form.  self_map (targets = sources): caller index -> position in
-// the source arrays, NULL when the sources are in caller order.
+// the source arrays, NULL when the sources are in caller order.  slots: as
+// for launch_panel_field, not with the pair-once evaluation.
 obem_status launch_pair_field(obem_ctx *ctx, int64_t n_src, const double *sx, const double *sy,
                               const double *sz, const double *sq, const TargetOrder &to, double soft,
                               obem_precision prec, bool tgt_is_src, bool want_v, const int8_t *species_t,
                               const int8_t *species_s, double *acc, int32_t *nn_idx, double *nn_d2,
                               const double *tbox = nullptr, double nn_cut = 0.0, const int32_t *self_map = nullptr,
-                              bool once = false);
+                              bool once = false, Slots *slots = nullptr);
+// scale * (cell slots + source-chunk slots) at the targets in caller order.
+obem_status launch_finish(obem_ctx *ctx, const TargetOrder &to, const Slots &cells, const Slots &pairs, double scale,
+                          double *Ex, double *Ey, double *Ez, double *V);
 // Whether the pair-once evaluation (targets = sources in one order, every
 // unordered pair of particles in different super-blocks evaluated once for
 // both) applies: mixed precision, softened, no potential, more than two

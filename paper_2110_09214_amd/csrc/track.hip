@@ -977,15 +977,22 @@ static obem_status step_field(obem_ctx *ctx, obem_meshh *mesh, const double *sig
     to.perm = sperm + nz;
     to.xs = srcb;
   }
-  if (map)
+  Slots cells, pairs;
+  if (map) {
     st = launch_map_acc(ctx, *map, to, acc);
-  else
-    st = mesh ? launch_panel_field(ctx, mesh, sigma, to, p->precision, false, acc) : launch_fill(ctx, acc, 4 * nz, 0.0);
+    cells = Slots{acc, 1};
+  } else if (mesh) {
+    st = launch_panel_field(ctx, mesh, sigma, to, p->precision, false, acc, once ? nullptr : &cells);
+  } else if (once) {
+    st = launch_fill(ctx, acc, 4 * nz, 0.0);
+  }
   if (st) return st;
   st = launch_pair_field(ctx, n, srcb, srcb + nz, srcb + 2 * nz, srcb + 3 * nz, to, p->soft, p->precision, true,
-                         false, S->species, ssp, acc, nn_s, nnd, tbox, p->r_rec, nullptr, once);
+                         false, S->species, ssp, acc, nn_s, nnd, tbox, p->r_rec, nullptr, once,
+                         once ? nullptr : &pairs);
   if (st) return st;
-  st = launch_scatter(ctx, to, acc, kKe, E, E + nz, E + 2 * nz, nullptr);
+  st = once ? launch_scatter(ctx, to, acc, kKe, E, E + nz, E + 2 * nz, nullptr)
+            : launch_finish(ctx, to, cells, pairs, kKe, E, E + nz, E + 2 * nz, nullptr);
   if (st) return st;
   if (nn) hipLaunchKernelGGL(k_scatter_nn, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, to.perm, nn_s, sperm + nz, nn);
   OBEM_HIP(ctx, hipGetLastError());
