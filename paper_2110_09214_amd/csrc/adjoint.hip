@@ -40,45 +40,33 @@ __device__ __forceinline__ void neum(float &s, float &c, float v) {
 
 // FP64 closed-form Jacobian of a unit-density cell contracted with w:
 //   gtw = G^T w = sum_e (m_e . w) grad f_e + (n . w) grad Omega
-// and ie_w = w . IE.  P[k] = vertex k minus the target.
+// and ie_w = w . IE.  P[k] = vertex k minus the target.  With f = log(a / b)
+// (edge_f) and C = 2 L / (a b),
+//   grad f_e = C (Pm/Rm + Pp/Rp),   grad Omega = sum_e (t_e x Pm) C (1/Rm + 1/Rp),
+// sums of terms of one sign in the far range: at 24-48 D the relative error
+// is 4.3e-14 (rms against 128 bits) where differences of reciprocals had
+// 1.2e-12.
 __device__ __forceinline__ void cell_grad_closed(const d3 P[3], d3 n, double twoarea, const CellEdges &E, d3 w,
                                                  d3 &gtw, double &ie_w) {
-  double R[3] = {norm3(P[0]), norm3(P[1]), norm3(P[2])};
-  double h = -dot3(P[0], n);
-  double num = twoarea * h;
-  double Om = 0.0;
-  if (num != 0.0) {
-    double den = R[0] * R[1] * R[2] + dot3(P[0], P[1]) * R[2] + dot3(P[0], P[2]) * R[1] + dot3(P[1], P[2]) * R[0];
-    Om = 2.0 * atan2(num, den);
-  }
+  double R[3];
+  const double h = -dot3(P[0], n);
+  const double Om = cell_omega(P, h, twoarea, R);
   const double nw = dot3(n, w);
   ie_w = nw * Om;
   gtw = mk3(0, 0, 0);
   d3 gO = mk3(0, 0, 0);
+  const double iR[3] = {rcp_f64(R[0]), rcp_f64(R[1]), rcp_f64(R[2])};
 #pragma unroll
   for (int e = 0; e < 3; ++e) {
     const int e1 = (e + 1) % 3;
-    const d3 t = E.t[e], m = E.m[e];
     const double L = E.L[e];
-    double lm, R0sq;
-    const double f = edge_log(P[e], R[e], R[e1], t, L, &lm, &R0sq);
-    const double lp = lm + L;
-    const double Rm = R[e], Rp = R[e1];
-    // (l+/R+ - l-/R-)/R0^2 without cancellation near the edge line
-    double Dd;
-    if (lm >= 0.0)
-      Dd = 1.0 / (Rm * (Rm + lm)) - 1.0 / (Rp * (Rp + lp));
-    else if (lp <= 0.0)
-      Dd = 1.0 / (Rp * (Rp - lp)) - 1.0 / (Rm * (Rm - lm));
-    else
-      Dd = (lp / Rp - lm / Rm) / R0sq;
-    const double inv_diff = -L * (lp + lm) / ((Rp + Rm) * Rp * Rm);  // 1/R+ - 1/R-
-    const d3 dvec = t * lm - P[e];                                     // target minus its foot on the edge line
-    const d3 gf = dvec * (-Dd) + t * (-inv_diff);
-    const double mw = dot3(m, w);
-    ie_w += mw * f;
-    gtw = gtw + gf * mw;
-    gO = gO + cross3(t, dvec) * (-Dd);
+    double b;
+    const double f = edge_f(P[e], R[e], R[e1], E.t[e], L, &b);
+    const double C = 2.0 * L * rcp_f64((R[e] + R[e1] + L) * b);
+    const double mw = dot3(E.m[e], w);
+    ie_w = fma(mw, f, ie_w);
+    gtw = gtw + (P[e] * iR[e] + P[e1] * iR[e1]) * (C * mw);
+    gO = gO + cross3(E.t[e], P[e]) * (C * (iR[e] + iR[e1]));
   }
   gtw = gtw + gO * nw;
 }
@@ -590,7 +578,7 @@ __global__ __launch_bounds__(kT) void k_panel_bwd_fp64(int n_t, const double *__
             const double ex = x0 - f[(size_t)(MF_Q7 + 3 * q) * N + kk];
             const double ey = x1 - f[(size_t)(MF_Q7 + 3 * q + 1) * N + kk];
             const double ez = x2 - f[(size_t)(MF_Q7 + 3 * q + 2) * N + kk];
-            const double ri = 1.0 / sqrt(fma(ex, ex, fma(ey, ey, ez * ez)));
+            const double ri = rsqrt_f64(fma(ex, ex, fma(ey, ey, ez * ez)));
             const double ri2 = ri * ri;
             const double a3 = aw * ri * ri2;
             const double dw = ex * w.x + ey * w.y + ez * w.z;
@@ -937,7 +925,7 @@ __global__ __launch_bounds__(kT) void k_pair_bwd_t_fp64(int n_t, const double *_
       const double4 s = S[jj];
       const double dx = x0 - s.x, dy = x1 - s.y, dz = x2 - s.z;
       const double rr = fma(dx, dx, fma(dy, dy, fma(dz, dz, soft2)));
-      double ri = 1.0 / sqrt(rr);
+      double ri = inv_sqrt_f64(rr);
       if (EXCL == 1) ri = rr > 0.0 ? ri : 0.0;
       if (EXCL == 2) ri = (jt + jj == self) ? 0.0 : ri;
       double ax = s.w * wx, ay = s.w * wy, az = s.w * wz;
@@ -1019,7 +1007,7 @@ __global__ __launch_bounds__(kT) void k_pair_bwd_s(int n_s, const double *__rest
         const double4 wv = Wt[ii];
         const double dx = xv.x - q0, dy = xv.y - q1, dz = xv.z - q2;
         const double rr = fma(dx, dx, fma(dy, dy, fma(dz, dz, soft2)));
-        double ri = 1.0 / sqrt(rr);
+        double ri = inv_sqrt_f64(rr);
         if (EXCL == 1) ri = rr > 0.0 ? ri : 0.0;
         const double ri2 = ri * ri, ri3 = ri * ri2;
         const double dw = fma(dx, wv.x, fma(dy, wv.y, dz * wv.z));

@@ -689,16 +689,6 @@ __device__ __forceinline__ double readlane_f64(double v, int k) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// 1/sqrt(x) for x > 0: the hardware estimate refined by two Newton steps
-// y <- y + y (1/2 - x/2 y^2) (quadratic convergence; a few ulp at the end).
-__device__ __forceinline__ double rsqrt_f64(double x) {
-  const double h = 0.5 * x;
-  double y = __builtin_amdgcn_rsq(x);
-  y = fma(y, fma(-h * y, y, 0.5), y);
-  y = fma(y, fma(-h * y, y, 0.5), y);
-  return y;
-}
-
 template <bool WANT_V>
 __global__ __launch_bounds__(kThreads) void k_panel_fp64(int n_t, const double *__restrict__ xs, int N,
                                                          const double *__restrict__ f,
@@ -1593,7 +1583,7 @@ __global__ __launch_bounds__(kThreads) void k_pair_fp64(int n_t, const double *_
       const double dx = x0 - s.x, dy = x1 - s.y, dz = x2 - s.z;
       const double dd = fma(dx, dx, fma(dy, dy, dz * dz));
       const double rr = dd + soft2;
-      double ri = 1.0 / sqrt(rr);
+      double ri = inv_sqrt_f64(rr);
       if (EXCL == 1) ri = rr > 0.0 ? ri : 0.0;
       if (EXCL == 2) ri = (jt + jj == self) ? 0.0 : ri;
       const double qr = s.w * ri;

@@ -342,7 +342,7 @@ __global__ __launch_bounds__(kTI) void k_influence_fp64(int N, const double *__r
           for (int m = 0; m < 7; ++m) {
             const double w = area * ((m == 0) ? Rule7::w0 : (m < 4 ? Rule7::wa : Rule7::wb));
             const double ax = p.x - q7[3 * m], ay = p.y - q7[3 * m + 1], az = p.z - q7[3 * m + 2];
-            const double ri = 1.0 / sqrt(fma(ax, ax, fma(ay, ay, az * az)));
+            const double ri = rsqrt_f64(fma(ax, ax, fma(ay, ay, az * az)));
             const double wr = p.w * w * ri;
             const double s = wr * ri * ri;
             sv += wr;

@@ -32,3 +32,27 @@ def test_matrix_passes_at_odd_sizes(ctx, orc, n):
     for refine in (0, 1):  # without info: nothing read back on the host
         s, _ = B.bem_solve_charges(ctx, bm, dev(m.rhs), max_refine=refine, want_info=False)
         assert rel_l2(host(s), ref) <= 1e-11
+
+
+@pytest.mark.parametrize("scale", [1e-2, 0.05, 0.2, 0.5, 0.9, 1.1, 2.9, 11.0, 47.0])
+def test_closed_form_around_its_switches(ctx, orc, scale):
+    """One cell's closed form on both sides of the switch to the distances
+    from the edge's line (sum of the two distances 1.25 edge lengths), of the
+    arctangent's (numerator a quarter of the denominator) and in the far
+    range: targets at scale diameters around the edges, the vertices and the
+    centroid.  The form's own error is below 1e-12 up to 48 diameters, the
+    rounding of the inputs adds 2^-53 |x| / distance < 1e-13."""
+    rng = np.random.default_rng(int(1000 * scale))
+    a, b, c = np.array([[0.3, -0.2, 0.1], [1.1, 0.1, -0.2], [0.5, 0.9, 0.3]])[:, None, :] * 1e-5
+    D = max(np.linalg.norm(b - a), np.linalg.norm(c - b), np.linalg.norm(a - c))
+    u = rng.normal(size=(192, 3))
+    u /= np.linalg.norm(u, axis=1, keepdims=True)
+    t = rng.uniform(size=(64, 1))
+    base = np.concatenate([a + t * (b - a), np.repeat(c, 64, 0), np.repeat((a + b + c) / 3, 64, 0)])
+    x = base + scale * D * u
+    m = W.Mesh(a, b, c, np.zeros(1, np.int8), np.ones(1), np.ones(1), np.zeros(1))
+    sig = np.array([1e-6])
+    E, V = B.field_eval(ctx, bind(ctx, m), dev(sig), None, None, dev(x), 0.0, B.OBEM_FP64, want_v=True)
+    Er, Vr = orc.panel_field(x, a, b, c, sig, want_v=True)
+    assert (np.linalg.norm(host(E) - Er, axis=1) / np.linalg.norm(Er, axis=1)).max() <= 2e-12
+    assert (np.abs(host(V) - Vr) / np.abs(Vr)).max() <= 2e-12
