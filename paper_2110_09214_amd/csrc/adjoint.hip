@@ -46,27 +46,27 @@ __device__ __forceinline__ void neum(float &s, float &c, float v) {
 // sums of terms of one sign in the far range: at 24-48 D the relative error
 // is 4.3e-14 (rms against 128 bits) where differences of reciprocals had
 // 1.2e-12.
-__device__ __forceinline__ void cell_grad_closed(const d3 P[3], d3 n, double twoarea, const CellEdges &E, d3 w,
-                                                 d3 &gtw, double &ie_w) {
-  double R[3];
-  const double h = -dot3(P[0], n);
-  const double Om = cell_omega(P, h, twoarea, R);
-  const double nw = dot3(n, w);
-  ie_w = nw * Om;
+__device__ __forceinline__ void cell_grad_closed(const double *__restrict__ rec, d3 x, d3 w, d3 &gtw, double &ie_w) {
+  CellSeen s = cell_seen(rec, x);
+  const double nw = dot3(s.n, w);
+  ie_w = nw * solid_angle(s.num, s.den);
   gtw = mk3(0, 0, 0);
   d3 gO = mk3(0, 0, 0);
-  const double iR[3] = {rcp_f64(R[0]), rcp_f64(R[1]), rcp_f64(R[2])};
-#pragma unroll
+#pragma unroll 1
   for (int e = 0; e < 3; ++e) {
-    const int e1 = (e + 1) % 3;
-    const double L = E.L[e];
+    double d[8];
+    load_doubles<8>(rec + CR_EDGE + CR_EDGE_SIZE * e, d);
+    const double L = d[0];
+    const d3 t = mk3(d[1], d[2], d[3]);
     double b;
-    const double f = edge_f(P[e], R[e], R[e1], E.t[e], L, &b);
-    const double C = 2.0 * L * rcp_f64((R[e] + R[e1] + L) * b);
-    const double mw = dot3(E.m[e], w);
+    const double f = edge_f(s.P[0], s.R[0], s.R[1], t, L, &b);
+    const double C = 2.0 * L * rcp_f64((s.R[0] + s.R[1] + L) * b);
+    const double im = rcp_f64(s.R[0]), ip = rcp_f64(s.R[1]);
+    const double mw = dot3(mk3(d[4], d[5], d[6]), w);
     ie_w = fma(mw, f, ie_w);
-    gtw = gtw + (P[e] * iR[e] + P[e1] * iR[e1]) * (C * mw);
-    gO = gO + cross3(E.t[e], P[e]) * (C * (iR[e] + iR[e1]));
+    gtw = gtw + (s.P[0] * im + s.P[1] * ip) * (C * mw);
+    gO = gO + cross3(t, s.P[0]) * (C * (im + ip));
+    rotate3(s);
   }
   gtw = gtw + gO * nw;
 }
@@ -429,6 +429,7 @@ __global__ __launch_bounds__(kT) void k_panel_bwd_mixed(int n_t, const double *_
 __global__ __launch_bounds__(kT) void k_panel_bwd_near(int n_t, const double *__restrict__ xs,
                                                        const double *__restrict__ ws, int N,
                                                        const double *__restrict__ f,
+                                                       const double *__restrict__ rec,
                                                        const double *__restrict__ sigma,
                                                        const double *__restrict__ tiles, int want_x, int cchunk,
                                                        double *gxp, double *gsp) {
@@ -506,13 +507,8 @@ __global__ __launch_bounds__(kT) void k_panel_bwd_near(int n_t, const double *__
       if (!__syncthreads_or(nearp)) continue;
       double un = 0.0;
       if (nearp) {
-        d3 P[3];
-        P[0] = mk3(f[(size_t)MF_AX * N + kk] - x0, f[(size_t)MF_AY * N + kk] - x1, f[(size_t)MF_AZ * N + kk] - x2);
-        P[1] = mk3(f[(size_t)MF_BX * N + kk] - x0, f[(size_t)MF_BY * N + kk] - x1, f[(size_t)MF_BZ * N + kk] - x2);
-        P[2] = mk3(f[(size_t)MF_CX * N + kk] - x0, f[(size_t)MF_CY * N + kk] - x1, f[(size_t)MF_CZ * N + kk] - x2);
-        const d3 nn = mk3(f[(size_t)MF_NX * N + kk], f[(size_t)MF_NY * N + kk], f[(size_t)MF_NZ * N + kk]);
         d3 g;
-        cell_grad_closed(P, nn, 2.0 * f[(size_t)MF_AREA * N + kk], cell_edges(f, N, kk), w, g, un);
+        cell_grad_closed(rec + (size_t)kk * CR_COUNT, mk3(x0, x1, x2), w, g, un);
         const double sg = sigma[kk];
         nx = fma(sg, g.x, nx);
         ny = fma(sg, g.y, ny);
@@ -537,6 +533,7 @@ __global__ __launch_bounds__(kT) void k_panel_bwd_near(int n_t, const double *__
 __global__ __launch_bounds__(kT) void k_panel_bwd_fp64(int n_t, const double *__restrict__ xs,
                                                        const double *__restrict__ ws, int N,
                                                        const double *__restrict__ f,
+                                                       const double *__restrict__ rec,
                                                        const double *__restrict__ sigma, int want_x, int cchunk,
                                                        double *gxp, double *gsp) {
   __shared__ double red[4][kPTb];
@@ -561,12 +558,7 @@ __global__ __launch_bounds__(kT) void k_panel_bwd_fp64(int n_t, const double *__
       double u = 0.0;
       if (!__all(quad)) {
         if (!quad) {
-          d3 P[3];
-          P[0] = mk3(f[(size_t)MF_AX * N + kk] - x0, f[(size_t)MF_AY * N + kk] - x1, f[(size_t)MF_AZ * N + kk] - x2);
-          P[1] = mk3(f[(size_t)MF_BX * N + kk] - x0, f[(size_t)MF_BY * N + kk] - x1, f[(size_t)MF_BZ * N + kk] - x2);
-          P[2] = mk3(f[(size_t)MF_CX * N + kk] - x0, f[(size_t)MF_CY * N + kk] - x1, f[(size_t)MF_CZ * N + kk] - x2);
-          const d3 nn = mk3(f[(size_t)MF_NX * N + kk], f[(size_t)MF_NY * N + kk], f[(size_t)MF_NZ * N + kk]);
-          cell_grad_closed(P, nn, 2.0 * f[(size_t)MF_AREA * N + kk], cell_edges(f, N, kk), w, g, u);
+          cell_grad_closed(rec + (size_t)kk * CR_COUNT, mk3(x0, x1, x2), w, g, u);
         }
       }
       if (__any(quad)) {
@@ -1157,7 +1149,7 @@ extern "C" obem_status field_eval_backward(obem_ctx *ctx, const obem_meshh *mesh
                          sigma, 1, cchunk, gxp, gsp);
       // the near kernel of split y adds into the same slot (and into gsp for
       // the cells of its range), then the slots are added in split order
-      hipLaunchKernelGGL(k_panel_bwd_near, dim3(bt, ns), dim3(kT), 0, ctx->stream, n_t, to.xs, wsrt, N, mesh->f,
+      hipLaunchKernelGGL(k_panel_bwd_near, dim3(bt, ns), dim3(kT), 0, ctx->stream, n_t, to.xs, wsrt, N, mesh->f, mesh->rec,
                          sigma, mesh->tiles, 1, cchunk, gxp, gsp);
       if (ns > 1) launch_slot_sum(ctx, n_t, 3, Slots{gxp, ns}, false, gx);
     } else {
@@ -1172,7 +1164,7 @@ extern "C" obem_status field_eval_backward(obem_ctx *ctx, const obem_meshh *mesh
         gxp = (double *)ws_get(ctx, WS_PANEL, sizeof(double) * 3 * (size_t)n_t * ns);
         if (!gxp) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
       }
-      hipLaunchKernelGGL(k_panel_bwd_fp64, dim3(bt, ns), dim3(kT), 0, ctx->stream, n_t, to.xs, wsrt, N, mesh->f,
+      hipLaunchKernelGGL(k_panel_bwd_fp64, dim3(bt, ns), dim3(kT), 0, ctx->stream, n_t, to.xs, wsrt, N, mesh->f, mesh->rec,
                          sigma, 1, cchunk, gxp, gsp);
       if (ns > 1) launch_slot_sum(ctx, n_t, 3, Slots{gxp, ns}, false, gx);
     }

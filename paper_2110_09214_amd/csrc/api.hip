@@ -117,7 +117,7 @@ bool is_device_ptr(const void *p) {
 // ---------------------------------------------------------------------------
 // Mesh derivation: normal, area, centroid, diameter, quadrature points.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_mesh_derive(int n, double *f, const int8_t *kind, const double *e1,
+__global__ __launch_bounds__(256) void k_mesh_derive(int n, double *f, double *rec, const int8_t *kind, const double *e1,
                                                      const double *e2, int *bad) {
   const int k = blockIdx.x * 256 + threadIdx.x;
   if (k >= n) return;
@@ -183,21 +183,32 @@ __global__ __launch_bounds__(256) void k_mesh_derive(int n, double *f, const int
     F(MF_Q4 + 3 * q + 1) = p.y;
     F(MF_Q4 + 3 * q + 2) = p.z;
   }
-  // edge data of the closed form: unit tangent, length, t x n
+  // the closed form's record: unit tangent, length, t x n
   const d3 v[3] = {a, b, c};
+  double *r = rec + (size_t)k * CR_COUNT;
   for (int e = 0; e < 3; ++e) {
     d3 t = v[(e + 1) % 3] - v[e];
     const double Le = norm3(t);
     t = t * (1.0 / Le);
     const d3 m = cross3(t, nn);
-    F(MF_T + 3 * e) = t.x;
-    F(MF_T + 3 * e + 1) = t.y;
-    F(MF_T + 3 * e + 2) = t.z;
-    F(MF_EL + e) = Le;
-    F(MF_M + 3 * e) = m.x;
-    F(MF_M + 3 * e + 1) = m.y;
-    F(MF_M + 3 * e + 2) = m.z;
+    r[3 * e] = v[e].x;
+    r[3 * e + 1] = v[e].y;
+    r[3 * e + 2] = v[e].z;
+    double *re = r + CR_EDGE + CR_EDGE_SIZE * e;
+    re[0] = Le;
+    re[1] = t.x;
+    re[2] = t.y;
+    re[3] = t.z;
+    re[4] = m.x;
+    re[5] = m.y;
+    re[6] = m.z;
+    re[7] = 0.0;
   }
+  r[CR_N] = nn.x;
+  r[CR_N + 1] = nn.y;
+  r[CR_N + 2] = nn.z;
+  r[CR_2A] = 2.0 * F(MF_AREA);
+  for (int u = CR_2A + 1; u < CR_EDGE; ++u) r[u] = 0.0;
 }
 
 // Zone bounding spheres of consecutive 64-cell tiles: centre = mean
@@ -426,6 +437,7 @@ static obem_status bind_fill(obem_ctx *ctx, const obem_mesh *mesh, obem_meshh *m
   const double *v[9] = {mesh->ax, mesh->ay, mesh->az, mesh->bx, mesh->by, mesh->bz, mesh->cx, mesh->cy, mesh->cz};
   const int ntile = (int)((n + 63) / 64);
   if (hipMalloc(&m->f, sizeof(double) * MF_COUNT * (size_t)n) != hipSuccess ||
+      hipMalloc(&m->rec, sizeof(double) * CR_COUNT * (size_t)n) != hipSuccess ||
       hipMalloc(&m->kind, (size_t)n) != hipSuccess || hipMalloc(&m->tiles, sizeof(double) * 4 * ntile) != hipSuccess ||
       hipMalloc(&m->tiles48, sizeof(double) * 4 * ntile) != hipSuccess ||
       hipMalloc(&m->order, sizeof(int32_t) * n) != hipSuccess) {
@@ -439,7 +451,7 @@ static obem_status bind_fill(obem_ctx *ctx, const obem_mesh *mesh, obem_meshh *m
   if (!bad) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
   OBEM_HIP(ctx, hipMemsetAsync(bad, 0, sizeof(int), ctx->stream));
   hipLaunchKernelGGL(k_mesh_derive, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, ctx->stream, (int)n, m->f,
-                     m->kind, mesh->eps_r1, mesh->eps_r2, bad);
+                     m->rec, m->kind, mesh->eps_r1, mesh->eps_r2, bad);
   OBEM_HIP(ctx, hipGetLastError());
   hipLaunchKernelGGL(k_tile_spheres, dim3(ntile), dim3(64), 0, ctx->stream, (int)n, m->f, kNearMixed, m->tiles);
   hipLaunchKernelGGL(k_tile_spheres, dim3(ntile), dim3(64), 0, ctx->stream, (int)n, m->f, kQuadFp64, m->tiles48);
@@ -477,6 +489,7 @@ static obem_status bind_fill(obem_ctx *ctx, const obem_mesh *mesh, obem_meshh *m
 
 static void free_mesh(obem_meshh *m) {
   (void)hipFree(m->f);
+  (void)hipFree(m->rec);
   (void)hipFree(m->kind);
   (void)hipFree(m->tiles);
   (void)hipFree(m->tiles48);

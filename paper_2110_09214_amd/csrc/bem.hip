@@ -33,7 +33,7 @@ namespace obem {
 // 7-point rule, nearer ones the closed form.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_bem_assemble(int N, const double *__restrict__ f,
-                                                      const int8_t *__restrict__ kind, double *A) {
+                                                      const double *__restrict__ rec, const int8_t *__restrict__ kind, double *A) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= N) return;
   const double x0 = f[(size_t)MF_GX * N + i], x1 = f[(size_t)MF_GY * N + i], x2 = f[(size_t)MF_GZ * N + i];
@@ -73,12 +73,7 @@ __global__ __launch_bounds__(256) void k_bem_assemble(int N, const double *__res
           ie = ie + mk3(qx, qy, qz) * s;
         }
       } else {
-        d3 P[3];
-        P[0] = mk3(f[(size_t)MF_AX * N + j] - x0, f[(size_t)MF_AY * N + j] - x1, f[(size_t)MF_AZ * N + j] - x2);
-        P[1] = mk3(f[(size_t)MF_BX * N + j] - x0, f[(size_t)MF_BY * N + j] - x1, f[(size_t)MF_BZ * N + j] - x2);
-        P[2] = mk3(f[(size_t)MF_CX * N + j] - x0, f[(size_t)MF_CY * N + j] - x1, f[(size_t)MF_CZ * N + j] - x2);
-        const d3 n = mk3(f[(size_t)MF_NX * N + j], f[(size_t)MF_NY * N + j], f[(size_t)MF_NZ * N + j]);
-        cell_closed_form<true>(P, n, 2.0 * f[(size_t)MF_AREA * N + j], cell_edges(f, N, j), ie, iv);
+        cell_closed_form<true>(rec + (size_t)j * CR_COUNT, mk3(x0, x1, x2), ie, iv);
       }
       val = dd ? coef * dot3(ni, ie) : coef * iv;
     }
@@ -404,7 +399,7 @@ obem_status bem_factor(obem_ctx *ctx, obem_meshh *m) {
   const int gy = std::min(N, 65535);
   {
     OBEM_PROF(ctx, "assemble");
-    hipLaunchKernelGGL(k_bem_assemble, dim3(nb(N), gy), dim3(256), 0, ctx->stream, N, m->f, m->kind, m->A);
+    hipLaunchKernelGGL(k_bem_assemble, dim3(nb(N), gy), dim3(256), 0, ctx->stream, N, m->f, m->rec, m->kind, m->A);
   }
   OBEM_HIP(ctx, hipGetLastError());
   // infinity norm of A (for the backward error)

@@ -58,6 +58,47 @@ __device__ __forceinline__ double rsqrt_f64(double x) {
   return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
+// a b + k for a constant k: k in a scalar register pair.  The compiler copies
+// a polynomial's constants to vector registers instead (one more instruction
+// per term, and the registers).
+__device__ __forceinline__ double fma_k(double a, double b, double k) {
+  double r;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(k));
+  return r;
+}
+// (atanh(s) - s) / s^3 on s^2 = z <= 0.0297 and (WIDE) z <= 0.075, and
+// (atan(t) - t) / t^3 on t^2 = u <= 1/16: minimax polynomials, relative error
+// of the functions 5e-18, 3e-18 and 2e-17.
+template <bool WIDE>
+__device__ __forceinline__ double atanh_tail(double z) {
+  double q;
+  if (WIDE) {
+    q = fma_k(z, 0.072060841267327696066, 0.055923049841696995365);
+    q = fma_k(q, z, 0.066893222591322001645);
+    q = fma_k(q, z, 0.076912886123458226635);
+    q = fma_k(q, z, 0.09090935855713595118);
+    q = fma_k(q, z, 0.11111110717632652524);
+    q = fma_k(q, z, 0.14285714288605414739);
+    q = fma_k(q, z, 0.19999999999991834572);
+    return fma_k(q, z, 0.33333333333333337125);
+  }
+  q = fma_k(z, 0.073145028437917779823, 0.076653489385718816166);
+  q = fma_k(q, z, 0.090914600915225965373);
+  q = fma_k(q, z, 0.11111105352279153539);
+  q = fma_k(q, z, 0.14285714314319351255);
+  q = fma_k(q, z, 0.19999999999946780889);
+  return fma_k(q, z, 0.33333333333333349485);
+}
+__device__ __forceinline__ double atan_tail(double u) {
+  double q = fma_k(u, 0.04726845190252479579, -0.06554434847623053629);
+  q = fma_k(q, u, 0.076865024041207992868);
+  q = fma_k(q, u, -0.090907412155468317155);
+  q = fma_k(q, u, 0.11111108462732517272);
+  q = fma_k(q, u, -0.14285714265141588082);
+  q = fma_k(q, u, 0.199999999999390121);
+  return fma_k(q, u, -0.33333333333333303632);
+}
+
 // 1/sqrt(x) of a squared distance that may overflow (x > 0): 0 beyond
 // 1e300, where the estimate's product would be infinity times zero.
 __device__ __forceinline__ double inv_sqrt_f64(double x) {
@@ -70,7 +111,7 @@ __device__ __forceinline__ double inv_sqrt_f64(double x) {
 // b = S - L,
 //   f = log(a / b),
 // as e ln 2 + 2 atanh(s), s = (a 2^-e - b) / (a 2^-e + b), |s| <= 0.172, the
-// atanh by its degree-13 minimax polynomial (relative error 5e-18): one
+// atanh by a degree-15 polynomial: one
 // quotient and one polynomial for every target, where log1p of one of four
 // quotients (by the position of the target's foot) ran up to four times in a
 // wave.  s is formed from S and L, exact in the small difference far from the
@@ -96,74 +137,134 @@ __device__ __forceinline__ double edge_f(d3 Pm, double Rm, double Rp, d3 t, doub
   const double num = close ? fma(a, k, -b) : fma(-S, 1.0 - k, L * (1.0 + k));
   const double den = close ? fma(a, k, b) : fma(S, 1.0 + k, -L * (1.0 - k));
   const double s = div_f64(num, den), z = s * s;
-  double q = 0.073145028437917779823;
-  q = fma(q, z, 0.076653489385718816166);
-  q = fma(q, z, 0.090914600915225965373);
-  q = fma(q, z, 0.11111105352279153539);
-  q = fma(q, z, 0.14285714314319351255);
-  q = fma(q, z, 0.19999999999946780889);
-  q = fma(q, z, 0.33333333333333349485);
   const double s2 = s + s;
-  const double f = fma((double)e, 0.69314718055994530942, fma(s2 * z, q, s2));
+  const double f = fma((double)e, 0.69314718055994530942, fma(s2 * z, atanh_tail<false>(z), s2));
   if (b_out) *b_out = b;
   return b == 0.0 ? (double)INFINITY : f;
 }
 
-// Solid angle 2 atan2(num, den): the minimax polynomial of atan (relative
-// error 2e-17 with degree 15 up to 1/4) where |num| <= den / 4, which holds
+// Large angles, rare: kept out of line, since the library's constants
+// otherwise take registers of every wave of the kernel.
+static __device__ __attribute__((noinline)) double wide_angle(double num, double den) { return 2.0 * atan2(num, den); }
+
+// Solid angle 2 atan2(num, den): by atan_tail where |num| <= den / 4, which holds
 // for every target farther than about a diameter; atan2 otherwise.
 __device__ __forceinline__ double solid_angle(double num, double den) {
   if (fabs(num) <= 0.25 * den) {
     if (num == 0.0) return 0.0;
     const double z = div_f64(num, den), u = z * z;
-    double q = 0.04726845190252479579;
-    q = fma(q, u, -0.06554434847623053629);
-    q = fma(q, u, 0.076865024041207992868);
-    q = fma(q, u, -0.090907412155468317155);
-    q = fma(q, u, 0.11111108462732517272);
-    q = fma(q, u, -0.14285714265141588082);
-    q = fma(q, u, 0.199999999999390121);
-    q = fma(q, u, -0.33333333333333303632);
-    return 2.0 * fma(z * u, q, z);
+    return 2.0 * fma(z * u, atan_tail(u), z);
   }
-  return num != 0.0 ? 2.0 * atan2(num, den) : 0.0;
+  return num != 0.0 ? wide_angle(num, den) : 0.0;
 }
 
-// Edge data of a cell, made once per cell when the mesh is bound: unit
-// tangent t_e of edge e (vertex e to vertex e + 1), its length and the
-// in-plane outward normal m_e = t_e x n.
-struct CellEdges {
-  d3 t[3], m[3];
-  double L[3];
-};
+// The closed form's data of one cell, contiguous (cell-major): vertices,
+// unit normal, twice the area (CR_*), then per edge e = a->b, b->c, c->a its
+// length, unit tangent t_e and in-plane outward normal t_e x n, with pads to
+// whole 16-byte loads.  One cell is then consecutive wide loads of a lane or
+// scalar loads of a wave, instead of 34 loads from as many arrays.
+enum CellRec { CR_V = 0, CR_N = 9, CR_2A = 12, CR_EDGE = 16, CR_EDGE_SIZE = 8, CR_COUNT = 40 };
 
-// Distances of the vertices and the signed solid angle of a cell.
-__device__ __forceinline__ double cell_omega(const d3 P[3], double h, double twoarea, double R[3]) {
+// n (even) consecutive doubles at 16-byte aligned p.
+template <int n>
+__device__ __forceinline__ void load_doubles(const double *__restrict__ p, double *d) {
 #pragma unroll
-  for (int k = 0; k < 3; ++k) R[k] = sqrt_f64(dot3(P[k], P[k]));
-  const double den = fma(R[0] * R[1], R[2],
-                         fma(dot3(P[0], P[1]), R[2], fma(dot3(P[0], P[2]), R[1], dot3(P[1], P[2]) * R[0])));
-  return solid_angle(twoarea * h, den);
+  for (int i = 0; i < n / 2; ++i) {
+    const double2 t = reinterpret_cast<const double2 *>(p)[i];
+    d[2 * i] = t.x;
+    d[2 * i + 1] = t.y;
+  }
 }
 
-// Closed form in FP64.  P[k] = vertex k minus the target; n = unit normal;
-// twoarea = |(b-a)x(c-a)|.  A target exactly in the plane gets Omega = 0 (the
-// principal value of the normal field).  Bound by FP64 operations.  Against
-// 128-bit arithmetic the relative error of IE is 3.2e-15 (rms) at 1.5-3 D and
-// 4.5e-14 at 24-48 D (3.4e-15 and 5.6e-14 for the log1p form it replaces).
+// The vertices of a cell's record (CellRec) minus x, their distances, the
+// normal, minus the height, and num / den of the solid angle's tangent.
+struct CellSeen {
+  d3 P[3], n;
+  double R[3], mh, num, den;
+};
+__device__ __forceinline__ CellSeen cell_seen(const double *__restrict__ rec, d3 x) {
+  CellSeen s;
+  double d[14];
+  load_doubles<14>(rec, d);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    s.P[k] = mk3(d[3 * k], d[3 * k + 1], d[3 * k + 2]) - x;
+    s.R[k] = sqrt_f64(dot3(s.P[k], s.P[k]));
+  }
+  s.n = mk3(d[9], d[10], d[11]);
+  s.mh = dot3(s.P[0], s.n);
+  s.num = -d[12] * s.mh;
+  s.den = fma(s.R[0] * s.R[1], s.R[2],
+              fma(dot3(s.P[0], s.P[1]), s.R[2],
+                  fma(dot3(s.P[0], s.P[2]), s.R[1], dot3(s.P[1], s.P[2]) * s.R[0])));
+  return s;
+}
+// Next edge: rotates the vertices.
+__device__ __forceinline__ void rotate3(CellSeen &s) {
+  const d3 p = s.P[0];
+  const double r = s.R[0];
+  s.P[0] = s.P[1];
+  s.R[0] = s.R[1];
+  s.P[1] = s.P[2];
+  s.R[1] = s.R[2];
+  s.P[2] = p;
+  s.R[2] = r;
+}
+
+// Closed form in FP64 of the cell with record rec at x.  A target exactly in
+// the plane gets Omega = 0 (the principal value of the normal field).  Bound
+// by FP64 operations; the edges run in a loop, each loading its own data,
+// since unrolled they take over 200 registers and two waves per SIMD.
+// Against 128-bit arithmetic the relative error of IE is 3.2e-15 (rms) at
+// 1.5-3 D and 4.5e-14 at 24-48 D (3.4e-15 and 5.6e-14 for the log1p form it
+// replaces).
 template <bool WANT_V>
-__device__ __forceinline__ void cell_closed_form(const d3 P[3], d3 n, double twoarea, const CellEdges &E, d3 &IE,
-                                                 double &IV) {
-  double R[3];
-  const double h = -dot3(P[0], n);
-  const double Om = cell_omega(P, h, twoarea, R);
-  IE = n * Om;
-  IV = -h * Om;
+__device__ __forceinline__ void cell_closed_form(const double *__restrict__ rec, d3 x, d3 &IE, double &IV) {
+  CellSeen s = cell_seen(rec, x);
+  const double Om = solid_angle(s.num, s.den);
+  IE = s.n * Om;
+  IV = s.mh * Om;
+#pragma unroll 1
+  for (int e = 0; e < 3; ++e) {
+    double d[8];
+    load_doubles<8>(rec + CR_EDGE + CR_EDGE_SIZE * e, d);
+    const double f = edge_f(s.P[0], s.R[0], s.R[1], mk3(d[1], d[2], d[3]), d[0], nullptr);
+    const d3 m = mk3(d[4], d[5], d[6]);
+    IE = IE + m * f;
+    if (WANT_V) IV = fma(dot3(m, s.P[0]), f, IV);
+    rotate3(s);
+  }
+}
+
+// The same for x at least kMidForm diameters D from the centroid: the
+// vertices are within 2 D / 3 of it, so each edge has L / S < 0.273 (f = 2
+// atanh(L / S), within the polynomial's range) and |num| < den / 4: no case
+// is left to tell apart, and the four quotients share one reciprocal.
+constexpr double kMidForm = 2.5;
+template <bool WANT_V>
+__device__ __forceinline__ void cell_mid_form(const double *__restrict__ rec, d3 x, d3 &IE, double &IV) {
+  const CellSeen s = cell_seen(rec, x);
+  const double S0 = s.R[0] + s.R[1], S1 = s.R[1] + s.R[2], S2 = s.R[2] + s.R[0];
+  const double p01 = S0 * S1, p23 = S2 * s.den, r = rcp_f64(p01 * p23);
+  const double r01 = r * p23, r23 = r * p01;
+  auto quot = [](double n, double d, double rd) {
+    const double q = n * rd;
+    return fma(fma(-d, q, n), rd, q);
+  };
+  const double z = quot(s.num, s.den, r23 * S2), u = z * z;
+  const double Om = 2.0 * fma(z * u, atan_tail(u), z);
+  IE = s.n * Om;
+  IV = s.mh * Om;
+  const double S[3] = {S0, S1, S2}, iS[3] = {r01 * S1, r01 * S0, r23 * s.den};
 #pragma unroll
   for (int e = 0; e < 3; ++e) {
-    const double f = edge_f(P[e], R[e], R[(e + 1) % 3], E.t[e], E.L[e], nullptr);
-    IE = IE + E.m[e] * f;
-    if (WANT_V) IV += dot3(E.m[e], P[e]) * f;
+    double d[8];
+    load_doubles<8>(rec + CR_EDGE + CR_EDGE_SIZE * e, d);
+    const double t = quot(d[0], S[e], iS[e]), w = t * t, t2 = t + t;
+    const double f = fma(t2 * w, atanh_tail<true>(w), t2);
+    const d3 m = mk3(d[4], d[5], d[6]);
+    IE = IE + m * f;
+    if (WANT_V) IV = fma(dot3(m, s.P[e]), f, IV);
   }
 }
 

@@ -336,26 +336,6 @@ __device__ __forceinline__ void neumaier(float &s, float &c, float v) {
   s = t;
 }
 
-// Near cells: FP64 closed form from the FP64 master geometry.
-template <bool WANT_V>
-__device__ __forceinline__ void near_cell(const double *__restrict__ f, int N, int k, double sig, double x0,
-                                          double x1, double x2, double &ex, double &ey, double &ez,
-                                          double &ev) {
-  d3 P[3];
-  P[0] = mk3(f[MF_AX * (size_t)N + k] - x0, f[MF_AY * (size_t)N + k] - x1, f[MF_AZ * (size_t)N + k] - x2);
-  P[1] = mk3(f[MF_BX * (size_t)N + k] - x0, f[MF_BY * (size_t)N + k] - x1, f[MF_BZ * (size_t)N + k] - x2);
-  P[2] = mk3(f[MF_CX * (size_t)N + k] - x0, f[MF_CY * (size_t)N + k] - x1, f[MF_CZ * (size_t)N + k] - x2);
-  d3 n = mk3(f[MF_NX * (size_t)N + k], f[MF_NY * (size_t)N + k], f[MF_NZ * (size_t)N + k]);
-  double twoarea = 2.0 * f[MF_AREA * (size_t)N + k];
-  d3 IE;
-  double IV;
-  cell_closed_form<WANT_V>(P, n, twoarea, cell_edges(f, N, k), IE, IV);
-  ex = fma(sig, IE.x, ex);
-  ey = fma(sig, IE.y, ey);
-  ez = fma(sig, IE.z, ez);
-  if (WANT_V) ev = fma(sig, IV, ev);
-}
-
 template <bool WANT_V>
 // gridDim.y splits the cells into ranges of cchunk; split y writes its sums
 // to part + 4 n_t y (part = acc when there is one split).
@@ -466,7 +446,7 @@ __global__ __launch_bounds__(kThreads) void k_panel_mixed(int n_t, const double 
     // against the wave's sphere: lane k tests cell k, and the ballots give
     // the cells some lane may see within 40 D (4 points or finer), 16 D (6
     // or finer), 6 D (7 points) and 3 D (the per-lane path, which leaves the
-    // near pairs to k_panel_near).  Thresholds 1 % wide of the per-lane
+    // near pairs to k_panel_close).  Thresholds 1 % wide of the per-lane
     // ones, so that a cell not flagged near has no lane inside 3 D by the
     // per-lane test, and a coarser rule is never taken where a lane needs a
     // finer one.
@@ -528,7 +508,7 @@ __global__ __launch_bounds__(kThreads) void k_panel_mixed(int n_t, const double 
       const int k = __builtin_ctzll(mnear);
       const float4 g = T[k].c[0];
       const float R2 = dist2f(r0, r1, r2, g.x, g.y, g.z);
-      const bool nearp = R2 < g.w;  // taken by k_panel_near in FP64
+      const bool nearp = R2 < g.w;  // taken by k_panel_close in FP64
       const float4 h = T[k].c[1];
       const float4 h7 = T[k].c[7];    // {.., area sigma / 3, (6 D)^2, D}
       const float4 h10 = T[k].c[10];  // {.., w1, w2, (16 D)^2}
@@ -584,93 +564,7 @@ __global__ __launch_bounds__(kThreads) void k_panel_mixed(int n_t, const double 
   }
 }
 
-// FP64 near zone (R < 3 D) of the mixed mode, added to the far kernel's
-// partial sums of the same cell range (gridDim.y splits the cells as in the
-// far kernel, so small target sets still fill the chip).  Each wave bounds
-// its 64 targets by a sphere and skips whole 64-cell tiles whose near-zone
-// sphere (tile centre, max over cells of |c_k - centre| + 3 D_k, slightly
-// inflated) it does not meet; inside a tile the per-pair test is the far
-// kernel's FP32 test, so the two kernels partition the pairs.
-template <bool WANT_V>
-__global__ __launch_bounds__(kThreads) void k_panel_near(int n_t, const double *__restrict__ xs, int N,
-                                                         const double *__restrict__ f,
-                                                         const double *__restrict__ sigma,
-                                                         const double *__restrict__ tiles, int cchunk,
-                                                         double *part) {
-  const int tid = threadIdx.x;
-  const int i0 = blockIdx.x * kThreads;
-  const int i = i0 + tid;
-  const bool active = i < n_t;
-  const int ii = active ? i : n_t - 1;
-  const double c0 = xs[i0], c1 = xs[(size_t)n_t + i0], c2 = xs[2 * (size_t)n_t + i0];
-  const double x0 = xs[ii], x1 = xs[(size_t)n_t + ii], x2 = xs[2 * (size_t)n_t + ii];
-  const float r0 = (float)(x0 - c0), r1 = (float)(x1 - c1), r2 = (float)(x2 - c2);
-  // wave bounding sphere
-  double lo0 = x0, lo1 = x1, lo2 = x2, hi0 = x0, hi1 = x1, hi2 = x2;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    lo0 = fmin(lo0, __shfl_xor(lo0, o));
-    lo1 = fmin(lo1, __shfl_xor(lo1, o));
-    lo2 = fmin(lo2, __shfl_xor(lo2, o));
-    hi0 = fmax(hi0, __shfl_xor(hi0, o));
-    hi1 = fmax(hi1, __shfl_xor(hi1, o));
-    hi2 = fmax(hi2, __shfl_xor(hi2, o));
-  }
-  const double wc0 = 0.5 * (lo0 + hi0), wc1 = 0.5 * (lo1 + hi1), wc2 = 0.5 * (lo2 + hi2);
-  const double wr = 0.5 * sqrt((hi0 - lo0) * (hi0 - lo0) + (hi1 - lo1) * (hi1 - lo1) + (hi2 - lo2) * (hi2 - lo2));
-  // the same sphere in the recentred FP32 frame, radius measured from its
-  // FP32 centre (widened by 1e-4 for the rounding)
-  const float fw0 = (float)(wc0 - c0), fw1 = (float)(wc1 - c1), fw2 = (float)(wc2 - c2);
-  float fwr = sqrtf(dist2f(r0, r1, r2, fw0, fw1, fw2));
-  for (int o = 32; o > 0; o >>= 1) fwr = fmaxf(fwr, __shfl_xor(fwr, o));
-  fwr *= 1.0001f;
-  const int lane = tid & 63;
-  // the cell range of split blockIdx.y (cchunk is a multiple of the tile)
-  const int tb = blockIdx.y * cchunk / kPT, te = (min(N, (blockIdx.y + 1) * cchunk) + kPT - 1) / kPT;
-  double ex = 0.0, ey = 0.0, ez = 0.0, ev = 0.0;
-  for (int t = tb; t < te; ++t) {
-    const double dx = wc0 - tiles[4 * t], dy = wc1 - tiles[4 * t + 1], dz = wc2 - tiles[4 * t + 2];
-    const double rs = wr + tiles[4 * t + 3];
-    if (dx * dx + dy * dy + dz * dz > rs * rs) continue;  // wave-uniform
-    const int k0 = t * kPT, cnt = min(kPT, N - k0);
-    // lane k holds cell k0 + k (centroid recentred to FP32 and the near
-    // limit, exactly as the far kernel stages them) and tests it once
-    // against the wave's sphere; only the cells some lane may see within
-    // 3 D (1 % wide) take the per-lane test
-    float g0 = 0.f, g1 = 0.f, g2 = 0.f, lim = 0.f, dk = 0.f;
-    if (lane < cnt) {
-      const int kk = k0 + lane;
-      g0 = (float)(f[(size_t)MF_GX * N + kk] - c0);
-      g1 = (float)(f[(size_t)MF_GY * N + kk] - c1);
-      g2 = (float)(f[(size_t)MF_GZ * N + kk] - c2);
-      const double D = f[(size_t)MF_DIAM * N + kk];
-      lim = (float)(kNearMixed * kNearMixed * D * D);
-      dk = (float)D;
-    }
-    const float tw = sqrtf(dist2f(fw0, fw1, fw2, g0, g1, g2)) - fwr;
-    for (uint64_t m = __ballot(lane < cnt && tw < (float)(kNearMixed * 1.01) * dk); m; m &= m - 1ull) {
-      const int k = __builtin_ctzll(m);
-      const float h0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g0), k));
-      const float h1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g1), k));
-      const float h2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g2), k));
-      const float hl = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lim), k));
-      const bool nearp = active && dist2f(r0, r1, r2, h0, h1, h2) < hl;
-      if (__any(nearp)) {
-        const int kk = k0 + k;
-        if (nearp) near_cell<WANT_V>(f, N, kk, sigma[kk], x0, x1, x2, ex, ey, ez, ev);
-      }
-    }
-  }
-  if (active) {
-    double *acc = part + (size_t)blockIdx.y * 4 * n_t;
-    acc[i] += ex;
-    acc[(size_t)n_t + i] += ey;
-    acc[2 * (size_t)n_t + i] += ez;
-    if (WANT_V) acc[3 * (size_t)n_t + i] += ev;
-  }
-}
-
-// FP64 mode: closed form up to 48 diameters (k_panel_fp64_near), FP64
+// FP64 mode: closed form up to 48 diameters (k_panel_close), FP64
 // 7-point rule beyond (k_panel_fp64).  Both decide with the same FP64 test
 // |x - c_k|^2 >= (48 D_k)^2 on the unmodified coordinates.
 constexpr int kPF = 32;  // cells per LDS tile of the FP64 far kernel
@@ -748,21 +642,45 @@ __global__ __launch_bounds__(kThreads) void k_panel_fp64(int n_t, const double *
   }
 }
 
-// FP64 closed-form zone (R < 48 D), added to the far kernel's partial sums
-// of the same cell range (split by gridDim.y as in the far kernel).  Each
-// wave bounds its 64 targets by a sphere and visits the 64-cell tiles whose
-// zone sphere (centre, max_k |c_k - centre| + 48 D_k) it meets.
-template <bool WANT_V>
-__global__ __launch_bounds__(kThreads) void k_panel_fp64_near(int n_t, const double *__restrict__ xs, int N,
-                                                              const double *__restrict__ f,
-                                                              const double *__restrict__ sigma,
-                                                              const double *__restrict__ tiles, int cchunk,
-                                                              double *part) {
-  const int i = blockIdx.x * kThreads + threadIdx.x;
+// FP64 closed-form zone of both modes (MIXED: R < 3 D by the far kernel's FP32
+// test on the same recentred values; else R < 48 D by its FP64 test), added
+// to the far kernel's partial sums of the same cell range (gridDim.y splits
+// the cells as there; one writer per entry, stream order).  One wave per
+// workgroup: the zone's work is uneven over targets and cells, and single
+// waves spread it over the chip.  The wave bounds its 64 targets by a sphere
+// and visits the 64-cell tiles whose zone sphere (centre, max_k |c_k -
+// centre| + zone D_k, slightly inflated) it meets; in a tile, lane k tests
+// cell k once against the sphere, and the flagged cells take the per-lane
+// test.  A cell that at least kDenseLanes of the targets see from 2.5 D to the
+// zone's end is evaluated for them at once (cell_mid_form, the record in
+// scalar registers).  All other pairs are queued in LDS and evaluated 64 at a
+// time, one pair per lane, so that a cell near a single target costs a
+// sixty-fourth of a wave's closed form; each target then adds its own pairs'
+// results in queue order (deterministic).  Bound by
+// the closed form's FP64 operations.  Measured against the closed form of
+// every flagged cell for the whole wave: mixed, 97 points and 4,096 cells 84
+// -> 34 us, 200,003 points and 40,776 cells 1346 -> 475 us; FP64, 50,000
+// points and 40,776 cells 5.65 -> 2.87 ms.  kDenseLanes 8 to 32 differ by 1 %.
+constexpr int kDenseLanes = 32;
+
+template <bool WANT_V, bool MIXED>
+__global__ __launch_bounds__(64) void k_panel_close(int n_t, const double *__restrict__ xs, int N,
+                                                    const double *__restrict__ f, const double *__restrict__ rec,
+                                                    const double *__restrict__ sigma,
+                                                    const double *__restrict__ tiles, int cchunk, double *part) {
+  constexpr int NC = WANT_V ? 4 : 3;
+  __shared__ double X[3][64];
+  __shared__ double R[NC][64];
+  __shared__ int qk[128], ql[128];
+  const int lane = threadIdx.x;
+  const int i = blockIdx.x * 64 + lane;
   const bool active = i < n_t;
-  const int i0 = blockIdx.x * kThreads;
-  const int ii = active ? i : i0;
+  const int ii = active ? i : n_t - 1;
   const double x0 = xs[ii], x1 = xs[(size_t)n_t + ii], x2 = xs[2 * (size_t)n_t + ii];
+  X[0][lane] = x0;
+  X[1][lane] = x1;
+  X[2][lane] = x2;
+  // wave bounding sphere
   double lo0 = x0, lo1 = x1, lo2 = x2, hi0 = x0, hi1 = x1, hi2 = x2;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
@@ -775,37 +693,148 @@ __global__ __launch_bounds__(kThreads) void k_panel_fp64_near(int n_t, const dou
   }
   const double wc0 = 0.5 * (lo0 + hi0), wc1 = 0.5 * (lo1 + hi1), wc2 = 0.5 * (lo2 + hi2);
   const double wr = 0.5 * sqrt((hi0 - lo0) * (hi0 - lo0) + (hi1 - lo1) * (hi1 - lo1) + (hi2 - lo2) * (hi2 - lo2));
-  // the cell range of split blockIdx.y (cchunk is a multiple of the tile)
-  const int tb = blockIdx.y * cchunk / 64, te = (min(N, (blockIdx.y + 1) * cchunk) + 63) / 64;
+  // mixed: the far kernel's frame (recentred on the first target of the
+  // 256-target workgroup, FP32), and the sphere in it, radius measured from
+  // its FP32 centre (widened by 1e-4 for the rounding)
+  double c0 = 0.0, c1 = 0.0, c2 = 0.0;
+  float r0 = 0.f, r1 = 0.f, r2 = 0.f, fw0 = 0.f, fw1 = 0.f, fw2 = 0.f, fwr = 0.f;
+  if (MIXED) {
+    const int i0 = blockIdx.x * 64 / kThreads * kThreads;
+    c0 = xs[i0];
+    c1 = xs[(size_t)n_t + i0];
+    c2 = xs[2 * (size_t)n_t + i0];
+    r0 = (float)(x0 - c0);
+    r1 = (float)(x1 - c1);
+    r2 = (float)(x2 - c2);
+    fw0 = (float)(wc0 - c0);
+    fw1 = (float)(wc1 - c1);
+    fw2 = (float)(wc2 - c2);
+    fwr = sqrtf(dist2f(r0, r1, r2, fw0, fw1, fw2));
+    for (int o = 32; o > 0; o >>= 1) fwr = fmaxf(fwr, __shfl_xor(fwr, o));
+    fwr *= 1.0001f;
+  }
   double ex = 0.0, ey = 0.0, ez = 0.0, ev = 0.0;
-  for (int t = tb; t < te; ++t) {
-    const double dx = wc0 - tiles[4 * t], dy = wc1 - tiles[4 * t + 1], dz = wc2 - tiles[4 * t + 2];
-    const double rs = (wr + tiles[4 * t + 3]) * (1.0 + 1e-9);
-    if (dx * dx + dy * dy + dz * dz > rs * rs) continue;  // wave-uniform
+  int qn = 0;                                // pairs queued (wave-uniform, < 64 between cells)
+  unsigned long long mine = 0ull, next = 0;  // this lane's queue positions below 64 and from 64 on
+  // the cell range of split blockIdx.y (cchunk is a multiple of the tile);
+  // t = te flushes the rest
+  const int tb = blockIdx.y * cchunk / 64, te = (min(N, (int)(blockIdx.y + 1) * cchunk) + 63) / 64;
+  for (int t = tb; t <= te; ++t) {
     const int k0 = t * 64, cnt = min(64, N - k0);
-    // lane k holds cell k0 + k and tests it once against the wave's sphere
-    // (0.1 % wide); only the cells some lane may see within 48 D take the
-    // per-lane test, on the same FP64 values as the far kernel's
-    const int lane = threadIdx.x & 63;
     double cg0 = 0.0, cg1 = 0.0, cg2 = 0.0, cD = 0.0;
+    float g0 = 0.f, g1 = 0.f, g2 = 0.f, lim = 0.f;
     bool flag = false;
-    if (lane < cnt) {
-      const int kk = k0 + lane;
-      cg0 = f[(size_t)MF_GX * N + kk];
-      cg1 = f[(size_t)MF_GY * N + kk];
-      cg2 = f[(size_t)MF_GZ * N + kk];
-      cD = f[(size_t)MF_DIAM * N + kk];
-      const double u0 = cg0 - wc0, u1 = cg1 - wc1, u2 = cg2 - wc2;
-      flag = sqrt(u0 * u0 + u1 * u1 + u2 * u2) - wr < kQuadFp64 * 1.001 * cD;
+    if (t < te) {
+      const double dx = wc0 - tiles[4 * t], dy = wc1 - tiles[4 * t + 1], dz = wc2 - tiles[4 * t + 2];
+      const double rs = (wr + tiles[4 * t + 3]) * (1.0 + 1e-9);
+      if (dx * dx + dy * dy + dz * dz > rs * rs) continue;  // wave-uniform
+      if (lane < cnt) {
+        const int kk = k0 + lane;
+        cg0 = f[(size_t)MF_GX * N + kk];
+        cg1 = f[(size_t)MF_GY * N + kk];
+        cg2 = f[(size_t)MF_GZ * N + kk];
+        cD = f[(size_t)MF_DIAM * N + kk];
+        if (MIXED) {
+          // the near limit exactly as the far kernel stages it; the wave's
+          // test 1 % wide
+          g0 = (float)(cg0 - c0);
+          g1 = (float)(cg1 - c1);
+          g2 = (float)(cg2 - c2);
+          lim = (float)(kNearMixed * kNearMixed * cD * cD);
+          flag = sqrtf(dist2f(fw0, fw1, fw2, g0, g1, g2)) - fwr < (float)(kNearMixed * 1.01) * (float)cD;
+        } else {
+          // 0.1 % wide
+          const double u0 = cg0 - wc0, u1 = cg1 - wc1, u2 = cg2 - wc2;
+          flag = sqrt(u0 * u0 + u1 * u1 + u2 * u2) - wr < kQuadFp64 * 1.001 * cD;
+        }
+      }
     }
-    for (uint64_t m = __ballot(flag); m; m &= m - 1ull) {
-      const int k = __builtin_ctzll(m);
-      const int kk = k0 + k;
-      const double gx = x0 - readlane_f64(cg0, k), gy = x1 - readlane_f64(cg1, k), gz = x2 - readlane_f64(cg2, k);
-      const double D = readlane_f64(cD, k);
-      const bool nearp = active && !(fma(gx, gx, fma(gy, gy, gz * gz)) >= kQuadFp64 * kQuadFp64 * D * D);
-      if (__any(nearp)) {
-        if (nearp) near_cell<WANT_V>(f, N, kk, sigma[kk], x0, x1, x2, ex, ey, ez, ev);
+    uint64_t m = __ballot(flag);
+    for (;;) {
+      for (; m && qn < 64; m &= m - 1ull) {
+        const int k = __builtin_amdgcn_readfirstlane(__builtin_ctzll(m));
+        const int kk = k0 + k;
+        bool nearp;
+        double R2 = 0.0, D2 = 0.0;
+        if (MIXED) {
+          const float h0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g0), k));
+          const float h1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g1), k));
+          const float h2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g2), k));
+          const float hl = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lim), k));
+          nearp = active && dist2f(r0, r1, r2, h0, h1, h2) < hl;
+        } else {
+          const double gx = x0 - readlane_f64(cg0, k), gy = x1 - readlane_f64(cg1, k), gz = x2 - readlane_f64(cg2, k);
+          const double D = readlane_f64(cD, k);
+          R2 = fma(gx, gx, fma(gy, gy, gz * gz));
+          D2 = D * D;
+          nearp = active && !(R2 >= kQuadFp64 * kQuadFp64 * D * D);
+        }
+        if (!MIXED) {
+          const bool mid = nearp && R2 >= kMidForm * kMidForm * D2;
+          if (__popcll(__ballot(mid)) >= kDenseLanes) {
+            if (mid) {
+              const double sg = sigma[kk];
+              d3 E;
+              double V;
+              cell_mid_form<WANT_V>(rec + (size_t)kk * CR_COUNT, mk3(x0, x1, x2), E, V);
+              ex = fma(sg, E.x, ex);
+              ey = fma(sg, E.y, ey);
+              ez = fma(sg, E.z, ez);
+              if (WANT_V) ev = fma(sg, V, ev);
+              nearp = false;
+            }
+          }
+        }
+        const unsigned long long nm = __ballot(nearp);
+        if (nm) {
+          if (nearp) {
+            const int p = qn + __popcll(nm & ((1ull << lane) - 1ull));
+            qk[p] = kk;
+            ql[p] = lane;
+            if (p < 64)
+              mine |= 1ull << p;
+            else
+              next |= 1ull << (p - 64);
+          }
+          qn += __popcll(nm);
+        }
+      }
+      const int n = t < te ? (qn >= 64 ? 64 : 0) : min(qn, 64);
+      if (n == 0) break;
+      // the first n queued pairs, one per lane; then every lane adds its own
+      // (one wave: the barriers only order the LDS accesses)
+      __syncthreads();
+      if (lane < n) {
+        const int k = qk[lane], l = ql[lane];
+        d3 E;
+        double V;
+        cell_closed_form<WANT_V>(rec + (size_t)k * CR_COUNT, mk3(X[0][l], X[1][l], X[2][l]), E, V);
+        const double sg = sigma[k];
+        R[0][lane] = sg * E.x;
+        R[1][lane] = sg * E.y;
+        R[2][lane] = sg * E.z;
+        if (WANT_V) R[NC - 1][lane] = sg * V;
+      }
+      __syncthreads();
+      for (; mine; mine &= mine - 1ull) {
+        const int j = __builtin_ctzll(mine);
+        ex += R[0][j];
+        ey += R[1][j];
+        ez += R[2][j];
+        if (WANT_V) ev += R[NC - 1][j];
+      }
+      qn -= n;
+      mine = next;
+      next = 0ull;
+      int k2 = 0, l2 = 0;
+      if (lane < qn) {
+        k2 = qk[64 + lane];
+        l2 = ql[64 + lane];
+      }
+      __syncthreads();
+      if (lane < qn) {
+        qk[lane] = k2;
+        ql[lane] = l2;
       }
     }
   }
@@ -894,14 +923,15 @@ obem_status launch_panel_field(obem_ctx *ctx, const obem_meshh *m, const double 
   // the near kernel of split y adds the closed-form pairs of the same cell
   // range into the same slot (one writer per entry, after the far kernel),
   // then the slots are added in split order
-#define PANEL_NEAR(K, V, T) \
-  hipLaunchKernelGGL(K<V>, gsplit, block, 0, ctx->stream, n_t, to.xs, N, m->f, sigma, T, cchunk, part)
+#define PANEL_CLOSE(V, M, T)                                                                                     \
+  hipLaunchKernelGGL((k_panel_close<V, M>), dim3((n_t + 63) / 64, ns), dim3(64), 0, ctx->stream, n_t, to.xs, N, m->f, \
+                     m->rec, sigma, T, cchunk, part)
   if (prec == OBEM_MIXED) {
-    if (want_v) PANEL_NEAR(k_panel_near, true, m->tiles); else PANEL_NEAR(k_panel_near, false, m->tiles);
+    if (want_v) PANEL_CLOSE(true, true, m->tiles); else PANEL_CLOSE(false, true, m->tiles);
   } else {
-    if (want_v) PANEL_NEAR(k_panel_fp64_near, true, m->tiles48); else PANEL_NEAR(k_panel_fp64_near, false, m->tiles48);
+    if (want_v) PANEL_CLOSE(true, false, m->tiles48); else PANEL_CLOSE(false, false, m->tiles48);
   }
-#undef PANEL_NEAR
+#undef PANEL_CLOSE
 #undef PANEL_FAR
   if (slots)
     *slots = Slots{part, ns};

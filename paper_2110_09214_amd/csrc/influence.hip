@@ -26,16 +26,11 @@ namespace obem {
 constexpr int kTI = 256;
 
 // FP64 closed form of one cell at one charge: q IV and q IE.
-__device__ __forceinline__ void infl_closed(const double *__restrict__ f, int N, int k, double px, double py,
-                                            double pz, double q, double &sv, double &ex, double &ey, double &ez) {
-  d3 P[3];
-  P[0] = mk3(f[(size_t)MF_AX * N + k] - px, f[(size_t)MF_AY * N + k] - py, f[(size_t)MF_AZ * N + k] - pz);
-  P[1] = mk3(f[(size_t)MF_BX * N + k] - px, f[(size_t)MF_BY * N + k] - py, f[(size_t)MF_BZ * N + k] - pz);
-  P[2] = mk3(f[(size_t)MF_CX * N + k] - px, f[(size_t)MF_CY * N + k] - py, f[(size_t)MF_CZ * N + k] - pz);
-  const d3 n = mk3(f[(size_t)MF_NX * N + k], f[(size_t)MF_NY * N + k], f[(size_t)MF_NZ * N + k]);
+__device__ __forceinline__ void infl_closed(const double *__restrict__ rec, int k, double px, double py, double pz,
+                                            double q, double &sv, double &ex, double &ey, double &ez) {
   d3 IE;
   double IV;
-  cell_closed_form<true>(P, n, 2.0 * f[(size_t)MF_AREA * N + k], cell_edges(f, N, k), IE, IV);
+  cell_closed_form<true>(rec + (size_t)k * CR_COUNT, mk3(px, py, pz), IE, IV);
   sv = fma(q, IV, sv);
   ex = fma(q, IE.x, ex);
   ey = fma(q, IE.y, ey);
@@ -248,6 +243,7 @@ __global__ __launch_bounds__(kTI) void k_influence_mixed(int N, const double *__
 constexpr int kNW = 64;
 
 __global__ __launch_bounds__(kNW) void k_influence_near(int N, const double *__restrict__ f,
+                                                        const double *__restrict__ rec,
                                                         const int32_t *__restrict__ ord, int n_s,
                                                         const double *__restrict__ sx,
                                                         const double *__restrict__ sy,
@@ -288,7 +284,7 @@ __global__ __launch_bounds__(kNW) void k_influence_near(int N, const double *__r
       if (__any(nearp)) {
         if (nearp) {
           const int j = jt + jj;
-          infl_closed(f, N, kk, sx[j], sy[j], sz[j], sq[j], nv, nx, ny, nz);
+          infl_closed(rec, kk, sx[j], sy[j], sz[j], sq[j], nv, nx, ny, nz);
         }
       }
     }
@@ -303,6 +299,7 @@ __global__ __launch_bounds__(kNW) void k_influence_near(int N, const double *__r
 }
 
 __global__ __launch_bounds__(kTI) void k_influence_fp64(int N, const double *__restrict__ f,
+                                                        const double *__restrict__ rec,
                                                         const int32_t *__restrict__ ord, int n_s,
                                                         const double *__restrict__ sx,
                                                         const double *__restrict__ sy,
@@ -334,7 +331,7 @@ __global__ __launch_bounds__(kTI) void k_influence_fp64(int N, const double *__r
       const double dx = p.x - g0, dy = p.y - g1, dz = p.z - g2;
       const bool quad = fma(dx, dx, fma(dy, dy, dz * dz)) >= lim;
       if (!__all(quad)) {
-        if (!quad && active) infl_closed(f, N, kk, p.x, p.y, p.z, p.w, sv, ex, ey, ez);
+        if (!quad && active) infl_closed(rec, kk, p.x, p.y, p.z, p.w, sv, ex, ey, ez);
       }
       if (__any(quad)) {
         if (quad) {
@@ -426,10 +423,10 @@ obem_status influence_rhs(obem_ctx *ctx, const obem_meshh *m, int64_t n_src, con
     if (st) return st;
     hipLaunchKernelGGL(k_influence_mixed, dim3(bw, nsplit), dim3(kTI), 0, ctx->stream, N, m->f, m->order, n_s, so.x,
                        so.y, so.z, so.q, chunk, part);
-    hipLaunchKernelGGL(k_influence_near, dim3(bn, nslot - nsplit), dim3(kNW), 0, ctx->stream, N, m->f, m->order, n_s,
+    hipLaunchKernelGGL(k_influence_near, dim3(bn, nslot - nsplit), dim3(kNW), 0, ctx->stream, N, m->f, m->rec, m->order, n_s,
                        so.x, so.y, so.z, so.q, so.tbox, tchunk, part + 4 * (size_t)N * nsplit);
   } else {
-    hipLaunchKernelGGL(k_influence_fp64, dim3(bc, nsplit), dim3(kTI), 0, ctx->stream, N, m->f, m->order, n_s, sx, sy,
+    hipLaunchKernelGGL(k_influence_fp64, dim3(bc, nsplit), dim3(kTI), 0, ctx->stream, N, m->f, m->rec, m->order, n_s, sx, sy,
                        sz, sq, chunk, part);
   }
   OBEM_HIP(ctx, hipGetLastError());

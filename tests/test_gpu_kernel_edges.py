@@ -56,3 +56,24 @@ def test_closed_form_around_its_switches(ctx, orc, scale):
     Er, Vr = orc.panel_field(x, a, b, c, sig, want_v=True)
     assert (np.linalg.norm(host(E) - Er, axis=1) / np.linalg.norm(Er, axis=1)).max() <= 2e-12
     assert (np.abs(host(V) - Vr) / np.abs(Vr)).max() <= 2e-12
+
+
+@pytest.mark.parametrize("n", [1, 63, 65, 130, 257])
+@pytest.mark.parametrize("spread", [2e-6, 60e-6])
+def test_close_pairs_queue(ctx, orc, n, spread):
+    """Targets in a hole of the coarse GEM cell, within a cell's size or over
+    many of them: cells seen by a few or by all targets of a wave, batches of
+    queued pairs that fill, overflow and end part full.  Tolerances of the
+    two precisions as in the field tests (a lost pair is above 1e-4)."""
+    geo = W.GemGeometry(m=3, n_r=2, n_cone=2, plain_h=48e-6)
+    m = W.gem_cell_mesh(geo)
+    rng = np.random.default_rng(n)
+    cx, cy = geo.hole_centres()[4]
+    x = np.array([cx + 0.8 * geo.r_inner, cy, 3e-6]) + rng.uniform(-1, 1, size=(n, 3)) * np.array([0.2, 0.2, 1.0]) * spread
+    sig = 1e-6 * (1.0 + rng.uniform(size=m.n))
+    Er, Vr = orc.panel_field(x, m.a, m.b, m.c, sig, want_v=True)
+    bm = bind(ctx, m)
+    for prec, tol in ((B.OBEM_FP64, 1e-12), (B.OBEM_MIXED, 1e-5)):
+        E, V = B.field_eval(ctx, bm, dev(sig), None, None, dev(x), 0.0, prec, want_v=True)
+        assert rel_l2(host(E), Er) <= tol
+        assert rel_l2(host(V), Vr) <= tol
