@@ -11,6 +11,8 @@
 // reduction has a fixed order.
 #include <hipcub/hipcub.hpp>
 
+#include <type_traits>
+
 #include "cellmath.hpp"
 #include "obem_internal.hpp"
 #include "paironce.hpp"
@@ -1540,6 +1542,199 @@ __global__ __launch_bounds__(kThreads, 4) void k_pair_sym(int n, const double *_
   }
 }
 
+// The pair-once evaluation of few super-block pairs.  A workgroup of
+// k_pair_sym is one long serial chain (2048 steps of 8 pairs a wave), so a
+// launch of W workgroups takes about 600 us for any W up to 256, with the
+// chip idle beside it.  Here each item (A, d) is cut in two roles: the sums
+// for A's particles (a workgroup holds kSplitA of A's tiles and streams all
+// of B) and the sums for B's (a workgroup streams kSplitB of B's tiles past
+// all of A); one tile each measured 3 to 15 % faster than two.  Every pair is evaluated twice, 24 instead of 15 VALU
+// operations, but the item is spread over 8 / kSplitA + 8 / kSplitB
+// workgroups.  Each sum takes the same terms in the same order as in
+// k_pair_sym, so the slots are the same bit for bit.
+constexpr int kSplitA = 1;
+constexpr int kSplitB = 1;
+constexpr int kSplitParts = kSymTiles / kSplitA + kSymTiles / kSplitB;
+
+// One group of 64 sources and one step of k_pair_sym's inner loop for KA
+// tiles of A: into A's sums e (SUM_A) or the source's running sum c.
+template <int KA, bool SUM_A, bool U>
+__device__ __forceinline__ void sym_step(const float4 sj, const float (&r0)[KA], const float (&r1)[KA],
+                                         const float (&r2)[KA], const float (&qa)[KA], const float (&s2k)[KA],
+                                         float (&ex)[KA], float (&ey)[KA], float (&ez)[KA], float &cx, float &cy,
+                                         float &cz) {
+#pragma unroll
+  for (int k = 0; k < KA; ++k) {
+    const float dx = r0[k] - sj.x, dy = r1[k] - sj.y, dz = r2[k] - sj.z;
+    const float rr = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, s2k[k])));
+    const float ri = __builtin_amdgcn_rsqf(rr);
+    const float w = ri * (ri * ri);
+    if (SUM_A) {
+      const float wi = U ? w : w * sj.w;
+      ex[k] = fmaf(wi, dx, ex[k]);
+      ey[k] = fmaf(wi, dy, ey[k]);
+      ez[k] = fmaf(wi, dz, ez[k]);
+    } else {
+      const float wj = U ? w : w * qa[k];
+      cx = fmaf(wj, dx, cx);
+      cy = fmaf(wj, dy, cy);
+      cz = fmaf(wj, dz, cz);
+    }
+  }
+}
+
+// A workgroup's share: tiles ka .. ka + KA - 1 of A against tiles bt0 .. bt0 +
+// NB - 1 of B, one of the two sums.
+template <int KA, int NB, bool SUM_A, bool NN>
+__device__ __forceinline__ void sym_part(int n, const double *__restrict__ sx, const double *__restrict__ sy,
+                                         const double *__restrict__ sz, const double *__restrict__ sq,
+                                         const double *__restrict__ tbox, double nn_cut2d,
+                                         const double *__restrict__ sb, float soft2, int A, int B, int dd, int ka,
+                                         int bt0, float *__restrict__ Pi, float *__restrict__ Pj,
+                                         float4 (*S)[128], float (*J)[3][kThreads]) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int nxt = ((lane + 1) & 63) << 2;
+  const int a0 = A * kSymSB, b0 = B * kSymSB;
+  const double *org = sym_origin(sb, A, B);
+  const double c0 = org[0], c1 = org[1], c2 = org[2];
+  float r0[KA], r1[KA], r2[KA], qa[KA], ex[KA], ey[KA], ez[KA];
+  const float qA = (float)sq[a0], qB = (float)sq[b0];
+#pragma unroll
+  for (int k = 0; k < KA; ++k) {
+    const int i = a0 + (ka + k) * kThreads + tid;
+    const bool act = i < n;
+    r0[k] = act ? (float)(sx[i] - c0) : 0.f;
+    r1[k] = act ? (float)(sy[i] - c1) : 0.f;
+    r2[k] = act ? (float)(sz[i] - c2) : 0.f;
+    qa[k] = act ? (float)sq[i] : 0.f;
+    ex[k] = ey[k] = ez[k] = 0.f;
+  }
+  // one charge on each side of the whole item
+  bool uni = true;
+#pragma unroll
+  for (int k = 0; k < kSymTiles; ++k) {
+    const int i = a0 + k * kThreads + tid, j = b0 + k * kThreads + tid;
+    uni = uni && i < n && (float)sq[min(i, n - 1)] == qA && j < n && (float)sq[min(j, n - 1)] == qB;
+  }
+  const bool U = __syncthreads_and(uni);
+  for (int bt = bt0; bt < bt0 + NB; ++bt) {
+    const int jt = b0 + bt * kThreads;
+    if (jt >= n) break;  // workgroup-uniform
+    const int cnt = min(kThreads, n - jt);
+    float s2k[KA];
+#pragma unroll
+    for (int k = 0; k < KA; ++k) {
+      const bool direct = a0 + (ka + k) * kThreads < n &&
+                          tile_pair_direct(tbox, sb, A * kSymTiles + ka + k, B * kSymTiles + bt, kSymTiles, NN, nn_cut2d);
+      s2k[k] = direct ? 1e36f : soft2;
+    }
+    __syncthreads();  // the previous tile's S and J are consumed
+    {
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (tid < cnt) {
+        const int j = jt + tid;
+        v = make_float4((float)(sx[j] - c0), (float)(sy[j] - c1), (float)(sz[j] - c2), (float)sq[j]);
+      }
+      S[tid >> 6][tid & 63] = v;
+      S[tid >> 6][(tid & 63) + 64] = v;
+    }
+    __syncthreads();
+    for (int g = 0; g < cnt; g += 128) {
+      float tx = 0.f, ty = 0.f, tz = 0.f, ux = 0.f, uy = 0.f, uz = 0.f;
+      const float4 *sa = &S[g >> 6][lane];
+      const float4 *sb2 = &S[(g >> 6) + 1][lane];
+      auto steps = [&](auto Uc) {
+        constexpr bool UC = decltype(Uc)::value;
+#pragma unroll 4
+        for (int m = 0; m < 64; ++m) {
+          sym_step<KA, SUM_A, UC>(sa[m], r0, r1, r2, qa, s2k, ex, ey, ez, tx, ty, tz);
+          if (!SUM_A) {
+            tx = __int_as_float(__builtin_amdgcn_ds_bpermute(nxt, __float_as_int(tx)));
+            ty = __int_as_float(__builtin_amdgcn_ds_bpermute(nxt, __float_as_int(ty)));
+            tz = __int_as_float(__builtin_amdgcn_ds_bpermute(nxt, __float_as_int(tz)));
+          }
+          sym_step<KA, SUM_A, UC>(sb2[m], r0, r1, r2, qa, s2k, ex, ey, ez, ux, uy, uz);
+          if (!SUM_A) {
+            ux = __int_as_float(__builtin_amdgcn_ds_bpermute(nxt, __float_as_int(ux)));
+            uy = __int_as_float(__builtin_amdgcn_ds_bpermute(nxt, __float_as_int(uy)));
+            uz = __int_as_float(__builtin_amdgcn_ds_bpermute(nxt, __float_as_int(uz)));
+          }
+        }
+      };
+      if (U)
+        steps(std::true_type());
+      else
+        steps(std::false_type());
+      if (!SUM_A) {
+        const int jl = g + lane;
+        J[wv][0][jl] = tx;
+        J[wv][1][jl] = ty;
+        J[wv][2][jl] = tz;
+        J[wv][0][jl + 64] = ux;
+        J[wv][1][jl + 64] = uy;
+        J[wv][2][jl + 64] = uz;
+      }
+    }
+    if (!SUM_A) {
+      __syncthreads();
+      if (tid < cnt) {
+        const float fj = U ? -qA : -1.f;
+        const size_t o = (size_t)dd * 3 * n + jt + tid;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const float v = ((J[0][c][tid] + J[1][c][tid]) + J[2][c][tid]) + J[3][c][tid];
+          Pj[o + (size_t)c * n] = fj * v;
+        }
+      }
+    }
+  }
+  if (SUM_A) {
+    const float fi = U ? qB : 1.f;
+#pragma unroll
+    for (int k = 0; k < KA; ++k) {
+      const int i = a0 + (ka + k) * kThreads + tid;
+      if (i < n) {
+        const size_t o = (size_t)dd * 3 * n + i;
+        Pi[o] = fi * ex[k];
+        Pi[o + (size_t)n] = fi * ey[k];
+        Pi[o + 2 * (size_t)n] = fi * ez[k];
+      }
+    }
+  }
+}
+
+template <bool NN>
+__global__ __launch_bounds__(kThreads, 4) void k_pair_sym_split(int n, const double *__restrict__ sx,
+                                                              const double *__restrict__ sy,
+                                                              const double *__restrict__ sz,
+                                                              const double *__restrict__ sq,
+                                                              const double *__restrict__ tbox, double nn_cut2d,
+                                                              const double *__restrict__ sb, float soft2, int ns,
+                                                              int d0, int dcnt, float *__restrict__ Pi,
+                                                              float *__restrict__ Pj) {
+  __shared__ float4 S[kThreads / 64][128];
+  __shared__ float J[kThreads / 64][3][kThreads];
+  const int item = (int)blockIdx.x / kSplitParts, part = (int)blockIdx.x % kSplitParts;
+  const int A = item / dcnt, dd = item % dcnt, d = d0 + dd;
+  if (d > sym_h(A, ns)) return;  // workgroup-uniform, before any barrier
+  const int B = (A + d) % ns;
+  constexpr int nA = kSymTiles / kSplitA;
+  if (part < nA)
+    sym_part<kSplitA, kSymTiles, true, NN>(n, sx, sy, sz, sq, tbox, nn_cut2d, sb, soft2, A, B, dd, part * kSplitA, 0, Pi,
+                                           Pj, S, J);
+  else
+    sym_part<kSymTiles, kSplitB, false, NN>(n, sx, sy, sz, sq, tbox, nn_cut2d, sb, soft2, A, B, dd, 0,
+                                            (part - nA) * kSplitB, Pi, Pj, S, J);
+}
+
+// Whether a launch of ns dcnt items takes the cut form: an item in parts adds
+// 2.6 us to the launch, a launch of whole items takes about 600 us up to a
+// quarter of the resident workgroups, so the line lies at 7/32 of them (224
+// of 1024).  Whole calls with 7,464 cells: 5,001 charges 880 -> 360 us, 20,001
+// 1237 -> 810 us, 40,001 (200 items) 1643 -> 1549 us; at 47,001 (253 items) the
+// parts took 1821 us against 1790.
+static bool sym_in_parts(int ns, int dcnt, int resident) { return (int64_t)ns * dcnt <= (int64_t)resident * 7 / 32; }
+
 // acc[c][p] += the launch's slots that hold a field at p, in slot order: the
 // slot of d as the owner of (A, A + d) and the slot of d as the partner of
 // (A - d, A).
@@ -1820,15 +2015,22 @@ obem_status launch_pair_field(obem_ctx *ctx, int64_t n_src, const double *sx, co
       const float soft2 = (float)(soft * soft);
       obem_status st = run_pair_once(ctx, n_t, kSymSB, ns, sym_resident(ctx, nn), kSymSlots, acc,
                                      [&](int d0, int dcnt, float *pi, float *pj) {
-                                       const dim3 g(sym_grid(ns, dcnt));
-                                       if (nn)
-                                         hipLaunchKernelGGL(k_pair_sym<true>, g, dim3(kThreads), 0, ctx->stream, n_t,
-                                                            sx, sy, sz, sq, tbox, nn_cut2d, sb, soft2, ns, d0, dcnt,
-                                                            pi, pj);
-                                       else
-                                         hipLaunchKernelGGL(k_pair_sym<false>, g, dim3(kThreads), 0, ctx->stream, n_t,
-                                                            sx, sy, sz, sq, tbox, nn_cut2d, sb, soft2, ns, d0, dcnt,
-                                                            pi, pj);
+#define SYM(K, G)                                                                                                     \
+  hipLaunchKernelGGL(K, dim3(G), dim3(kThreads), 0, ctx->stream, n_t, sx, sy, sz, sq, tbox, nn_cut2d, sb, soft2, ns,   \
+                     d0, dcnt, pi, pj)
+                                       if (sym_in_parts(ns, dcnt, sym_resident(ctx, nn))) {
+                                         const unsigned g = (unsigned)ns * dcnt * kSplitParts;
+                                         if (nn)
+                                           SYM(k_pair_sym_split<true>, g);
+                                         else
+                                           SYM(k_pair_sym_split<false>, g);
+                                       } else {
+                                         if (nn)
+                                           SYM(k_pair_sym<true>, sym_grid(ns, dcnt));
+                                         else
+                                           SYM(k_pair_sym<false>, sym_grid(ns, dcnt));
+                                       }
+#undef SYM
                                      });
       if (st) return st;
     }

@@ -77,3 +77,17 @@ def test_close_pairs_queue(ctx, orc, n, spread):
         E, V = B.field_eval(ctx, bm, dev(sig), None, None, dev(x), 0.0, prec, want_v=True)
         assert rel_l2(host(E), Er) <= tol
         assert rel_l2(host(V), Vr) <= tol
+
+
+@pytest.mark.parametrize("n", [6145, 43008, 43009])
+def test_pair_once_in_parts(ctx, orc, n):
+    """The pair-once evaluation cut in parts (up to 224 super-block pairs: 21
+    full super-blocks) and whole (one charge more), and the first size with
+    an even number of super-blocks, at the error bound of the pair-once
+    tests, on a sample of the charges."""
+    rng = np.random.default_rng(n)
+    x = rng.normal(size=(n, 3)) * 50e-6
+    q = np.where(rng.uniform(size=n) < 0.6, -W.E_CHARGE, W.E_CHARGE)
+    E = host(B.field_eval(ctx, None, None, dev(x), dev(q), dev(x), 1e-7, B.OBEM_MIXED, tgt_is_src=True))
+    at = np.concatenate([rng.choice(n, 400, replace=False), [0, n - 1]])
+    assert rel_l2(E[at], orc.pair_field(x[at], x, q, 1e-7)) <= 1e-5
