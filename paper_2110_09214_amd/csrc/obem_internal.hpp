@@ -62,7 +62,7 @@ enum WsSlot {
   WS_BBOX = 0, WS_KEYS0, WS_KEYS1, WS_IDX0, WS_IDX1, WS_SORT_TMP, WS_TSORT, WS_ACC, WS_PART,
   WS_NN, WS_MISC0, WS_MISC1, WS_MISC2, WS_MISC3, WS_MISC4, WS_MISC5, WS_MISC6, WS_MISC7,
   WS_SOLVE0, WS_SOLVE1, WS_SOLVE2, WS_SRC, WS_SRCPERM, WS_SRCKEY, WS_SORT_TMP2, WS_TBOX, WS_MAP, WS_STATUS, WS_SRCINV, WS_PANEL,
-  WS_SYMI, WS_SYMJ, WS_SYMR, WS_SYMM, WS_INC_IDX, WS_INC_DB, WS_COUNT
+  WS_SYMI, WS_SYMJ, WS_SYMR, WS_SYMM, WS_INC_IDX, WS_INC_DB, WS_MAPNODES, WS_COUNT
 };
 
 }  // namespace obem
@@ -294,10 +294,15 @@ struct MapDev {
   int nx, ny, nz;
   double lo[3], h[3];
   const double *ex, *ey, *ez;
+  const double *nodes = nullptr;  // the same values as (Ex, Ey, Ez) per node, if packed
 };
+// For many points: packs the map's values node by node into the workspace
+// (g->nodes); no-op for few.
+obem_status map_pack(obem_ctx *ctx, int64_t n_points, MapDev *g);
 
 // Trilinear interpolation; points outside the grid box take the value at the
 // nearest point of the box.
+template <bool PACKED>
 __device__ __forceinline__ void map_interp(const MapDev &g, double x, double y, double z, double E[3]) {
   const double p[3] = {x, y, z};
   const int nn[3] = {g.nx, g.ny, g.nz};
@@ -316,15 +321,29 @@ __device__ __forceinline__ void map_interp(const MapDev &g, double x, double y, 
 #pragma unroll
   for (int dz = 0; dz < 2; ++dz)
 #pragma unroll
-    for (int dy = 0; dy < 2; ++dy)
+    for (int dy = 0; dy < 2; ++dy) {
+      const double wy = dy ? f[1] : 1.0 - f[1], wz = dz ? f[2] : 1.0 - f[2];
+      const size_t k = ((size_t)(i0[2] + dz) * g.ny + (i0[1] + dy)) * g.nx + i0[0];
+      // two neighbouring nodes of the row: 48 consecutive bytes if packed
+      double v[6];
+      if (PACKED) {
+        __builtin_memcpy(v, g.nodes + 3 * k, sizeof v);
+      } else {
+        v[0] = g.ex[k];
+        v[1] = g.ey[k];
+        v[2] = g.ez[k];
+        v[3] = g.ex[k + 1];
+        v[4] = g.ey[k + 1];
+        v[5] = g.ez[k + 1];
+      }
 #pragma unroll
       for (int dx = 0; dx < 2; ++dx) {
-        const double w = (dx ? f[0] : 1.0 - f[0]) * (dy ? f[1] : 1.0 - f[1]) * (dz ? f[2] : 1.0 - f[2]);
-        const size_t k = ((size_t)(i0[2] + dz) * g.ny + (i0[1] + dy)) * g.nx + (i0[0] + dx);
-        E[0] += w * g.ex[k];
-        E[1] += w * g.ey[k];
-        E[2] += w * g.ez[k];
+        const double w = (dx ? f[0] : 1.0 - f[0]) * wy * wz;
+        E[0] += w * v[3 * dx];
+        E[1] += w * v[3 * dx + 1];
+        E[2] += w * v[3 * dx + 2];
       }
+    }
 }
 // Checks a caller's map (sizes >= 2, spacing > 0, device arrays) and copies it.
 bool map_dev(const obem_field_map *m, MapDev *g);

@@ -91,3 +91,34 @@ def test_pair_once_in_parts(ctx, orc, n):
     E = host(B.field_eval(ctx, None, None, dev(x), dev(q), dev(x), 1e-7, B.OBEM_MIXED, tgt_is_src=True))
     at = np.concatenate([rng.choice(n, 400, replace=False), [0, n - 1]])
     assert rel_l2(E[at], orc.pair_field(x[at], x, q, 1e-7)) <= 1e-5
+
+
+@pytest.mark.parametrize("grid", [(40, 41, 43), (128, 128, 129)])
+def test_map_packed_and_plain(ctx, orc, grid):
+    """Map interpolation just below and at the count that packs the map (2^18
+    points, for at most eight times as many nodes): the same values bit for
+    bit as in small calls, which read the three arrays, and the oracle's on a
+    sample; the currents of the packed map against the plain ones."""
+    n = 1 << 18
+    lo, h = (-1e-3, -2e-3, 0.0), (1e-5, 2e-5, 1.5e-5)
+    fmap = B.FieldMap(lo, h, grid)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    for k in range(3):
+        fmap.e[k].normal_(generator=gen)
+    ext = torch.tensor([h[k] * (grid[k] - 1) for k in range(3)], dtype=torch.float64, device="cuda")
+    x = torch.tensor(lo, dtype=torch.float64, device="cuda") + ext * (
+        1.04 * torch.rand(n, 3, dtype=torch.float64, device="cuda", generator=gen) - 0.02)
+    E = B.field_map_eval(ctx, fmap, x)
+    assert torch.equal(E[: n - 1], B.field_map_eval(ctx, fmap, x[: n - 1]))
+    assert torch.equal(E[-999:], B.field_map_eval(ctx, fmap, x[-999:]))
+    ref = orc.trilinear(host(fmap.values()), lo, h, host(x[:500]))
+    assert np.abs(host(E[:500]) - ref).max() <= 1e-12 * np.abs(ref).max()
+    v = torch.randn(n, 3, dtype=torch.float64, device="cuda", generator=gen)
+    sp = torch.randint(0, 3, (n,), device="cuda", generator=gen).to(torch.int8)
+    cur, terms = B.induced_current(ctx, x, v, sp, fmap=fmap, want_terms=True)
+    cur2, terms2 = B.induced_current(ctx, x[: n - 1], v[: n - 1], sp[: n - 1], fmap=fmap, want_terms=True)
+    assert torch.equal(terms[: n - 1], terms2)
+    last = float(terms[-1])
+    scale = float(terms.abs().sum())
+    for k in range(3):
+        assert abs(cur[k] - cur2[k] - (last if int(sp[-1]) == k else 0.0)) <= 1e-13 * scale
