@@ -122,3 +122,21 @@ def test_map_packed_and_plain(ctx, orc, grid):
     scale = float(terms.abs().sum())
     for k in range(3):
         assert abs(cur[k] - cur2[k] - (last if int(sp[-1]) == k else 0.0)) <= 1e-13 * scale
+
+
+def test_point_layouts(ctx):
+    """Points in any layout that has the three coordinates along dimension 1
+    (contiguous, column-major, strided, with further columns, as columns of a
+    3-d tensor) give the same field."""
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    for n in (1, 2, 65):
+        x = 1e-4 * torch.rand(n, 3, dtype=torch.float64, device="cuda", generator=gen)
+        q = torch.full((n,), -W.E_CHARGE, dtype=torch.float64, device="cuda")
+        wide = torch.rand(2 * n, 5, dtype=torch.float64, device="cuda", generator=gen)
+        wide[::2, :3] = x
+        E = B.field_eval(ctx, None, None, x, q, x, 1e-7, B.OBEM_FP64, tgt_is_src=True)
+        assert E.shape == (n, 3) and E.is_contiguous()
+        for y in (x.t().contiguous().t(), wide[::2], wide[::2, :3], x[:, :, None]):
+            assert torch.equal(E, B.field_eval(ctx, None, None, y, q, y, 1e-7, B.OBEM_FP64, tgt_is_src=True))
+        with pytest.raises(IndexError):
+            B.field_eval(ctx, None, None, x[:, :2], q, x, 1e-7)
