@@ -586,23 +586,20 @@ static obem_status field_eval_impl(obem_ctx *ctx, const obem_meshh *mesh, const 
     REQ_DEV(ctx, sq, "sq");
   }
   if (mesh) REQ_DEV(ctx, sigma, "sigma");
-  // sources first (their ordering reuses the target-ordering workspace)
-  SourceOrder so;
-  if (n_src > 0) {
-    obem_status st = order_sources(ctx, n_src, sx, sy, sz, sq, tis, &so);
-    if (st) return st;
-  }
   // targets = sources: with the pair-once evaluation the targets take the
   // sources' order (same particles, same tiles)
+  SourceOrder so;
   const bool once = tis && pair_once_applies(n_tgt, precision, soft, want_v);
   TargetOrder to;
   obem_status st = OBEM_OK;
   if (once) {
+    st = order_sources(ctx, n_src, sx, sy, sz, sq, true, &so);
+    if (st) return st;
     to.n = (int32_t)n_tgt;
     to.perm = const_cast<int32_t *>(so.perm);
     to.xs = const_cast<double *>(so.x);
   } else {
-    st = order_targets(ctx, n_tgt, tx, ty, tz, &to);
+    st = order_both(ctx, n_src, sx, sy, sz, sq, tis, &so, n_tgt, tx, ty, tz, &to);
     if (st) return st;
   }
   double *acc = (double *)ws_get(ctx, WS_ACC, sizeof(double) * 4 * (size_t)n_tgt);

@@ -24,65 +24,70 @@ constexpr int kThreads = 256;
 // ---------------------------------------------------------------------------
 // Target ordering
 // ---------------------------------------------------------------------------
+// v of another lane of the wave by a DPP pattern (VALU; a shuffle of a double
+// is two LDS-crossbar instructions); lanes without a source keep v.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp((int)(unsigned)u, (int)(unsigned)u, CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp((int)(unsigned)(u >> 32), (int)(unsigned)(u >> 32), CTRL, ROWS, 0xf, false);
+  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
+// Minimum (or maximum) over the wave's 64 lanes, valid in lane 63: within
+// quads, eights and rows of 16, then rows 0 to 1 and 2 to 3, then 1 to 3.
+template <bool MAX>
+__device__ __forceinline__ double wave_extreme(double v) {
+  auto op = [](double a, double b) { return MAX ? fmax(a, b) : fmin(a, b); };
+  v = op(v, dpp_f64<0xB1, 0xf>(v));   // quad_perm 1 0 3 2
+  v = op(v, dpp_f64<0x4E, 0xf>(v));   // quad_perm 2 3 0 1
+  v = op(v, dpp_f64<0x141, 0xf>(v));  // row_half_mirror
+  v = op(v, dpp_f64<0x140, 0xf>(v));  // row_mirror
+  v = op(v, dpp_f64<0x142, 0xa>(v));  // row_bcast:15 into rows 1 and 3
+  return op(v, dpp_f64<0x143, 0xc>(v));  // row_bcast:31 into rows 2 and 3
+}
+
+// Combines the waves' boxes b (lo xyz, hi xyz) of a workgroup of T threads;
+// every thread gets the whole one.  red: 6 T / 64 doubles of LDS.
+template <int T>
+__device__ __forceinline__ void block_box(double b[6], double *red) {
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    b[c] = wave_extreme<false>(b[c]);
+    b[3 + c] = wave_extreme<true>(b[3 + c]);
+  }
+  if ((threadIdx.x & 63) == 63)
+#pragma unroll
+    for (int c = 0; c < 6; ++c) red[6 * (threadIdx.x >> 6) + c] = b[c];
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 6; ++c) b[c] = red[c];
+#pragma unroll 4
+  for (int w = 1; w < T / 64; ++w)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      b[c] = fmin(b[c], red[6 * w + c]);
+      b[3 + c] = fmax(b[3 + c], red[6 * w + 3 + c]);
+    }
+}
+
 __global__ __launch_bounds__(256) void k_bbox_partial(int n, const double *__restrict__ x,
                                                       const double *__restrict__ y,
                                                       const double *__restrict__ z, double *part) {
-  __shared__ double s[6][256];
-  double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+  __shared__ double red[24];
+  double b[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
   for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
-    double v[3] = {x[i], y[i], z[i]};
+    const double v[3] = {x[i], y[i], z[i]};
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      lo[c] = fmin(lo[c], v[c]);
-      hi[c] = fmax(hi[c], v[c]);
+      b[c] = fmin(b[c], v[c]);
+      b[3 + c] = fmax(b[3 + c], v[c]);
     }
   }
+  block_box<256>(b, red);
+  if (threadIdx.x == 0)
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    s[c][threadIdx.x] = lo[c];
-    s[3 + c][threadIdx.x] = hi[c];
-  }
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        s[c][threadIdx.x] = fmin(s[c][threadIdx.x], s[c][threadIdx.x + w]);
-        s[3 + c][threadIdx.x] = fmax(s[3 + c][threadIdx.x], s[3 + c][threadIdx.x + w]);
-      }
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x < 6) part[blockIdx.x * 6 + threadIdx.x] = s[threadIdx.x][0];
-}
-
-__global__ __launch_bounds__(256) void k_bbox_final(int nb, const double *part, double *bbox) {
-  __shared__ double s[6][256];
-  double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (int b = threadIdx.x; b < nb; b += 256) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      lo[c] = fmin(lo[c], part[b * 6 + c]);
-      hi[c] = fmax(hi[c], part[b * 6 + 3 + c]);
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    s[c][threadIdx.x] = lo[c];
-    s[3 + c][threadIdx.x] = hi[c];
-  }
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        s[c][threadIdx.x] = fmin(s[c][threadIdx.x], s[c][threadIdx.x + w]);
-        s[3 + c][threadIdx.x] = fmax(s[3 + c][threadIdx.x], s[3 + c][threadIdx.x + w]);
-      }
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x < 6) bbox[threadIdx.x] = s[threadIdx.x][0];
+    for (int c = 0; c < 6; ++c) part[blockIdx.x * 6 + c] = b[c];
 }
 
 __device__ __forceinline__ uint32_t spread3(uint32_t v) {
@@ -128,154 +133,296 @@ __device__ __forceinline__ uint32_t hilbert3(uint32_t x0, uint32_t x1, uint32_t 
   return spread3(X[2]) | (spread3(X[1]) << 1) | (spread3(X[0]) << 2);
 }
 
-__global__ __launch_bounds__(256) void k_curve_key(int n, const double *__restrict__ x, const double *__restrict__ y,
-                                                   const double *__restrict__ z, const double *bbox,
-                                                   uint32_t *keys, int32_t *idx) {
-  int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  double v[3] = {x[i], y[i], z[i]};
+// Sorting key of point i: its class (species, or sign of the charge: -, +,
+// other; 0 without either) above the 30 bits of its place along the curve in
+// the box lo .. hi.  Points in (class, curve, caller) order are then one
+// stable sort.
+__device__ __forceinline__ uint32_t order_key(const OrderJob &J, int i, const double lo[3], const double hi[3]) {
+  const double v[3] = {J.x[i], J.y[i], J.z[i]};
   uint32_t q[3];
   // one scale for the three axes, so that runs along the curve are compact
   // in space also in a flat or elongated point set
-  const double span = fmax(fmax(bbox[3] - bbox[0], bbox[4] - bbox[1]), bbox[5] - bbox[2]);
+  const double span = fmax(fmax(hi[0] - lo[0], hi[1] - lo[1]), hi[2] - lo[2]);
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    double t = span > 0.0 ? (v[c] - bbox[c]) / span : 0.0;
+    double t = span > 0.0 ? (v[c] - lo[c]) / span : 0.0;
     int qi = (int)(t * 1024.0);
     q[c] = (uint32_t)min(max(qi, 0), 1023);
   }
-  keys[i] = hilbert3(q[0], q[1], q[2]);
-  idx[i] = i;
+  uint32_t cls = 0;
+  if (J.species)
+    cls = (uint32_t)(J.species[i] & 3);
+  else if (J.q)
+    cls = J.q[i] < 0.0 ? 0u : (J.q[i] > 0.0 ? 1u : 2u);
+  return (cls << 30) | hilbert3(q[0], q[1], q[2]);
 }
 
-__global__ __launch_bounds__(256) void k_gather3(int n, const int32_t *__restrict__ perm,
-                                                 const double *__restrict__ x, const double *__restrict__ y,
-                                                 const double *__restrict__ z, double *out) {
-  int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  int j = perm[i];
-  out[i] = x[j];
-  out[(size_t)n + i] = y[j];
-  out[2 * (size_t)n + i] = z[j];
+// Keys of a large set; every workgroup reduces the nb partial boxes itself.
+__global__ __launch_bounds__(256) void k_order_key(OrderJob J, int nb, const double *__restrict__ part, uint32_t *keys,
+                                                   int32_t *idx) {
+  __shared__ double red[24];
+  double b[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+  for (int k = threadIdx.x; k < nb; k += 256)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      b[c] = fmin(b[c], part[6 * k + c]);
+      b[3 + c] = fmax(b[3 + c], part[6 * k + 3 + c]);
+    }
+  block_box<256>(b, red);
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= J.n) return;
+  keys[i] = order_key(J, i, b, b + 3);
+  idx[i] = i;
 }
 
 static inline int nblk(int64_t n, int t = 256) { return (int)((n + t - 1) / t); }
 
+// Element i of the ordered copies: the point's coordinates (and charge), the
+// inverse permutation.
+__device__ __forceinline__ void order_gather(const OrderJob &J, int i, int j, double v[3]) {
+  const size_t n = (size_t)J.n;
+  v[0] = J.x[j];
+  v[1] = J.y[j];
+  v[2] = J.z[j];
+  if (J.xs) {
+    J.xs[i] = v[0];
+    J.xs[n + i] = v[1];
+    J.xs[2 * n + i] = v[2];
+    if (J.q) J.xs[3 * n + i] = J.q[j];
+  }
+  if (J.inv) J.inv[j] = i;
+}
+
+// Box (lo xyz, hi xyz) of a 256-point tile held by four consecutive waves
+// (thread tt of the tile); red: 24 doubles of LDS per tile.
+__device__ __forceinline__ void tile_box(const double v[3], bool ok, int tt, double *red, double *box) {
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const double lo = wave_extreme<false>(ok ? v[c] : INFINITY), hi = wave_extreme<true>(ok ? v[c] : -INFINITY);
+    if ((tt & 63) == 63) {
+      red[6 * (tt >> 6) + c] = lo;
+      red[6 * (tt >> 6) + 3 + c] = hi;
+    }
+  }
+  __syncthreads();
+  if (tt < 6 && box) {
+    double r = red[tt];
+    for (int w = 1; w < 4; ++w) r = tt < 3 ? fmin(r, red[6 * w + tt]) : fmax(r, red[6 * w + tt]);
+    box[tt] = r;
+  }
+}
+
+struct OrderPair {
+  OrderJob job[2];
+};
+
+// The copies of one or two orderings (gridDim.y) from their permutations.
+__global__ __launch_bounds__(256) void k_order_gather(OrderPair jobs) {
+  __shared__ double red[24];
+  const OrderJob &J = jobs.job[blockIdx.y];
+  if ((int)blockIdx.x * 256 >= J.n) return;  // workgroup-uniform
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  double v[3] = {0.0, 0.0, 0.0};
+  if (i < J.n) order_gather(J, i, J.perm[i], v);
+  if (J.tbox) tile_box(v, i < J.n, threadIdx.x, red, J.tbox + 6 * (size_t)blockIdx.x);
+}
+
 // Bounding box of each 256-source tile of the source copy (lo xyz, hi xyz).
 __global__ __launch_bounds__(256) void k_tile_boxes(int n, const double *__restrict__ src, double *box) {
-  __shared__ double red[6][4];
+  __shared__ double red[24];
   const int i = blockIdx.x * 256 + threadIdx.x;
   const int k = min(i, n - 1);
-  double v[6];
-  for (int c = 0; c < 3; ++c) v[c] = v[3 + c] = src[(size_t)c * n + k];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      v[c] = fmin(v[c], __shfl_xor(v[c], o));
-      v[3 + c] = fmax(v[3 + c], __shfl_xor(v[3 + c], o));
-    }
-  if ((threadIdx.x & 63) == 0)
-    for (int c = 0; c < 6; ++c) red[c][threadIdx.x >> 6] = v[c];
-  __syncthreads();
-  if (threadIdx.x < 6) {
-    const int c = threadIdx.x;
-    double r = red[c][0];
-    for (int w = 1; w < 4; ++w) r = c < 3 ? fmin(r, red[c][w]) : fmax(r, red[c][w]);
-    box[6 * (size_t)blockIdx.x + c] = r;
-  }
+  const double v[3] = {src[k], src[(size_t)n + k], src[2 * (size_t)n + k]};
+  tile_box(v, true, threadIdx.x, red, box + 6 * (size_t)blockIdx.x);
 }
 
 void launch_tile_boxes(obem_ctx *ctx, int n, const double *src, double *box) {
   if (n > 0) hipLaunchKernelGGL(k_tile_boxes, dim3(nblk(n)), dim3(256), 0, ctx->stream, n, src, box);
 }
 
-// Sources in (charge sign, Hilbert) order: key of the i-th Hilbert-sorted
-// source, value its caller index.
-__global__ __launch_bounds__(256) void k_charge_key(int n, const int32_t *__restrict__ perm,
-                                                    const double *__restrict__ q, uint8_t *key, int32_t *idx) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) {
-    const int j = perm[i];
-    key[i] = q[j] < 0.0 ? 0 : (q[j] > 0.0 ? 1 : 2);
-    idx[i] = j;
+// Small sets, one workgroup each and two of them side by side: box, keys,
+// sort and (GATHER) copies in one launch instead of five to ten, each of which
+// costs its latency.  T threads of ITEMS points, stable block radix sort in
+// LDS.  Source copy and target order of 64 points took about 65 us before and
+// take 6, of 1,000 points 16, of 4,096 points 35; above 256 points the copies
+// are faster in a launch of their own (4,096: 51 us with them), above 4,096
+// the launches of order_large.
+constexpr int kSmallOrder = 4096;
+
+template <int T, int ITEMS, bool GATHER>
+__global__ __launch_bounds__(T) void k_order_small(OrderPair jobs) {
+  using Sort = hipcub::BlockRadixSort<uint32_t, T, ITEMS, int32_t>;
+  __shared__ typename Sort::TempStorage tmp;
+  __shared__ int32_t order[T * ITEMS];
+  __shared__ double red[6 * (T / 64)];
+  const OrderJob &J = jobs.job[blockIdx.x];
+  const int n = J.n, t = threadIdx.x;
+  double box[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+  for (int i = t; i < n; i += T) {
+    const double v[3] = {J.x[i], J.y[i], J.z[i]};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      box[c] = fmin(box[c], v[c]);
+      box[3 + c] = fmax(box[3 + c], v[c]);
+    }
+  }
+  block_box<T>(box, red);
+  // padding keys sort behind every point (equal keys keep their order)
+  uint32_t key[ITEMS];
+  int32_t idx[ITEMS];
+#pragma unroll
+  for (int u = 0; u < ITEMS; ++u) {
+    const int i = t * ITEMS + u;
+    idx[u] = i;
+    key[u] = i < n ? order_key(J, i, box, box + 3) : 0xffffffffu;
+  }
+  Sort(tmp).Sort(key, idx, 0, (J.q || J.species) ? 32 : 30);
+  if (!GATHER) {
+#pragma unroll
+    for (int u = 0; u < ITEMS; ++u)
+      if (t * ITEMS + u < n) J.perm[t * ITEMS + u] = idx[u];
+    return;
+  }
+#pragma unroll
+  for (int u = 0; u < ITEMS; ++u) order[t * ITEMS + u] = idx[u];
+  for (int i0 = 0; i0 < n; i0 += T) {
+    __syncthreads();  // order is written, the previous round's red consumed
+    const int i = i0 + t;
+    double v[3] = {0.0, 0.0, 0.0};
+    if (i < n) {
+      const int j = order[i];
+      J.perm[i] = j;
+      order_gather(J, i, j, v);
+    }
+    if (J.tbox)
+      tile_box(v, i < n, t & 255, red + 24 * (t >> 8), i / 256 * 256 < n ? J.tbox + 6 * (size_t)(i / 256) : nullptr);
   }
 }
 
-__global__ __launch_bounds__(256) void k_gather_src(int n, const int32_t *__restrict__ perm, const double *__restrict__ x,
-                                                    const double *__restrict__ y, const double *__restrict__ z,
-                                                    const double *__restrict__ q, double *out, int32_t *inv) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  const int j = perm[i];
-  out[i] = x[j];
-  out[(size_t)n + i] = y[j];
-  out[2 * (size_t)n + i] = z[j];
-  out[3 * (size_t)n + i] = q[j];
-  if (inv) inv[j] = i;
+// A large set: partial boxes, keys, one radix sort, copies.
+static obem_status order_large(obem_ctx *ctx, const OrderJob &J) {
+  const int n = J.n;
+  const int nb = std::min(256, nblk(n, 1024));
+  double *part = (double *)ws_get(ctx, WS_BBOX, sizeof(double) * 6 * nb);
+  uint32_t *k0 = (uint32_t *)ws_get(ctx, WS_KEYS0, sizeof(uint32_t) * n);
+  uint32_t *k1 = (uint32_t *)ws_get(ctx, WS_KEYS1, sizeof(uint32_t) * n);
+  int32_t *i0 = (int32_t *)ws_get(ctx, WS_IDX0, sizeof(int32_t) * n);
+  if (!part || !k0 || !k1 || !i0) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
+  hipLaunchKernelGGL(k_bbox_partial, dim3(nb), dim3(256), 0, ctx->stream, n, J.x, J.y, J.z, part);
+  hipLaunchKernelGGL(k_order_key, dim3(nblk(n)), dim3(256), 0, ctx->stream, J, nb, part, k0, i0);
+  const int bits = (J.q || J.species) ? 32 : 30;
+  size_t tmp_bytes = 0;
+  OBEM_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(nullptr, tmp_bytes, k0, k1, i0, J.perm, n, 0, bits, ctx->stream));
+  void *tmp = ws_get(ctx, WS_SORT_TMP, tmp_bytes + 256);
+  if (!tmp) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
+  OBEM_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(tmp, tmp_bytes, k0, k1, i0, J.perm, n, 0, bits, ctx->stream));
+  if (J.xs || J.inv || J.tbox) {
+    OrderPair one;
+    one.job[0] = J;
+    hipLaunchKernelGGL(k_order_gather, dim3(nblk(n), 1), dim3(256), 0, ctx->stream, one);
+  }
+  OBEM_HIP(ctx, hipGetLastError());
+  return OBEM_OK;
 }
 
-obem_status order_sources(obem_ctx *ctx, int64_t n64, const double *sx, const double *sy, const double *sz,
-                          const double *sq, bool want_inv, SourceOrder *out) {
-  const int n = (int)n64;
+obem_status order_points(obem_ctx *ctx, const OrderJob &a, const OrderJob &b) {
+  OBEM_PROF(ctx, "order");
+  OrderPair small;
+  int ns = 0;
+  for (const OrderJob *J : {&a, &b}) {
+    if (J->n == 0) continue;
+    if (J->n <= kSmallOrder) {
+      small.job[ns++] = *J;
+    } else {
+      const obem_status st = order_large(ctx, *J);
+      if (st) return st;
+    }
+  }
+  if (ns) {
+    const int m = std::max(small.job[0].n, small.job[1].n);
+    if (m <= 256) {
+      hipLaunchKernelGGL((k_order_small<256, 1, true>), dim3(ns), dim3(256), 0, ctx->stream, small);
+    } else {
+      if (m <= 1024)
+        hipLaunchKernelGGL((k_order_small<1024, 1, false>), dim3(ns), dim3(1024), 0, ctx->stream, small);
+      else
+        hipLaunchKernelGGL((k_order_small<1024, 4, false>), dim3(ns), dim3(1024), 0, ctx->stream, small);
+      hipLaunchKernelGGL(k_order_gather, dim3(nblk(m), ns), dim3(256), 0, ctx->stream, small);
+    }
+    OBEM_HIP(ctx, hipGetLastError());
+  }
+  return OBEM_OK;
+}
+
+// The jobs of a source copy and of a target order (workspace of ctx).
+static obem_status source_job(obem_ctx *ctx, int n, const double *sx, const double *sy, const double *sz,
+                              const double *sq, bool want_inv, OrderJob *J, SourceOrder *out) {
   const size_t nz = (size_t)n;
   out->n = n;
   if (n == 0) return OBEM_OK;
-  TargetOrder mo;
-  obem_status st = order_targets(ctx, n, sx, sy, sz, &mo);
-  if (st) return st;
-  uint8_t *key = (uint8_t *)ws_get(ctx, WS_SRCKEY, 2 * nz + 64);
-  int32_t *perm = (int32_t *)ws_get(ctx, WS_SRCPERM, sizeof(int32_t) * 2 * nz);
+  int32_t *perm = (int32_t *)ws_get(ctx, WS_SRCPERM, sizeof(int32_t) * nz);
   double *src = (double *)ws_get(ctx, WS_SRC, sizeof(double) * 4 * nz + nz + 64);
   double *tbox = (double *)ws_get(ctx, WS_TBOX, sizeof(double) * 6 * (size_t)nblk(n));
   int32_t *inv = want_inv ? (int32_t *)ws_get(ctx, WS_SRCINV, sizeof(int32_t) * nz) : nullptr;
-  if (!key || !perm || !src || !tbox || (want_inv && !inv)) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
-  hipLaunchKernelGGL(k_charge_key, dim3(nblk(n)), dim3(256), 0, ctx->stream, n, mo.perm, sq, key, perm);
-  size_t tb = 0;
-  OBEM_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(nullptr, tb, key, key + nz, perm, perm + nz, n, 0, 2, ctx->stream));
-  void *tmp = ws_get(ctx, WS_SORT_TMP2, tb + 256);
-  if (!tmp) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
-  OBEM_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(tmp, tb, key, key + nz, perm, perm + nz, n, 0, 2, ctx->stream));
-  hipLaunchKernelGGL(k_gather_src, dim3(nblk(n)), dim3(256), 0, ctx->stream, n, perm + nz, sx, sy, sz, sq, src, inv);
-  launch_tile_boxes(ctx, n, src, tbox);
-  OBEM_HIP(ctx, hipGetLastError());
+  if (!perm || !src || !tbox || (want_inv && !inv)) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
+  J->n = n;
+  J->x = sx;
+  J->y = sy;
+  J->z = sz;
+  J->q = sq;
+  J->perm = perm;
+  J->xs = src;
+  J->inv = inv;
+  J->tbox = tbox;
   out->x = src;
   out->y = src + nz;
   out->z = src + 2 * nz;
   out->q = src + 3 * nz;
   out->tbox = tbox;
   out->inv = inv;
-  out->perm = perm + nz;
+  out->perm = perm;
   return OBEM_OK;
 }
 
-obem_status order_targets(obem_ctx *ctx, int64_t n64, const double *tx, const double *ty, const double *tz,
-                          TargetOrder *out) {
-  int n = (int)n64;
+static obem_status target_job(obem_ctx *ctx, int n, const double *tx, const double *ty, const double *tz, OrderJob *J,
+                              TargetOrder *out) {
   out->n = n;
   if (n == 0) return OBEM_OK;
-  OBEM_PROF(ctx, "order");
-  const int nb = 256;
-  double *bbox = (double *)ws_get(ctx, WS_BBOX, sizeof(double) * (6 * nb + 6));
-  uint32_t *k0 = (uint32_t *)ws_get(ctx, WS_KEYS0, sizeof(uint32_t) * n);
-  uint32_t *k1 = (uint32_t *)ws_get(ctx, WS_KEYS1, sizeof(uint32_t) * n);
-  int32_t *i0 = (int32_t *)ws_get(ctx, WS_IDX0, sizeof(int32_t) * n);
-  int32_t *i1 = (int32_t *)ws_get(ctx, WS_IDX1, sizeof(int32_t) * n);
+  int32_t *perm = (int32_t *)ws_get(ctx, WS_IDX1, sizeof(int32_t) * n);
   double *xs = (double *)ws_get(ctx, WS_TSORT, sizeof(double) * 3 * (size_t)n);
-  if (!bbox || !k0 || !k1 || !i0 || !i1 || !xs) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
-  hipLaunchKernelGGL(k_bbox_partial, dim3(nb), dim3(256), 0, ctx->stream, n, tx, ty, tz, bbox + 6);
-  hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(256), 0, ctx->stream, nb, bbox + 6, bbox);
-  hipLaunchKernelGGL(k_curve_key, dim3(nblk(n)), dim3(256), 0, ctx->stream, n, tx, ty, tz, bbox, k0, i0);
-  size_t tmp_bytes = 0;
-  OBEM_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(nullptr, tmp_bytes, k0, k1, i0, i1, n, 0, 30, ctx->stream));
-  void *tmp = ws_get(ctx, WS_SORT_TMP, tmp_bytes + 256);
-  if (!tmp) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
-  OBEM_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(tmp, tmp_bytes, k0, k1, i0, i1, n, 0, 30, ctx->stream));
-  hipLaunchKernelGGL(k_gather3, dim3(nblk(n)), dim3(256), 0, ctx->stream, n, i1, tx, ty, tz, xs);
-  OBEM_HIP(ctx, hipGetLastError());
-  out->perm = i1;
+  if (!perm || !xs) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
+  J->n = n;
+  J->x = tx;
+  J->y = ty;
+  J->z = tz;
+  J->perm = perm;
+  J->xs = xs;
+  out->perm = perm;
   out->xs = xs;
   return OBEM_OK;
+}
+
+obem_status order_sources(obem_ctx *ctx, int64_t n, const double *sx, const double *sy, const double *sz,
+                          const double *sq, bool want_inv, SourceOrder *out) {
+  OrderJob J;
+  const obem_status st = source_job(ctx, (int)n, sx, sy, sz, sq, want_inv, &J, out);
+  return st ? st : order_points(ctx, J, OrderJob{});
+}
+
+obem_status order_targets(obem_ctx *ctx, int64_t n, const double *tx, const double *ty, const double *tz,
+                          TargetOrder *out) {
+  OrderJob J;
+  const obem_status st = target_job(ctx, (int)n, tx, ty, tz, &J, out);
+  return st ? st : order_points(ctx, J, OrderJob{});
+}
+
+obem_status order_both(obem_ctx *ctx, int64_t n_src, const double *sx, const double *sy, const double *sz,
+                       const double *sq, bool want_inv, SourceOrder *so, int64_t n_tgt, const double *tx,
+                       const double *ty, const double *tz, TargetOrder *to) {
+  OrderJob a, b;
+  obem_status st = source_job(ctx, (int)n_src, sx, sy, sz, sq, want_inv, &a, so);
+  if (!st) st = target_job(ctx, (int)n_tgt, tx, ty, tz, &b, to);
+  return st ? st : order_points(ctx, a, b);
 }
 
 // ---------------------------------------------------------------------------

@@ -61,7 +61,7 @@ struct DevBuf {
 enum WsSlot {
   WS_BBOX = 0, WS_KEYS0, WS_KEYS1, WS_IDX0, WS_IDX1, WS_SORT_TMP, WS_TSORT, WS_ACC, WS_PART,
   WS_NN, WS_MISC0, WS_MISC1, WS_MISC2, WS_MISC3, WS_MISC4, WS_MISC5, WS_MISC6, WS_MISC7,
-  WS_SOLVE0, WS_SOLVE1, WS_SOLVE2, WS_SRC, WS_SRCPERM, WS_SRCKEY, WS_SORT_TMP2, WS_TBOX, WS_MAP, WS_STATUS, WS_SRCINV, WS_PANEL,
+  WS_SOLVE0, WS_SOLVE1, WS_SOLVE2, WS_SRC, WS_SRCPERM, WS_TBOX, WS_MAP, WS_STATUS, WS_SRCINV, WS_PANEL,
   WS_SYMI, WS_SYMJ, WS_SYMR, WS_SYMM, WS_INC_IDX, WS_INC_DB, WS_MAPNODES, WS_COUNT
 };
 
@@ -177,6 +177,23 @@ struct ProfScope {
 #define OBEM_PROF(ctx, name) obem::ProfScope obem_prof_scope_(ctx, name)
 
 
+// One ordering: points (caller arrays) sorted by class (species, else sign of
+// the charge q, else none), then along the Hilbert curve, ties in caller
+// order.  Outputs: perm (ordered position -> caller index) and where not NULL
+// the ordered copy xs (x, y, z and q if given, n each), the inverse
+// permutation and the boxes of the 256-point tiles of the copy.
+struct OrderJob {
+  int n = 0;
+  const double *x = nullptr, *y = nullptr, *z = nullptr, *q = nullptr;
+  const int8_t *species = nullptr;
+  int32_t *perm = nullptr;
+  double *xs = nullptr;
+  int32_t *inv = nullptr;
+  double *tbox = nullptr;
+};
+// Runs one or two orderings (n = 0: none); small ones share a launch.
+obem_status order_points(obem_ctx *ctx, const OrderJob &a, const OrderJob &b);
+
 // Target ordering (Hilbert keys) used by the field kernels.
 struct TargetOrder {
   int32_t n = 0;
@@ -261,8 +278,7 @@ obem_status run_pair_once(obem_ctx *ctx, int n, int sbsz, int ns, int resident, 
                           const std::function<void(int, int, float *, float *)> &launch);
 
 // Copy of the point sources in (charge sign, Hilbert) order with per-256-tile
-// boxes (field.hip); inv (caller index -> position) when asked for.  Uses the
-// target-ordering workspace: call before order_targets of the targets.
+// boxes (field.hip); inv (caller index -> position) when asked for.
 struct SourceOrder {
   int32_t n = 0;
   const double *x = nullptr, *y = nullptr, *z = nullptr, *q = nullptr;
@@ -272,6 +288,10 @@ struct SourceOrder {
 };
 obem_status order_sources(obem_ctx *ctx, int64_t n, const double *sx, const double *sy, const double *sz,
                           const double *sq, bool want_inv, SourceOrder *out);
+// Both orderings of a field call with separate target order.
+obem_status order_both(obem_ctx *ctx, int64_t n_src, const double *sx, const double *sy, const double *sz,
+                       const double *sq, bool want_inv, SourceOrder *so, int64_t n_tgt, const double *tx,
+                       const double *ty, const double *tz, TargetOrder *to);
 void launch_tile_boxes(obem_ctx *ctx, int n, const double *src, double *box);
 obem_status launch_scatter(obem_ctx *ctx, const TargetOrder &to, const double *acc, double scale,
                            double *Ex, double *Ey, double *Ez, double *V);

@@ -679,17 +679,6 @@ __global__ __launch_bounds__(256) void k_scatter_nn(int n, const int32_t *__rest
   }
 }
 
-// Species key of the particles taken in the targets' Hilbert order.
-__global__ __launch_bounds__(256) void k_species_key(int n, const int32_t *__restrict__ perm,
-                                                     const int8_t *__restrict__ sp, uint8_t *key, int32_t *idx) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) {
-    const int j = perm[i];
-    key[i] = (uint8_t)(sp[j] & 3);
-    idx[i] = j;
-  }
-}
-
 // Source copy grouped by species, Hilbert order within a species (a stable
 // sort of the Hilbert-ordered particles by species): its 256-source tiles
 // each carry one charge, which the pairwise kernel takes out of the inner
@@ -945,36 +934,42 @@ static obem_status step_field(obem_ctx *ctx, obem_meshh *mesh, const double *sig
                               const obem_particles *S, int n, const obem_step_params *p, const uint8_t *dead,
                               const int8_t *status, double *E, int32_t *nn) {
   const size_t nz = (size_t)n;
-  uint8_t *skey = (uint8_t *)ws_get(ctx, WS_SRCKEY, 2 * nz + 64);
-  int32_t *sperm = (int32_t *)ws_get(ctx, WS_SRCPERM, sizeof(int32_t) * 2 * nz);
+  int32_t *sperm = (int32_t *)ws_get(ctx, WS_SRCPERM, sizeof(int32_t) * nz);
   double *srcb = (double *)ws_get(ctx, WS_SRC, sizeof(double) * 4 * nz + nz + 64);
   double *acc = (double *)ws_get(ctx, WS_ACC, sizeof(double) * 4 * nz);
   const int ntile = nbt(n);
   double *tbox = (double *)ws_get(ctx, WS_TBOX, sizeof(double) * 6 * (size_t)ntile);
   int32_t *nn_s = nn ? (int32_t *)ws_get(ctx, WS_MISC0, sizeof(int32_t) * nz) : nullptr;
   double *nnd = nn ? (double *)ws_get(ctx, WS_MISC3, sizeof(double) * nz) : nullptr;
-  if (!skey || !sperm || !srcb || !acc || !tbox || (nn && (!nn_s || !nnd)))
+  if (!sperm || !srcb || !acc || !tbox || (nn && (!nn_s || !nnd)))
     return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
   int8_t *ssp = (int8_t *)(srcb + 4 * nz);
+  // with the pair-once evaluation the targets take the source copy's order
+  const bool once = pair_once_applies(n, p->precision, p->soft, false);
   TargetOrder to;
-  obem_status st = order_targets(ctx, n, S->x, S->y, S->z, &to);
+  to.n = n;
+  OrderJob src, tgt;
+  src.n = n;
+  src.x = S->x;
+  src.y = S->y;
+  src.z = S->z;
+  src.species = S->species;
+  src.perm = sperm;
+  if (!once) {
+    tgt = src;
+    tgt.species = nullptr;
+    tgt.perm = to.perm = (int32_t *)ws_get(ctx, WS_IDX1, sizeof(int32_t) * nz);
+    tgt.xs = to.xs = (double *)ws_get(ctx, WS_TSORT, sizeof(double) * 3 * nz);
+    if (!to.perm || !to.xs) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
+  }
+  obem_status st = order_points(ctx, src, tgt);
   if (st) return st;
-  hipLaunchKernelGGL(k_species_key, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, to.perm, S->species, skey, sperm);
-  size_t tb = 0;
-  OBEM_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(nullptr, tb, skey, skey + nz, sperm, sperm + nz, n, 0, 2,
-                                                   ctx->stream));
-  void *tmp = ws_get(ctx, WS_SORT_TMP2, tb + 256);
-  if (!tmp) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
-  OBEM_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(tmp, tb, skey, skey + nz, sperm, sperm + nz, n, 0, 2,
-                                                   ctx->stream));
-  hipLaunchKernelGGL(k_gather_sources, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, sperm + nz, S->x, S->y, S->z,
+  hipLaunchKernelGGL(k_gather_sources, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, sperm, S->x, S->y, S->z,
                      S->species, dead, status, srcb, ssp);
   launch_tile_boxes(ctx, n, srcb, tbox);
   OBEM_HIP(ctx, hipGetLastError());
-  // with the pair-once evaluation the targets take the source copy's order
-  const bool once = pair_once_applies(n, p->precision, p->soft, false);
   if (once) {
-    to.perm = sperm + nz;
+    to.perm = sperm;
     to.xs = srcb;
   }
   Slots cells, pairs;
@@ -994,7 +989,7 @@ static obem_status step_field(obem_ctx *ctx, obem_meshh *mesh, const double *sig
   st = once ? launch_scatter(ctx, to, acc, kKe, E, E + nz, E + 2 * nz, nullptr)
             : launch_finish(ctx, to, cells, pairs, kKe, E, E + nz, E + 2 * nz, nullptr);
   if (st) return st;
-  if (nn) hipLaunchKernelGGL(k_scatter_nn, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, to.perm, nn_s, sperm + nz, nn);
+  if (nn) hipLaunchKernelGGL(k_scatter_nn, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, to.perm, nn_s, sperm, nn);
   OBEM_HIP(ctx, hipGetLastError());
   return OBEM_OK;
 }

@@ -140,3 +140,27 @@ def test_point_layouts(ctx):
             assert torch.equal(E, B.field_eval(ctx, None, None, y, q, y, 1e-7, B.OBEM_FP64, tgt_is_src=True))
         with pytest.raises(IndexError):
             B.field_eval(ctx, None, None, x[:, :2], q, x, 1e-7)
+
+
+@pytest.mark.parametrize("n", [1, 2, 127, 128, 129, 1024, 1025, 4095, 4096, 4097, 5000])
+@pytest.mark.parametrize("kind", ["spread", "same_cell", "line"])
+def test_orderings(ctx, orc, n, kind):
+    """Source copy and target order around the sizes of the one-workgroup
+    sort (128, 1,024 threads, 4,096): many points in one cell of the curve's
+    grid (ties keep the caller's order), on a line, charges of both signs and
+    zero, through the field with separate targets, against the oracle, and
+    the same bit for bit in a second call."""
+    rng = np.random.default_rng(n)
+    x = rng.uniform(size=(n, 3)) * 1e-4
+    if kind == "same_cell":
+        x[n // 3:] = x[0] + 1e-9 * rng.uniform(size=(n - n // 3, 3))
+    elif kind == "line":
+        x[:, 1:] = 2e-5
+    q = rng.choice([-W.E_CHARGE, 0.0, W.E_CHARGE], size=n)
+    xt = rng.uniform(size=(n, 3)) * 1e-4
+    ref, vref = orc.pair_field(xt, x, q, 1e-6, want_v=True)
+    for prec, tol in ((B.OBEM_FP64, 1e-12), (B.OBEM_MIXED, 1e-5)):
+        E, V = B.field_eval(ctx, None, None, dev(x), dev(q), dev(xt), 1e-6, prec, want_v=True)
+        E2, V2 = B.field_eval(ctx, None, None, dev(x), dev(q), dev(xt), 1e-6, prec, want_v=True)
+        assert torch.equal(E, E2) and torch.equal(V, V2)
+        assert np.abs(host(E) - ref).max() <= tol * max(np.abs(ref).max(), 1e-300)
