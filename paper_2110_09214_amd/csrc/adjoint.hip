@@ -1042,8 +1042,9 @@ __global__ __launch_bounds__(256) void k_scatter3(int n, const int32_t *__restri
 
 static void split_for(int nb_rows, int n_cols, int *nsplit, int *chunk) {
   int s = (kSplitWorkgroups + nb_rows - 1) / nb_rows;
-  s = std::max(1, std::min(s, (n_cols + 1023) / 1024));
-  s = std::min(s, 64);
+  s = std::max(1, std::min(s, (n_cols + kT - 1) / kT));
+  if ((int64_t)nb_rows * s > kFewWorkgroups) s = std::max(1, std::min(s, (n_cols + 1023) / 1024));
+  s = std::min(s, max_slots(nb_rows));
   int c = (n_cols + s - 1) / s;
   c = (c + kT - 1) / kT * kT;
   *chunk = c;
@@ -1136,7 +1137,7 @@ extern "C" obem_status field_eval_backward(obem_ctx *ctx, const obem_meshh *mesh
       // cell ranges of >= 64 cells (whole 64-cell tiles of the near kernel),
       // about kSplitWorkgroups workgroups in all
       int ns = std::max(1, std::min((kSplitWorkgroups + bt - 1) / bt, (N + 63) / 64));
-      ns = std::min(ns, 64);
+      ns = std::min(ns, max_slots(bt));
       int cchunk = (N + ns - 1) / ns;
       cchunk = (cchunk + 63) / 64 * 64;
       ns = (N + cchunk - 1) / cchunk;
@@ -1155,7 +1156,7 @@ extern "C" obem_status field_eval_backward(obem_ctx *ctx, const obem_meshh *mesh
     } else {
       // cell ranges as in the mixed path (whole tiles of kPTb cells)
       int ns = std::max(1, std::min((kSplitWorkgroups + bt - 1) / bt, (N + 63) / 64));
-      ns = std::min(ns, 64);
+      ns = std::min(ns, max_slots(bt));
       int cchunk = (N + ns - 1) / ns;
       cchunk = (cchunk + 63) / 64 * 64;
       ns = (N + cchunk - 1) / cchunk;

@@ -1051,7 +1051,7 @@ obem_status launch_panel_field(obem_ctx *ctx, const obem_meshh *m, const double 
   // cell ranges of >= 64 cells (a multiple of both LDS tiles), about
   // kSplitWorkgroups workgroups in all
   int ns = std::max(1, std::min((kSplitWorkgroups + bt - 1) / bt, (N + 63) / 64));
-  ns = std::min(ns, 64);
+  ns = std::min(ns, max_slots(bt));
   int cchunk = (N + ns - 1) / ns;
   cchunk = (cchunk + 63) / 64 * 64;
   ns = (N + cchunk - 1) / cchunk;
@@ -2069,10 +2069,11 @@ obem_status launch_pair_field(obem_ctx *ctx, int64_t n_src, const double *sx, co
   const int bt = nblk(n_t);
   // about 128k workgroups (64 rounds of the 2048 resident ones), so that the
   // last workgroups to start are short and the chip drains quickly at the
-  // end; chunks >= 512 sources
+  // end; chunks of at least one tile, of two where these fill the chip
   int nsplit = (kSplitWorkgroups + bt - 1) / bt;
-  nsplit = std::max(1, std::min(nsplit, (n_s + 511) / 512));
-  nsplit = std::min(nsplit, 64);
+  nsplit = std::max(1, std::min(nsplit, (n_s + kThreads - 1) / kThreads));
+  if ((int64_t)bt * nsplit > kFewWorkgroups) nsplit = std::max(1, std::min(nsplit, (n_s + 511) / 512));
+  nsplit = std::min(nsplit, max_slots(bt));
   int chunk = (n_s + nsplit - 1) / nsplit;
   chunk = (chunk + kThreads - 1) / kThreads * kThreads;
   nsplit = (n_s + chunk - 1) / chunk;

@@ -399,10 +399,13 @@ obem_status influence_rhs(obem_ctx *ctx, const obem_meshh *m, int64_t n_src, con
   const int bw = (prec == OBEM_MIXED) ? (N + kCB - 1) / kCB : bc;
   int nsplit = 1, chunk = std::max(n_s, 1);
   if (n_s > 0) {
-    nsplit = std::max(1, std::min((kSplitWorkgroups + bw - 1) / bw, (n_s + 1023) / 1024));
-    nsplit = std::min(nsplit, 64);
+    // whole blocks of the mixed far kernel, single tiles of the FP64 kernel
+    const int unit = prec == OBEM_MIXED ? kTI * kCS : kTI;
+    nsplit = std::max(1, std::min((kSplitWorkgroups + bw - 1) / bw, (n_s + unit - 1) / unit));
+    if ((int64_t)bw * nsplit > kFewWorkgroups) nsplit = std::max(1, std::min(nsplit, (n_s + 1023) / 1024));
+    nsplit = std::min(nsplit, max_slots(bw));
     chunk = (n_s + nsplit - 1) / nsplit;
-    chunk = (chunk + kTI * kCS - 1) / (kTI * kCS) * (kTI * kCS);
+    chunk = (chunk + unit - 1) / unit * unit;
     nsplit = (n_s + chunk - 1) / chunk;
   }
   // mixed: partial slots of the near kernel after those of the far kernel

@@ -45,6 +45,16 @@ constexpr double kQuadFp64 = 48.0;
 // keeps the drain at the end of a launch short (measured: 3 % faster pairwise
 // field than one round-robin pass of 15,625 long workgroups at 4M charges).
 constexpr int kSplitWorkgroups = 131072;
+// Launches of up to two rounds of resident workgroups are cut to single tiles
+// instead of two (or four) per workgroup: there a workgroup is a serial chain
+// on an idle chip.
+constexpr int kFewWorkgroups = 4096;
+// Most slots (splits of the cells, sources or targets) for bt tiles of points:
+// 64, and for few tiles up to 256.  Measured with 64 and 256: field at 300
+// points of 40,776 cells 384 and 160 us, at 100 points of 200,000 charges and
+// these cells 696 and 311 us; beyond 256 the sum over the slots costs more
+// than it gives.
+inline int max_slots(int bt) { return bt <= 4 ? 256 : (bt >= 16 ? 64 : 1024 / bt); }
 // Incremental re-solve of a tracking step (resolve = 3): at most kIncMax
 // changed right-hand-side entries per step, and a full refined solve after
 // kIncEvery incremental updates.

@@ -164,3 +164,38 @@ def test_orderings(ctx, orc, n, kind):
         E2, V2 = B.field_eval(ctx, None, None, dev(x), dev(q), dev(xt), 1e-6, prec, want_v=True)
         assert torch.equal(E, E2) and torch.equal(V, V2)
         assert np.abs(host(E) - ref).max() <= tol * max(np.abs(ref).max(), 1e-300)
+
+
+@pytest.mark.parametrize("n_t,n_s", [(3, 70001), (1025, 20001), (4097, 257)])
+def test_splits_of_few_targets(ctx, orc, n_t, n_s):
+    """Target counts on both sides of the slot rule (up to 4 tiles of 256, to
+    16, more) with many cells and sources: field, potential, gradients and
+    FP64 influence on a sample against the oracle, at the field tests'
+    tolerances."""
+    m = W.gem_cell_mesh(W.GemGeometry(m=3, n_r=2, n_cone=2, plain_h=48e-6))
+    rng = np.random.default_rng(n_t)
+    xt = W.gem_cell_points(n_t, seed=n_t)
+    xs, q, _ = W.gaussian_clouds(n_s - n_s // 3, n_s // 3, (0, 0, 230e-6), (0, 0, 210e-6), 50e-6, rng)
+    sig = 1e-6 * rng.normal(size=m.n)
+    w = rng.normal(size=(n_t, 3))
+    bm = bind(ctx, m)
+    at = np.concatenate([[0, n_t - 1], rng.choice(n_t, 1)])
+    Er, Vr = orc.panel_field(xt[at], m.a, m.b, m.c, sig, want_v=True)
+    Ep, Vp = orc.pair_field(xt[at], xs, q, 1e-7, want_v=True)
+    for prec, tol in ((B.OBEM_FP64, 1e-12), (B.OBEM_MIXED, 1e-5)):
+        E, V = B.field_eval(ctx, bm, dev(sig), dev(xs), dev(q), dev(xt), 1e-7, prec, want_v=True)
+        assert rel_l2(host(E)[at], Er + Ep) <= tol
+        assert rel_l2(host(V)[at], Vr + Vp) <= tol
+        # g_sigma is linear in the weights: sum_k sigma_k g_sigma_k = sum w . E_cells
+        gs, gt, gsrc = B.field_eval_backward(ctx, bm, dev(sig), dev(xs), dev(q), dev(xt), 1e-7, dev(w), prec)
+        Ec = B.field_eval(ctx, bm, dev(sig), None, None, dev(xt), 1e-7, prec)
+        lhs, rhs = float((dev(sig) * gs).sum()), float((dev(w) * Ec).sum())
+        assert abs(lhs - rhs) <= tol * float((dev(w) * Ec).abs().sum())
+        # translating charges and targets together leaves the pairwise term: g_t + g_s of it sum to 0
+        _, gt0, gs0 = B.field_eval_backward(ctx, None, None, dev(xs), dev(q), dev(xt), 1e-7, dev(w), prec)
+        s = (gt0.sum(0) + gs0.sum(0)).abs().max()
+        assert float(s) <= 10 * tol * float(gt0.abs().sum())
+    out = host(B.bem_influence(ctx, bm, dev(m.rhs), dev(xs[:n_t]), dev(q[:n_t]), B.OBEM_FP64))
+    ref = orc.influence(m, m.rhs, xs[:n_t], q[:n_t])
+    ref = ref[0] if isinstance(ref, tuple) else ref
+    assert np.abs(out - ref).max() <= 1e-11 * np.abs(ref - m.rhs).max() + 1e-15 * np.abs(m.rhs).max()
