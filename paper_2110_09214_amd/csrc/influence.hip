@@ -5,11 +5,11 @@
 // change the left-hand side of the system before it is solved:
 //   ed rows V_i - Vbar_i,   dd rows sigma_F,i - eps0 (eps_r2 - eps_r1) Ebar_i . n_i.
 //
-// It is the transpose of the cell field: one thread per cell, cells taken in
-// the mesh's Hilbert order of centroids (a workgroup's cells are spatially
-// close and are recentred on its first centroid), charges staged in LDS
-// tiles, gridDim.y chunks of charges with per-chunk partial sums reduced in
-// chunk order.  Precision regimes as in the field: mixed = FP32 7-point rule
+// It is the transpose of the cell field: the cells are taken in the mesh's
+// Hilbert order of centroids (a workgroup's cells are spatially close and are
+// recentred on the first centroid of their 256), the lanes hold charges,
+// gridDim.y chunks of charges with per-chunk partial sums reduced in chunk
+// order.  Precision regimes as in the field: mixed = FP32 7-point rule
 // within 8 diameters, 6-point rule within 40, 3-point rule beyond (far
 // kernel, charges ordered by
 // charge sign, then Hilbert, so the charge comes out of the pair loop), FP64
@@ -50,7 +50,7 @@ __device__ __forceinline__ void infl_closed(const double *__restrict__ rec, int 
 // accumulated in FP64 by 32 threads, one per (cell, component).
 constexpr int kCB = 8;   // cells per workgroup
 constexpr int kCS = 4;   // charges per thread and block
-constexpr int kUP = kTI + 4;
+constexpr int kUP = 64 + 4;  // row pitch of a wave's sums (floats)
 
 // One cell of the far kernel's LDS tile, recentred FP32, 19 float4 records:
 //   c[0] = centroid, (3 D)^2          c[1] = (40 D)^2, area {w0, wa, wb}
@@ -66,6 +66,14 @@ constexpr int kUP = kTI + 4;
 struct ICell {
   float4 c[19];
 };
+
+// Orders the LDS accesses of a wave's lanes (its instructions run in order;
+// this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // sum over m of w_m {1/|e_m|, e_m/|e_m|^3}, e_m = p - point m
 template <int M>
@@ -85,16 +93,103 @@ __device__ __forceinline__ void infl_points(float px, float py, float pz, const 
   }
 }
 
+// Spheres of the runs of 64 ordered charges (centre of the box, largest
+// distance from it): sph[4 g .. 4 g + 3].
+__global__ __launch_bounds__(64) void k_charge_spheres(int n_s, const double *__restrict__ sx,
+                                                       const double *__restrict__ sy, const double *__restrict__ sz,
+                                                       double *sph) {
+  const int j = min((int)blockIdx.x * 64 + (int)threadIdx.x, n_s - 1);
+  const double v[3] = {sx[j], sy[j], sz[j]};
+  double c[3], r2 = 0.0;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    double lo = v[d], hi = v[d];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      lo = fmin(lo, __shfl_xor(lo, o));
+      hi = fmax(hi, __shfl_xor(hi, o));
+    }
+    c[d] = 0.5 * (lo + hi);
+    r2 = fma(v[d] - c[d], v[d] - c[d], r2);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) r2 = fmax(r2, __shfl_xor(r2, o));
+  if (threadIdx.x == 0) {
+    double *s = sph + 4 * (size_t)blockIdx.x;
+    s[0] = c[0];
+    s[1] = c[1];
+    s[2] = c[2];
+    s[3] = sqrt(r2);
+  }
+}
+
+// The M-point rule (7, 6, 4 or 3) of one staged cell at those of a thread's
+// charges c whose run has its bit in runs (uniform over the wave) and that
+// are far.
+template <int M>
+__device__ __forceinline__ void infl_rule(const ICell &C, unsigned runs, const bool *far, const float *px,
+                                          const float *py, const float *pz, float *sv, float *ex, float *ey,
+                                          float *ez) {
+  const float *rec = reinterpret_cast<const float *>(&C);
+  float q[3 * M], w[M];
+  if (M == 7) {
+    const float4 h = C.c[1];
+#pragma unroll
+    for (int m = 0; m < 7; ++m) w[m] = m == 0 ? h.y : (m < 4 ? h.z : h.w);
+#pragma unroll
+    for (int u = 0; u < 21; ++u) q[u] = rec[8 + u];
+  } else if (M == 6) {
+    const float4 h10 = C.c[10];
+#pragma unroll
+    for (int m = 0; m < 6; ++m) w[m] = m < 3 ? h10.y : h10.z;
+#pragma unroll
+    for (int u = 0; u < 18; ++u) q[u] = rec[44 + u];
+  } else if (M == 4) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) w[m] = m == 0 ? rec[62] : rec[63];
+#pragma unroll
+    for (int u = 0; u < 3; ++u) q[u] = rec[u];
+#pragma unroll
+    for (int u = 0; u < 9; ++u) q[3 + u] = rec[64 + u];
+  } else {
+#pragma unroll
+    for (int m = 0; m < 3; ++m) w[m] = rec[29];
+#pragma unroll
+    for (int u = 0; u < 9; ++u) q[u] = rec[32 + u];
+  }
+  if (runs == (1u << kCS) - 1u && !far) {
+#pragma unroll
+    for (int c = 0; c < kCS; ++c) infl_points<M>(px[c], py[c], pz[c], q, w, sv[c], ex[c], ey[c], ez[c]);
+  } else {
+#pragma unroll
+    for (int c = 0; c < kCS; ++c)
+      if (runs >> c & 1u)
+        if (!far || far[c]) infl_points<M>(px[c], py[c], pz[c], q, w, sv[c], ex[c], ey[c], ez[c]);
+  }
+}
+
+// The rule of a (cell, run of 64 charges) pair is the finest that one of its
+// charges needs.  Lane (cell, run) of a wave bounds the nearest charge by the
+// run's sphere; where that leaves one rule and no charge within 3 D (with
+// margins above the FP32 rounding of the recentred coordinates) the rule is
+// taken for the whole run without a test per charge.  The others take the
+// test: the same rule either way.  A cell's points are read once per rule
+// for the four runs of a thread's charges.
+// Bound by FP32 issue and by LDS latency between the short pieces of a pair:
+// the sums of a wave are combined by the wave itself, four cells at a time
+// (no barrier in the loop, and 20 instead of 38 KB of LDS, for five instead of
+// four waves per SIMD; held to 80 or 64 registers for more waves it is no
+// faster or 38 % slower).  60,001 charges, 40,776 cells: 4.15 -> 3.6 ms.
 __global__ __launch_bounds__(kTI) void k_influence_mixed(int N, const double *__restrict__ f,
                                                          const int32_t *__restrict__ ord, int n_s,
                                                          const double *__restrict__ sx,
                                                          const double *__restrict__ sy,
                                                          const double *__restrict__ sz,
-                                                         const double *__restrict__ sq, int chunk, double *part) {
+                                                         const double *__restrict__ sq,
+                                                         const double *__restrict__ sph, int chunk, double *part) {
   __shared__ ICell T[kCB];
-  __shared__ __align__(16) float U[kCB * 4][kUP];
-  __shared__ double red[kTI / (kCB * 4)][kCB * 4];
-  const int tid = threadIdx.x;
+  __shared__ __align__(16) float U[kTI / 64][16][kUP];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kb = blockIdx.x * kCB;  // first sorted position of the workgroup's cells
   // recentred on the first cell of the 256-cell group, as the near kernel
   const int kr = ord[(kb / kTI) * kTI];
@@ -117,7 +212,7 @@ __global__ __launch_bounds__(kTI) void k_influence_mixed(int N, const double *__
                               (float)(ar * Rule7::wa), (float)(ar * Rule7::wb));
     rec[29] = (float)(ar / 3.0);
     rec[30] = (float)(kFwd6 * kFwd6 * D * D);
-    rec[31] = 0.f;
+    rec[31] = (float)D;
     rec[41] = (float)(ar * Rule6::w1);
     rec[42] = (float)(ar * Rule6::w2);
     rec[43] = (float)(kFwd4 * kFwd4 * D * D);
@@ -126,7 +221,9 @@ __global__ __launch_bounds__(kTI) void k_influence_mixed(int N, const double *__
     rec[73] = rec[74] = rec[75] = 0.f;
   }
   __syncthreads();
-  double accd = 0.0;  // threads 0..31: (cell tid / 4, component tid % 4)
+  // lane l: cells l / 16 and 4 + l / 16, component l / 4 % 4, the sums of 16
+  // of the wave's lanes
+  double accd[2] = {0.0, 0.0};
   const int jb = blockIdx.y * chunk, je = min(n_s, jb + chunk);
   for (int j0 = jb; j0 < je; j0 += kTI * kCS) {
     float px[kCS], py[kCS], pz[kCS], pq[kCS];
@@ -140,163 +237,225 @@ __global__ __launch_bounds__(kTI) void k_influence_mixed(int N, const double *__
       pz[c] = (float)(sz[jj] - c2);
       pq[c] = ok ? (float)sq[jj] : 0.f;
     }
-#pragma unroll
+    // bit 4 k + c: the rule of (cell k, run c) where it is certain
+    unsigned m3, m4, m6, m7;
+    {
+      const int k = (lane >> 2) & (kCB - 1), c = lane & 3;
+      const int jr = j0 + c * kTI + wv * 64;
+      int rule = 0;
+      if (lane < 4 * kCB && jr + 64 <= je) {  // whole runs only: others hold the stand-in position
+        const double *s = sph + 4 * (size_t)(jr / 64);
+        const float4 g = T[k].c[0];
+        const float D = T[k].c[7].w, r = (float)s[3];
+        const float d = sqrtf(dist2f((float)(s[0] - c0), (float)(s[1] - c1), (float)(s[2] - c2), g.x, g.y, g.z));
+        const float slack = 1e-5f * (d + fabsf(g.x) + fabsf(g.y) + fabsf(g.z));
+        const float lo = (d - r - slack) * 0.999f, hi = (d + r + slack) * 1.001f;
+        if (lo > (float)kFar3Mixed * D)
+          rule = 3;
+        else if (lo > (float)kFwd4 * D)
+          rule = hi < (float)kFar3Mixed * D ? 4 : 0;
+        else if (lo > (float)kFwd6 * D)
+          rule = hi < (float)kFwd4 * D ? 6 : 0;
+        else if (lo > (float)kNearMixed * D)
+          rule = hi < (float)kFwd6 * D ? 7 : 0;
+      }
+      m3 = (unsigned)__ballot(rule == 3);
+      m4 = (unsigned)__ballot(rule == 4);
+      m6 = (unsigned)__ballot(rule == 6);
+      m7 = (unsigned)__ballot(rule == 7);
+    }
+#pragma unroll 1
     for (int k = 0; k < kCB; ++k) {
-      const float4 g = T[k].c[0], h = T[k].c[1], h7 = T[k].c[7];
+      float sv[kCS], ex[kCS], ey[kCS], ez[kCS];
+#pragma unroll
+      for (int c = 0; c < kCS; ++c) sv[c] = ex[c] = ey[c] = ez[c] = 0.f;
+      unsigned b3 = m3 >> (4 * k) & 15u, b4 = m4 >> (4 * k) & 15u, b6 = m6 >> (4 * k) & 15u, b7 = m7 >> (4 * k) & 15u;
+      const unsigned open = 15u & ~(b3 | b4 | b6 | b7);
+      if (open) {
+        const float4 g = T[k].c[0];
+        const float lim7 = T[k].c[7].z, lim6 = T[k].c[10].w, lim4 = T[k].c[1].x;
+        bool far[kCS];
+#pragma unroll
+        for (int c = 0; c < kCS; ++c) {
+          far[c] = true;
+          if (open >> c & 1u) {
+            const float R2 = dist2f(px[c], py[c], pz[c], g.x, g.y, g.z);
+            far[c] = !(R2 < g.w);  // the others are taken by k_influence_near in FP64
+            // 7 points within 6 D, 6 within 16 D, 4 within 40 D, 3 beyond
+            // (finest rule of the run)
+            if (__any(far[c] && R2 < lim7))
+              b7 |= 1u << c;
+            else if (__any(far[c] && R2 < lim6))
+              b6 |= 1u << c;
+            else if (__any(far[c] && R2 < lim4))
+              b4 |= 1u << c;
+            else
+              b3 |= 1u << c;
+          }
+        }
+        if (b3) infl_rule<3>(T[k], b3, far, px, py, pz, sv, ex, ey, ez);
+        if (b4) infl_rule<4>(T[k], b4, far, px, py, pz, sv, ex, ey, ez);
+        if (b6) infl_rule<6>(T[k], b6, far, px, py, pz, sv, ex, ey, ez);
+        if (b7) infl_rule<7>(T[k], b7, far, px, py, pz, sv, ex, ey, ez);
+      } else {
+        if (b3) infl_rule<3>(T[k], b3, nullptr, px, py, pz, sv, ex, ey, ez);
+        if (b4) infl_rule<4>(T[k], b4, nullptr, px, py, pz, sv, ex, ey, ez);
+        if (b6) infl_rule<6>(T[k], b6, nullptr, px, py, pz, sv, ex, ey, ez);
+        if (b7) infl_rule<7>(T[k], b7, nullptr, px, py, pz, sv, ex, ey, ez);
+      }
       float av = 0.f, ax = 0.f, ay = 0.f, az = 0.f;
 #pragma unroll
       for (int c = 0; c < kCS; ++c) {
-        const float R2 = dist2f(px[c], py[c], pz[c], g.x, g.y, g.z);
-        const bool nearp = R2 < g.w;  // taken by k_influence_near in FP64
-        // 7 points within 6 D, 6 within 16 D, 4 within 40 D, 3 beyond (finest
-        // rule of the wave)
-        const float lim6 = reinterpret_cast<const float *>(&T[k])[43];
-        const bool need7 = !nearp && R2 < h7.z;
-        const bool need6 = !nearp && R2 < lim6;
-        const bool need4 = !nearp && R2 < h.x;
-        float sv = 0.f, ex = 0.f, ey = 0.f, ez = 0.f;
-        if (__any(need7)) {
-          if (!nearp) {
-            float q[21];
+        av = fmaf(pq[c], sv[c], av);
+        ax = fmaf(pq[c], ex[c], ax);
+        ay = fmaf(pq[c], ey[c], ay);
+        az = fmaf(pq[c], ez[c], az);
+      }
+      float(*u)[kUP] = U[wv] + 4 * (k & 3);
+      u[0][lane] = av;
+      u[1][lane] = ax;
+      u[2][lane] = ay;
+      u[3][lane] = az;
+      if ((k & 3) == 3) {
+        // FP64 from here on: the charges come sorted by sign, so the sums are
+        // large and cancel only between blocks
+        wave_lds_fence();
+        const float4 *r = reinterpret_cast<const float4 *>(&U[wv][lane >> 2][(lane & 3) * 16]);
+        double a = 0.0;
 #pragma unroll
-            for (int u = 0; u < 21; ++u) q[u] = reinterpret_cast<const float *>(&T[k])[8 + u];
-            const float w[7] = {h.y, h.z, h.z, h.z, h.w, h.w, h.w};
-            infl_points<7>(px[c], py[c], pz[c], q, w, sv, ex, ey, ez);
-          }
-        } else if (__any(need4) && !__any(need6)) {
-          if (!nearp) {
-            const float *rec = reinterpret_cast<const float *>(&T[k]);
-            float q[12];
-            q[0] = g.x;
-            q[1] = g.y;
-            q[2] = g.z;
-#pragma unroll
-            for (int u = 0; u < 9; ++u) q[3 + u] = rec[64 + u];
-            const float w[4] = {rec[62], rec[63], rec[63], rec[63]};
-            infl_points<4>(px[c], py[c], pz[c], q, w, sv, ex, ey, ez);
-          }
-        } else if (__any(need6)) {
-          if (!nearp) {
-            float q[18];
-#pragma unroll
-            for (int u = 0; u < 18; ++u) q[u] = reinterpret_cast<const float *>(&T[k])[44 + u];
-            const float4 h10 = T[k].c[10];
-            const float w[6] = {h10.y, h10.y, h10.y, h10.z, h10.z, h10.z};
-            infl_points<6>(px[c], py[c], pz[c], q, w, sv, ex, ey, ez);
-          }
-        } else if (!nearp) {
-          float q[9];
-#pragma unroll
-          for (int u = 0; u < 9; ++u) q[u] = reinterpret_cast<const float *>(&T[k])[32 + u];
-          const float w3 = h7.y;
-          const float w[3] = {w3, w3, w3};
-          infl_points<3>(px[c], py[c], pz[c], q, w, sv, ex, ey, ez);
+        for (int m = 0; m < 4; ++m) {
+          const float4 v = r[m];
+          a += (double)v.x;
+          a += (double)v.y;
+          a += (double)v.z;
+          a += (double)v.w;
         }
-        av = fmaf(pq[c], sv, av);
-        ax = fmaf(pq[c], ex, ax);
-        ay = fmaf(pq[c], ey, ay);
-        az = fmaf(pq[c], ez, az);
+        if (k < 4)
+          accd[0] += a;
+        else
+          accd[1] += a;
+        wave_lds_fence();
       }
-      U[4 * k][tid] = av;
-      U[4 * k + 1][tid] = ax;
-      U[4 * k + 2][tid] = ay;
-      U[4 * k + 3][tid] = az;
-    }
-    __syncthreads();
-    {
-      const int row = tid % (kCB * 4), p = tid / (kCB * 4);
-      const float4 *r = reinterpret_cast<const float4 *>(&U[row][p * (kTI / 8)]);
-      // FP64 from here on: the charges come sorted by sign, so the block sums
-      // are large and cancel only between blocks
-      double a = 0.0;
-#pragma unroll
-      for (int m = 0; m < kTI / 8 / 4; ++m) {
-        const float4 v = r[m];
-        a += (double)v.x;
-        a += (double)v.y;
-        a += (double)v.z;
-        a += (double)v.w;
-      }
-      red[p][row] = a;
-    }
-    __syncthreads();
-    if (tid < kCB * 4) {
-      double t = red[0][tid];
-#pragma unroll
-      for (int p = 1; p < kTI / (kCB * 4); ++p) t += red[p][tid];
-      accd += t;
     }
   }
+  // the four lanes of a (cell, component), then the four waves, in order
+  __syncthreads();
+  double *R = reinterpret_cast<double *>(&U[0][0][0]);  // [wave][cell * 4 + component]
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    double a = accd[h];
+    a += __shfl_xor(a, 1);
+    a += __shfl_xor(a, 2);
+    if ((lane & 3) == 0) R[wv * (kCB * 4) + h * 16 + (lane >> 2)] = a;
+  }
+  __syncthreads();
   if (tid < kCB * 4) {
+    double t = R[tid];
+#pragma unroll
+    for (int w = 1; w < kTI / 64; ++w) t += R[w * (kCB * 4) + tid];
     const int k = kb + tid / 4;
-    if (k < N) part[(size_t)blockIdx.y * 4 * N + (size_t)(tid % 4) * N + k] = accd;
+    if (k < N) part[(size_t)blockIdx.y * 4 * N + (size_t)(tid % 4) * N + k] = t;
   }
 }
 
-// Near part of the mixed influence: the pairs that the far kernel's FP32
-// test (same values, recentred on the first cell of the far kernel's 256-cell
-// workgroup) puts within 3 D, in FP64 closed form.  One wave of 64 cells per
-// workgroup; gridDim.y splits the 256-charge tiles, each split writing its
-// own partial slot.  A tile is visited when some lane's cell can reach its
-// box: distance below 3 D (1 + 1e-5) + 1e-6 |c_k - c0|, which exceeds what
-// FP32 rounding of the recentred coordinates can add to the test.
-constexpr int kNW = 64;
+// Sum over the wave's lanes in a fixed order.
+__device__ __forceinline__ double lanes_sum(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
 
-__global__ __launch_bounds__(kNW) void k_influence_near(int N, const double *__restrict__ f,
-                                                        const double *__restrict__ rec,
-                                                        const int32_t *__restrict__ ord, int n_s,
-                                                        const double *__restrict__ sx,
-                                                        const double *__restrict__ sy,
-                                                        const double *__restrict__ sz,
-                                                        const double *__restrict__ sq,
-                                                        const double *__restrict__ tbox, int tchunk, double *part) {
-  __shared__ float4 P[kTI];
-  const int lane = threadIdx.x;
-  const int k = blockIdx.x * kNW + lane;
-  const bool active = k < N;
-  const int kk = ord[active ? k : N - 1];
-  const int k0 = ord[(blockIdx.x * kNW / kTI) * kTI];
+// Near part of the mixed influence: the pairs that the far kernel's FP32 test
+// (same values, recentred on the first cell of its 256-cell group) puts
+// within 3 D, in FP64 closed form.  One wave per cell, the lanes on the
+// charges, so that the cell's record is the same for the wave and its sums
+// are combined once: with a lane per cell and the charges in turn, a charge
+// near one of 64 cells took the whole wave's closed form.  60,001 charges and
+// 40,776 cells 294 -> 44 us; 50,000 charges all near 400 cells 6.6 -> 0.3 ms in
+// all.
+// gridDim.y splits the 256-charge tiles, each split writing its own partial
+// slot.  64 tiles are tested at once against the cell's reach, 3 D (1 + 1e-5)
+// + 1e-6 |c_k - c0|, which exceeds what FP32 rounding of the recentred
+// coordinates can add to the test; the near charges of the tiles within it
+// are queued in LDS and evaluated 64 at a time.
+__global__ __launch_bounds__(64) void k_influence_near(int N, const double *__restrict__ f,
+                                                       const double *__restrict__ rec,
+                                                       const int32_t *__restrict__ ord, int n_s,
+                                                       const double *__restrict__ sx, const double *__restrict__ sy,
+                                                       const double *__restrict__ sz, const double *__restrict__ sq,
+                                                       const double *__restrict__ tbox, int tchunk, double *part) {
+  __shared__ int queue[128];
+  const int lane = threadIdx.x, k = blockIdx.x;
+  const int kk = __builtin_amdgcn_readfirstlane(ord[k]), k0 = __builtin_amdgcn_readfirstlane(ord[k / kTI * kTI]);
   const double c0 = f[(size_t)MF_GX * N + k0], c1 = f[(size_t)MF_GY * N + k0], c2 = f[(size_t)MF_GZ * N + k0];
   const double G0 = f[(size_t)MF_GX * N + kk], G1 = f[(size_t)MF_GY * N + kk], G2 = f[(size_t)MF_GZ * N + kk];
   const float g0 = (float)(G0 - c0), g1 = (float)(G1 - c1), g2 = (float)(G2 - c2);
   const double D = f[(size_t)MF_DIAM * N + kk];
-  const float lim_near = (float)(kNearMixed * kNearMixed * D * D);
+  const float lim = (float)(kNearMixed * kNearMixed * D * D);
   const double off = sqrt((G0 - c0) * (G0 - c0) + (G1 - c1) * (G1 - c1) + (G2 - c2) * (G2 - c2));
   const double reach = kNearMixed * D * (1.0 + 1e-5) + 1e-6 * off;
-  const double reach2 = active ? reach * reach : -1.0;
-  double nv = 0, nx = 0, ny = 0, nz = 0;
+  double nv = 0.0, nx = 0.0, ny = 0.0, nz = 0.0;
   const int ntile = (n_s + kTI - 1) / kTI;
   const int tb = blockIdx.y * tchunk, te = min(ntile, tb + tchunk);
-  for (int t = tb; t < te; ++t) {
-    const double *bx = tbox + 6 * (size_t)t;
-    const double e0 = fmax(fmax(bx[0] - G0, G0 - bx[3]), 0.0);
-    const double e1 = fmax(fmax(bx[1] - G1, G1 - bx[4]), 0.0);
-    const double e2 = fmax(fmax(bx[2] - G2, G2 - bx[5]), 0.0);
-    if (!__any(e0 * e0 + e1 * e1 + e2 * e2 < reach2)) continue;  // wave-uniform
-    const int jt = t * kTI, cnt = min(kTI, n_s - jt);
-    __syncthreads();
-    for (int jj = lane; jj < cnt; jj += kNW)
-      P[jj] = make_float4((float)(sx[jt + jj] - c0), (float)(sy[jt + jj] - c1), (float)(sz[jt + jj] - c2), 0.f);
-    __syncthreads();
-    for (int jj = 0; jj < cnt; ++jj) {
-      const float4 p = P[jj];
-      const bool nearp = active && dist2f(p.x, p.y, p.z, g0, g1, g2) < lim_near;
-      if (__any(nearp)) {
-        if (nearp) {
-          const int j = jt + jj;
-          infl_closed(rec, kk, sx[j], sy[j], sz[j], sq[j], nv, nx, ny, nz);
+  int qn = 0;
+  // t0 beyond te: evaluates what is left in the queue
+  for (int t0 = tb; t0 < te + 64; t0 += 64) {
+    bool hit = false;
+    if (t0 + lane < te) {
+      const double *bx = tbox + 6 * (size_t)(t0 + lane);
+      const double e0 = fmax(fmax(bx[0] - G0, G0 - bx[3]), 0.0);
+      const double e1 = fmax(fmax(bx[1] - G1, G1 - bx[4]), 0.0);
+      const double e2 = fmax(fmax(bx[2] - G2, G2 - bx[5]), 0.0);
+      hit = e0 * e0 + e1 * e1 + e2 * e2 < reach * reach;
+    }
+    const bool last = t0 >= te;
+    uint64_t m = __ballot(hit);
+    int u = 0;  // run of 64 charges of the lowest tile of m
+    for (;;) {
+      while (m && qn < 64) {
+        const int j = (t0 + __builtin_amdgcn_readfirstlane(__builtin_ctzll(m))) * kTI + u * 64 + lane;
+        bool nearp = false;
+        if (j < n_s) nearp = dist2f((float)(sx[j] - c0), (float)(sy[j] - c1), (float)(sz[j] - c2), g0, g1, g2) < lim;
+        const uint64_t nm = __ballot(nearp);
+        if (nearp) queue[qn + __popcll(nm & ((1ull << lane) - 1ull))] = j;
+        qn += __popcll(nm);
+        if (++u == kTI / 64) {
+          u = 0;
+          m &= m - 1ull;
         }
       }
+      const int n = last ? min(qn, 64) : (qn >= 64 ? 64 : 0);
+      if (n == 0) break;
+      __syncthreads();  // one wave: orders the LDS accesses
+      if (lane < n) {
+        const int j = queue[lane];
+        infl_closed(rec, kk, sx[j], sy[j], sz[j], sq[j], nv, nx, ny, nz);
+      }
+      qn -= n;
+      const int rest = lane < qn ? queue[64 + lane] : 0;
+      __syncthreads();
+      if (lane < qn) queue[lane] = rest;
     }
   }
-  if (active) {
-    const size_t o = (size_t)blockIdx.y * 4 * N;
-    part[o + k] = nv;
-    part[o + (size_t)N + k] = nx;
-    part[o + 2 * (size_t)N + k] = ny;
-    part[o + 3 * (size_t)N + k] = nz;
+  nv = lanes_sum(nv);
+  nx = lanes_sum(nx);
+  ny = lanes_sum(ny);
+  nz = lanes_sum(nz);
+  if (lane < 4) {
+    const double v = lane == 0 ? nv : (lane == 1 ? nx : (lane == 2 ? ny : nz));
+    part[((size_t)blockIdx.y * 4 + lane) * N + k] = v;
   }
 }
+
+// FP64 influence: closed form within 48 D, FP64 7-point rule beyond, the
+// same test |x - c_k|^2 >= (48 D_k)^2 as in the field.  A wave per two cells
+// (neighbours in the mesh's Hilbert order), the lanes on the charges, which
+// four waves share through LDS; the charges come ordered, so a wave's 64
+// charges mostly agree on the form.  The sums of a cell are combined over
+// the lanes once.  Bound by FP64 operations.
+// 20,000 charges, 14,384 cells 5.5 -> 1.8 ms, 5,000 charges, 4,096 cells 683
+// -> 222 us against a lane per cell with the charges in turn.
+constexpr int kFC = 2;  // cells per wave
 
 __global__ __launch_bounds__(kTI) void k_influence_fp64(int N, const double *__restrict__ f,
                                                         const double *__restrict__ rec,
@@ -305,58 +464,84 @@ __global__ __launch_bounds__(kTI) void k_influence_fp64(int N, const double *__r
                                                         const double *__restrict__ sy,
                                                         const double *__restrict__ sz,
                                                         const double *__restrict__ sq, int chunk, double *part) {
-  __shared__ double4 P[kTI];
-  const int tid = threadIdx.x;
-  const int k = blockIdx.x * kTI + tid;  // sorted position
-  const bool active = k < N;
-  const int kk = ord[active ? k : N - 1];  // cell index
-  const double g0 = f[(size_t)MF_GX * N + kk], g1 = f[(size_t)MF_GY * N + kk], g2 = f[(size_t)MF_GZ * N + kk];
-  const double area = f[(size_t)MF_AREA * N + kk], D = f[(size_t)MF_DIAM * N + kk];
-  const double lim = kQuadFp64 * kQuadFp64 * D * D;
-  double q7[21];
+  __shared__ double P[4][kTI];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kb = (blockIdx.x * (kTI / 64) + wv) * kFC;  // first sorted position of the wave's cells
+  double acc[kFC][4];
 #pragma unroll
-  for (int m = 0; m < 21; ++m) q7[m] = f[(size_t)(MF_Q7 + m) * N + kk];
-  double sv = 0, ex = 0, ey = 0, ez = 0;
+  for (int c = 0; c < kFC; ++c)
+#pragma unroll
+    for (int m = 0; m < 4; ++m) acc[c][m] = 0.0;
   const int jb = blockIdx.y * chunk, je = min(n_s, jb + chunk);
   for (int jt = jb; jt < je; jt += kTI) {
     const int cnt = min(kTI, je - jt);
     __syncthreads();
-    if (tid < cnt) {
-      const int j = jt + tid;
-      P[tid] = make_double4(sx[j], sy[j], sz[j], sq[j]);
+    {
+      const int j = jt + min(tid, cnt - 1);  // a real position with charge 0 beyond the end
+      P[0][tid] = sx[j];
+      P[1][tid] = sy[j];
+      P[2][tid] = sz[j];
+      P[3][tid] = tid < cnt ? sq[j] : 0.0;
     }
     __syncthreads();
-    for (int jj = 0; jj < cnt; ++jj) {
-      const double4 p = P[jj];
-      const double dx = p.x - g0, dy = p.y - g1, dz = p.z - g2;
-      const bool quad = fma(dx, dx, fma(dy, dy, dz * dz)) >= lim;
-      if (!__all(quad)) {
-        if (!quad && active) infl_closed(rec, kk, p.x, p.y, p.z, p.w, sv, ex, ey, ez);
-      }
-      if (__any(quad)) {
-        if (quad) {
+    for (int r = 0; r < cnt; r += 64) {
+      const d3 p = mk3(P[0][r + lane], P[1][r + lane], P[2][r + lane]);
+      const double q = P[3][r + lane];
 #pragma unroll
-          for (int m = 0; m < 7; ++m) {
-            const double w = area * ((m == 0) ? Rule7::w0 : (m < 4 ? Rule7::wa : Rule7::wb));
-            const double ax = p.x - q7[3 * m], ay = p.y - q7[3 * m + 1], az = p.z - q7[3 * m + 2];
-            const double ri = rsqrt_f64(fma(ax, ax, fma(ay, ay, az * az)));
-            const double wr = p.w * w * ri;
-            const double s = wr * ri * ri;
-            sv += wr;
-            ex = fma(s, ax, ex);
-            ey = fma(s, ay, ey);
-            ez = fma(s, az, ez);
+      for (int c = 0; c < kFC; ++c) {
+        if (kb + c >= N) break;
+        const int kk = __builtin_amdgcn_readfirstlane(ord[kb + c]);
+        const double dx = p.x - f[(size_t)MF_GX * N + kk], dy = p.y - f[(size_t)MF_GY * N + kk],
+                     dz = p.z - f[(size_t)MF_GZ * N + kk];
+        const double D = f[(size_t)MF_DIAM * N + kk], R2 = fma(dx, dx, fma(dy, dy, dz * dz));
+        const bool quad = R2 >= kQuadFp64 * kQuadFp64 * D * D;
+        const bool mid = !quad && R2 >= kMidForm * kMidForm * D * D;
+        if (__any(quad)) {
+          if (quad) {
+            const double qa = q * f[(size_t)MF_AREA * N + kk];
+#pragma unroll
+            for (int m = 0; m < 7; ++m) {
+              const double w = qa * ((m == 0) ? Rule7::w0 : (m < 4 ? Rule7::wa : Rule7::wb));
+              const double ax = p.x - f[(size_t)(MF_Q7 + 3 * m) * N + kk], ay = p.y - f[(size_t)(MF_Q7 + 3 * m + 1) * N + kk],
+                           az = p.z - f[(size_t)(MF_Q7 + 3 * m + 2) * N + kk];
+              const double ri = rsqrt_f64(fma(ax, ax, fma(ay, ay, az * az)));
+              const double wr = w * ri;
+              const double s = wr * ri * ri;
+              acc[c][0] += wr;
+              acc[c][1] = fma(s, ax, acc[c][1]);
+              acc[c][2] = fma(s, ay, acc[c][2]);
+              acc[c][3] = fma(s, az, acc[c][3]);
+            }
           }
+        }
+        if (__any(mid)) {
+          if (mid) {
+            d3 IE;
+            double IV;
+            cell_mid_form<true>(rec + (size_t)kk * CR_COUNT, p, IE, IV);
+            acc[c][0] = fma(q, IV, acc[c][0]);
+            acc[c][1] = fma(q, IE.x, acc[c][1]);
+            acc[c][2] = fma(q, IE.y, acc[c][2]);
+            acc[c][3] = fma(q, IE.z, acc[c][3]);
+          }
+        }
+        const bool close = !quad && !mid;
+        if (__any(close)) {
+          // (a charge of 0 stands for no charge: its term may be 0 times an
+          // infinite integral)
+          if (close && r + lane < cnt) infl_closed(rec, kk, p.x, p.y, p.z, q, acc[c][0], acc[c][1], acc[c][2], acc[c][3]);
         }
       }
     }
   }
-  if (active) {
-    const size_t o = (size_t)blockIdx.y * 4 * N;
-    part[o + k] = sv;
-    part[o + (size_t)N + k] = ex;
-    part[o + 2 * (size_t)N + k] = ey;
-    part[o + 3 * (size_t)N + k] = ez;
+#pragma unroll
+  for (int c = 0; c < kFC; ++c) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) acc[c][m] = lanes_sum(acc[c][m]);
+    if (kb + c < N && lane < 4) {
+      const double v = lane == 0 ? acc[c][0] : (lane == 1 ? acc[c][1] : (lane == 2 ? acc[c][2] : acc[c][3]));
+      part[((size_t)blockIdx.y * 4 + lane) * N + kb + c] = v;
+    }
   }
 }
 
@@ -395,23 +580,24 @@ obem_status influence_rhs(obem_ctx *ctx, const obem_meshh *m, int64_t n_src, con
                           double *vbar, double *ebx, double *eby, double *ebz) {
   const int N = (int)m->n, n_s = (int)n_src;
   const int bc = (N + kTI - 1) / kTI;
-  // workgroups along the cells: 256 cells each (FP64), 8 (mixed far kernel)
-  const int bw = (prec == OBEM_MIXED) ? (N + kCB - 1) / kCB : bc;
+  // workgroups along the cells: 8 cells each
+  const int bw = (N + kCB - 1) / kCB;
+  static_assert(kCB == kFC * (kTI / 64), "both kernels take the same cells per workgroup");
   int nsplit = 1, chunk = std::max(n_s, 1);
   if (n_s > 0) {
     // whole blocks of the mixed far kernel, single tiles of the FP64 kernel
     const int unit = prec == OBEM_MIXED ? kTI * kCS : kTI;
     nsplit = std::max(1, std::min((kSplitWorkgroups + bw - 1) / bw, (n_s + unit - 1) / unit));
     if ((int64_t)bw * nsplit > kFewWorkgroups) nsplit = std::max(1, std::min(nsplit, (n_s + 1023) / 1024));
-    nsplit = std::min(nsplit, max_slots(bw));
+    nsplit = std::min(nsplit, 64);
     chunk = (n_s + nsplit - 1) / nsplit;
     chunk = (chunk + unit - 1) / unit * unit;
     nsplit = (n_s + chunk - 1) / chunk;
   }
-  // mixed: partial slots of the near kernel after those of the far kernel
+  // mixed: partial slots of the near kernel after those of the far kernel;
+  // one wave per cell and split, at least four tiles a split
   const int ntile = (n_s + kTI - 1) / kTI;
-  const int bn = (N + kNW - 1) / kNW;
-  const int nnear = std::max(1, std::min(ntile, std::min(16, (2048 + bn - 1) / bn)));
+  const int nnear = std::max(1, std::min((ntile + 3) / 4, std::min(64, (8192 + N - 1) / N)));
   const int tchunk = std::max(1, (ntile + nnear - 1) / nnear);
   const int nslot = (n_s > 0 && prec == OBEM_MIXED) ? nsplit + (ntile + tchunk - 1) / tchunk : nsplit;
   double *part = (double *)ws_get(ctx, WS_MISC3, sizeof(double) * 4 * (size_t)N * nslot);
@@ -420,17 +606,23 @@ obem_status influence_rhs(obem_ctx *ctx, const obem_meshh *m, int64_t n_src, con
   if (n_s == 0) {
     obem_status st = launch_fill(ctx, part, 4 * (size_t)N, 0.0);
     if (st) return st;
-  } else if (prec == OBEM_MIXED) {
+  } else {
     SourceOrder so;
     obem_status st = order_sources(ctx, n_s, sx, sy, sz, sq, false, &so);
     if (st) return st;
-    hipLaunchKernelGGL(k_influence_mixed, dim3(bw, nsplit), dim3(kTI), 0, ctx->stream, N, m->f, m->order, n_s, so.x,
-                       so.y, so.z, so.q, chunk, part);
-    hipLaunchKernelGGL(k_influence_near, dim3(bn, nslot - nsplit), dim3(kNW), 0, ctx->stream, N, m->f, m->rec, m->order, n_s,
-                       so.x, so.y, so.z, so.q, so.tbox, tchunk, part + 4 * (size_t)N * nsplit);
-  } else {
-    hipLaunchKernelGGL(k_influence_fp64, dim3(bc, nsplit), dim3(kTI), 0, ctx->stream, N, m->f, m->rec, m->order, n_s, sx, sy,
-                       sz, sq, chunk, part);
+    if (prec == OBEM_MIXED) {
+      const int ng = (n_s + 63) / 64;
+      double *sph = (double *)ws_get(ctx, WS_MISC2, sizeof(double) * 4 * (size_t)ng);
+      if (!sph) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
+      hipLaunchKernelGGL(k_charge_spheres, dim3(ng), dim3(64), 0, ctx->stream, n_s, so.x, so.y, so.z, sph);
+      hipLaunchKernelGGL(k_influence_mixed, dim3(bw, nsplit), dim3(kTI), 0, ctx->stream, N, m->f, m->order, n_s, so.x,
+                         so.y, so.z, so.q, sph, chunk, part);
+      hipLaunchKernelGGL(k_influence_near, dim3(N, nslot - nsplit), dim3(64), 0, ctx->stream, N, m->f, m->rec, m->order,
+                         n_s, so.x, so.y, so.z, so.q, so.tbox, tchunk, part + 4 * (size_t)N * nsplit);
+    } else {
+      hipLaunchKernelGGL(k_influence_fp64, dim3(bw, nsplit), dim3(kTI), 0, ctx->stream, N, m->f, m->rec, m->order, n_s,
+                         so.x, so.y, so.z, so.q, chunk, part);
+    }
   }
   OBEM_HIP(ctx, hipGetLastError());
   hipLaunchKernelGGL(k_influence_rhs, dim3(bc), dim3(256), 0, ctx->stream, N, n_s > 0 ? nslot : 1, part, m->order,

@@ -199,3 +199,23 @@ def test_splits_of_few_targets(ctx, orc, n_t, n_s):
     ref = orc.influence(m, m.rhs, xs[:n_t], q[:n_t])
     ref = ref[0] if isinstance(ref, tuple) else ref
     assert np.abs(out - ref).max() <= 1e-11 * np.abs(ref - m.rhs).max() + 1e-15 * np.abs(m.rhs).max()
+
+
+@pytest.mark.parametrize("n_s", [1, 63, 64, 65, 1023, 1025, 2100])
+@pytest.mark.parametrize("n_c", [1, 7, 9, 130])
+def test_influence_remainders(ctx, orc, n_s, n_c):
+    """Cells not a multiple of the 8 (2) of a workgroup (wave), charges around
+    the runs of 64 and the blocks of 1,024, near, at zone bounds of and far
+    from the cells, in both precisions (tolerances of the influence tests)."""
+    m = _first_cells(W.parallel_plate_mesh(n=12), n_c)
+    rng = np.random.default_rng(n_s + n_c)
+    x, q = W.parallel_plate_electrons(n_s, seed=n_s)
+    x[: n_s // 2] *= 0.2                     # a dense half near one corner of the cells
+    x[: n_s // 2, 2] += 1e-4
+    x[:, :2] += rng.choice([0.0, -5e-3, 4e-2], size=(n_s, 1))
+    ref = orc.influence(m, m.rhs, x, q)[0]
+    scale = np.abs(ref - m.rhs).max()
+    bm = bind(ctx, m)
+    for prec, tol in ((B.OBEM_FP64, 1e-11), (B.OBEM_MIXED, 1e-5)):
+        out = host(B.bem_influence(ctx, bm, dev(m.rhs), dev(x), dev(q), prec))
+        assert np.abs(out - ref).max() <= tol * scale + 4e-16 * np.abs(m.rhs).max()
