@@ -50,6 +50,18 @@ __device__ __forceinline__ double sqrt_f64(double x) {
   g = fma(fma(-g, g, x), h, g);
   return x == 0.0 ? 0.0 : g;
 }
+// The square root and its reciprocal (x > 0).
+__device__ __forceinline__ double sqrt_rcp_f64(double x, double &inv) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  const double r = fma(-h, g, 0.5);
+  g = fma(g, r, g);
+  h = fma(h, r, h);
+  g = fma(fma(-g, g, x), h, g);
+  const double i = h + h;
+  inv = fma(fma(-g, i, 1.0), i, i);
+  return g;
+}
 // y (1 + e/2 + 3 e^2/8), e = 1 - x y^2: third order, one step from the
 // estimate (two Newton steps took two operations more).
 __device__ __forceinline__ double rsqrt_f64(double x) {

@@ -24,27 +24,17 @@ constexpr int kThreads = 256;
 // ---------------------------------------------------------------------------
 // Target ordering
 // ---------------------------------------------------------------------------
-// v of another lane of the wave by a DPP pattern (VALU; a shuffle of a double
-// is two LDS-crossbar instructions); lanes without a source keep v.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp((int)(unsigned)u, (int)(unsigned)u, CTRL, ROWS, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp((int)(unsigned)(u >> 32), (int)(unsigned)(u >> 32), CTRL, ROWS, 0xf, false);
-  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
 // Minimum (or maximum) over the wave's 64 lanes, valid in lane 63: within
 // quads, eights and rows of 16, then rows 0 to 1 and 2 to 3, then 1 to 3.
 template <bool MAX>
 __device__ __forceinline__ double wave_extreme(double v) {
   auto op = [](double a, double b) { return MAX ? fmax(a, b) : fmin(a, b); };
-  v = op(v, dpp_f64<0xB1, 0xf>(v));   // quad_perm 1 0 3 2
-  v = op(v, dpp_f64<0x4E, 0xf>(v));   // quad_perm 2 3 0 1
-  v = op(v, dpp_f64<0x141, 0xf>(v));  // row_half_mirror
-  v = op(v, dpp_f64<0x140, 0xf>(v));  // row_mirror
-  v = op(v, dpp_f64<0x142, 0xa>(v));  // row_bcast:15 into rows 1 and 3
-  return op(v, dpp_f64<0x143, 0xc>(v));  // row_bcast:31 into rows 2 and 3
+  v = op(v, dpp_f64<0xB1, 0xf>(v, v));   // quad_perm 1 0 3 2
+  v = op(v, dpp_f64<0x4E, 0xf>(v, v));   // quad_perm 2 3 0 1
+  v = op(v, dpp_f64<0x141, 0xf>(v, v));  // row_half_mirror
+  v = op(v, dpp_f64<0x140, 0xf>(v, v));  // row_mirror
+  v = op(v, dpp_f64<0x142, 0xa>(v, v));  // row_bcast:15 into rows 1 and 3
+  return op(v, dpp_f64<0x143, 0xc>(v, v));  // row_bcast:31 into rows 2 and 3
 }
 
 // Combines the waves' boxes b (lo xyz, hi xyz) of a workgroup of T threads;
@@ -723,14 +713,6 @@ constexpr int kPF = 32;  // cells per LDS tile of the FP64 far kernel
 struct CellF64 {
   double g[3], lim, q[21], w[7];
 };
-
-// The value of lane k (wave-uniform k) of a double.
-__device__ __forceinline__ double readlane_f64(double v, int k) {
-  const unsigned long long u = __double_as_longlong(v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, k);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), k);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
 
 template <bool WANT_V>
 __global__ __launch_bounds__(kThreads) void k_panel_fp64(int n_t, const double *__restrict__ xs, int N,

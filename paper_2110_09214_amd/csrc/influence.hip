@@ -67,14 +67,6 @@ struct ICell {
   float4 c[19];
 };
 
-// Orders the LDS accesses of a wave's lanes (its instructions run in order;
-// this keeps the compiler from moving them).
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // sum over m of w_m {1/|e_m|, e_m/|e_m|^3}, e_m = p - point m
 template <int M>
 __device__ __forceinline__ void infl_points(float px, float py, float pz, const float *q, const float *w, float &sv,

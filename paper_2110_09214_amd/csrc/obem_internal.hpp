@@ -213,6 +213,33 @@ struct TargetOrder {
 obem_status order_targets(obem_ctx *ctx, int64_t n, const double *tx, const double *ty,
                           const double *tz, TargetOrder *out);
 
+// v of another lane of the wave by a DPP pattern (VALU; a shuffle of a double
+// is two LDS-crossbar instructions); lanes without a source get `none`.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_f64(double v, double none) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  const unsigned long long z = (unsigned long long)__double_as_longlong(none);
+  const int lo = __builtin_amdgcn_update_dpp((int)(unsigned)z, (int)(unsigned)u, CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp((int)(unsigned)(z >> 32), (int)(unsigned)(u >> 32), CTRL, ROWS, 0xf, false);
+  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
+// The value of lane k (wave-uniform k) of a double.
+__device__ __forceinline__ double readlane_f64(double v, int k) {
+  const unsigned long long u = __double_as_longlong(v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, k);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), k);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Orders the LDS accesses of a wave's lanes (its instructions run in order;
+// this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Partial sums in n slots, each [components][points] FP64.
 struct Slots {
   const double *p = nullptr;

@@ -219,3 +219,26 @@ def test_influence_remainders(ctx, orc, n_s, n_c):
     for prec, tol in ((B.OBEM_FP64, 1e-11), (B.OBEM_MIXED, 1e-5)):
         out = host(B.bem_influence(ctx, bm, dev(m.rhs), dev(x), dev(q), prec))
         assert np.abs(out - ref).max() <= tol * scale + 4e-16 * np.abs(m.rhs).max()
+
+
+@pytest.mark.parametrize("n", [1, 65, 257])
+@pytest.mark.parametrize("spread", [2e-6, 60e-6])
+def test_close_pairs_of_the_adjoint(ctx, orc, n, spread):
+    """The cell adjoint at targets in a hole of the coarse GEM cell (cells near
+    a few or most targets of a wave, batches that fill and end part full,
+    cells seen by several waves), both gradients against the oracle at the
+    adjoint tests' tolerances."""
+    geo = W.GemGeometry(m=3, n_r=2, n_cone=2, plain_h=48e-6)
+    m = W.gem_cell_mesh(geo)
+    rng = np.random.default_rng(100 + n)
+    cx, cy = geo.hole_centres()[4]
+    x = np.array([cx + 0.8 * geo.r_inner, cy, 3e-6]) + rng.uniform(-1, 1, size=(n, 3)) * np.array([0.2, 0.2, 1.0]) * spread
+    w = rng.normal(size=(n, 3))
+    mesh = W.Mesh(m.a, m.b, m.c, m.kind, m.eps1, m.eps2, m.rhs)
+    sig = 1e-6 * (1.0 + rng.uniform(size=m.n))
+    gs_r, gx_r = orc.panel_backward(x, mesh, sig, w)
+    bm = bind(ctx, m)
+    for prec, tol in ((B.OBEM_FP64, 1e-10), (B.OBEM_MIXED, 1e-5)):
+        gs, gx, _ = B.field_eval_backward(ctx, bm, dev(sig), None, None, dev(x), 0.0, dev(w), prec)
+        assert rel_l2(host(gs), gs_r) <= tol
+        assert rel_l2(host(gx), gx_r) <= tol
