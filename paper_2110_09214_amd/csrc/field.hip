@@ -706,20 +706,33 @@ __global__ __launch_bounds__(kThreads) void k_panel_mixed(int n_t, const double 
 // FP64 mode: closed form up to 48 diameters (k_panel_close), FP64
 // 7-point rule beyond (k_panel_fp64).  Both decide with the same FP64 test
 // |x - c_k|^2 >= (48 D_k)^2 on the unmodified coordinates.
-constexpr int kPF = 32;  // cells per LDS tile of the FP64 far kernel
+//
+// With d = x - c, kappa = 1 / |d|^2 and the vertices at c + e_j, a rule point
+// c + t e_j (t = 1 - 3 a or 1 - 3 b) is at the squared distance
+// |d|^2 (1 + delta), delta = kappa (t^2 |e_j|^2 - 2 t d.e_j), and beyond 48
+// diameters |delta| <= 0.0195.  So the six outer points need no root of their
+// own, only far_series(delta), and as e_1 + e_2 + e_3 = 0 the sums over points
+// leave the plane once per cell: 103 FP64 operations and one root a pair
+// instead of 147 and seven.  Bound by FP64 issue: 50,000 targets and 40,776
+// cells of the GEM cell 8.9 -> 7.1 ms, 546 cycles a wave and pair of which the
+// operations need 430; two targets a thread (half the LDS reads) take 1 %
+// longer.
+constexpr int kPF = 64;  // cells per LDS tile of the FP64 far kernel
 
-// One cell of the FP64 far kernel's LDS tile: centroid, (48 D)^2, the 7 rule
-// points, area sigma {w0, wa, wa, wa, wb, wb, wb} folded per point.
-struct CellF64 {
-  double g[3], lim, q[21], w[7];
+// One cell of the FP64 far kernel's LDS tile: centroid, (48 D)^2, e_1, e_2,
+// t^2 |e_j|^2 of the six outer points, area sigma.
+struct alignas(16) CellF64 {
+  double g[3], lim, e[6], qa[3], qb[3], as;
 };
 
 template <bool WANT_V>
 __global__ __launch_bounds__(kThreads) void k_panel_fp64(int n_t, const double *__restrict__ xs, int N,
                                                          const double *__restrict__ f,
+                                                         const double *__restrict__ rec,
                                                          const double *__restrict__ sigma, int cchunk,
                                                          double *part) {
   __shared__ CellF64 T[kPF];
+  constexpr double kTa = 1.0 - 3.0 * Rule7::a, kTb = 1.0 - 3.0 * Rule7::b;
   const int tid = threadIdx.x;
   const int i = blockIdx.x * kThreads + tid;
   const bool active = i < n_t;
@@ -730,37 +743,61 @@ __global__ __launch_bounds__(kThreads) void k_panel_fp64(int n_t, const double *
   for (int k0 = kb; k0 < ke; k0 += kPF) {
     const int cnt = min(kPF, ke - k0);
     __syncthreads();
-    for (int idx = tid; idx < 21 * kPF; idx += kThreads) {
-      const int m = idx / kPF, k = idx % kPF;
-      if (k < cnt) T[k].q[m] = f[(size_t)(MF_Q7 + m) * N + k0 + k];
-    }
     if (tid < cnt) {
       const int kk = k0 + tid;
       const double D = f[(size_t)MF_DIAM * N + kk];
-      const double as = f[(size_t)MF_AREA * N + kk] * sigma[kk];
-      T[tid].g[0] = f[(size_t)MF_GX * N + kk];
-      T[tid].g[1] = f[(size_t)MF_GY * N + kk];
-      T[tid].g[2] = f[(size_t)MF_GZ * N + kk];
-      T[tid].lim = kQuadFp64 * kQuadFp64 * D * D;
+      const double *v = rec + (size_t)CR_COUNT * kk + CR_V;
+      const d3 g = mk3(f[(size_t)MF_GX * N + kk], f[(size_t)MF_GY * N + kk], f[(size_t)MF_GZ * N + kk]);
+      CellF64 &c = T[tid];
+      c.g[0] = g.x;
+      c.g[1] = g.y;
+      c.g[2] = g.z;
+      c.lim = kQuadFp64 * kQuadFp64 * D * D;
+      c.as = f[(size_t)MF_AREA * N + kk] * sigma[kk];
 #pragma unroll
-      for (int m = 0; m < 7; ++m) T[tid].w[m] = as * (m == 0 ? Rule7::w0 : (m < 4 ? Rule7::wa : Rule7::wb));
+      for (int j = 0; j < 3; ++j) {
+        const d3 e = mk3(v[3 * j], v[3 * j + 1], v[3 * j + 2]) - g;
+        if (j < 2) {
+          c.e[3 * j] = e.x;
+          c.e[3 * j + 1] = e.y;
+          c.e[3 * j + 2] = e.z;
+        }
+        const double e2 = dot3(e, e);
+        c.qa[j] = kTa * kTa * e2;
+        c.qb[j] = kTb * kTb * e2;
+      }
     }
     __syncthreads();
     for (int k = 0; k < cnt; ++k) {
-      const double dx = x0 - T[k].g[0], dy = x1 - T[k].g[1], dz = x2 - T[k].g[2];
+      const CellF64 &c = T[k];
+      const double dx = x0 - c.g[0], dy = x1 - c.g[1], dz = x2 - c.g[2];
       const double R2 = fma(dx, dx, fma(dy, dy, dz * dz));
-      if (R2 >= T[k].lim) {  // the near kernel takes the others
+      if (R2 >= c.lim) {  // the near kernel takes the others
+        const double ri = rsqrt_f64(R2), kappa = ri * ri;
+        double p[3];
+        p[0] = fma(dx, c.e[0], fma(dy, c.e[1], dz * c.e[2]));
+        p[1] = fma(dx, c.e[3], fma(dy, c.e[4], dz * c.e[5]));
+        p[2] = -(p[0] + p[1]);
+        double s[3], ta = 0.0, tb = 0.0, va = 0.0, vb = 0.0;
 #pragma unroll
-        for (int m = 0; m < 7; ++m) {
-          const double qx = x0 - T[k].q[3 * m], qy = x1 - T[k].q[3 * m + 1], qz = x2 - T[k].q[3 * m + 2];
-          const double ri = rsqrt_f64(fma(qx, qx, fma(qy, qy, qz * qz)));
-          const double wr = T[k].w[m] * ri;
-          const double t = wr * ri * ri;
-          ex = fma(t, qx, ex);
-          ey = fma(t, qy, ey);
-          ez = fma(t, qz, ez);
-          if (WANT_V) ev += wr;
+        for (int j = 0; j < 3; ++j) {
+          const double da = kappa * fma_k(p[j], -2.0 * kTa, c.qa[j]), db = kappa * fma_k(p[j], -2.0 * kTb, c.qb[j]);
+          const double ga = far_series(da), gb = far_series(db);
+          ta += ga;
+          tb += gb;
+          if (WANT_V) {
+            va += fma(da, ga, ga);
+            vb += fma(db, gb, gb);
+          }
+          s[j] = fma(ga, kTa * Rule7::wa, gb * (kTb * Rule7::wb));
         }
+        const double wr = c.as * ri, w = wr * kappa;
+        const double t = w * fma(ta, Rule7::wa, fma(tb, Rule7::wb, Rule7::w0));
+        const double s0 = w * (s[2] - s[0]), s1 = w * (s[2] - s[1]);
+        ex = fma(t, dx, fma(s0, c.e[0], fma(s1, c.e[3], ex)));
+        ey = fma(t, dy, fma(s0, c.e[1], fma(s1, c.e[4], ey)));
+        ez = fma(t, dz, fma(s0, c.e[2], fma(s1, c.e[5], ez)));
+        if (WANT_V) ev = fma(wr, fma(va, Rule7::wa, fma(vb, Rule7::wb, Rule7::w0)), ev);
       }
     }
   }
@@ -1045,11 +1082,11 @@ obem_status launch_panel_field(obem_ctx *ctx, const obem_meshh *m, const double 
   dim3 gsplit(bt, ns), block(kThreads);
   OBEM_PROF(ctx, "panel");
 #define PANEL_FAR(K, V, ...) \
-  hipLaunchKernelGGL(K<V>, gsplit, block, 0, ctx->stream, n_t, to.xs, N, m->f, sigma, cchunk, part __VA_ARGS__)
+  hipLaunchKernelGGL(K<V>, gsplit, block, 0, ctx->stream, n_t, to.xs, N, m->f, __VA_ARGS__ sigma, cchunk, part)
   if (prec == OBEM_MIXED) {
-    if (want_v) PANEL_FAR(k_panel_mixed, true); else PANEL_FAR(k_panel_mixed, false);
+    if (want_v) PANEL_FAR(k_panel_mixed, true, ); else PANEL_FAR(k_panel_mixed, false, );
   } else {
-    if (want_v) PANEL_FAR(k_panel_fp64, true); else PANEL_FAR(k_panel_fp64, false);
+    if (want_v) PANEL_FAR(k_panel_fp64, true, m->rec, ); else PANEL_FAR(k_panel_fp64, false, m->rec, );
   }
   // the near kernel of split y adds the closed-form pairs of the same cell
   // range into the same slot (one writer per entry, after the far kernel),

@@ -242,3 +242,32 @@ def test_close_pairs_of_the_adjoint(ctx, orc, n, spread):
         gs, gx, _ = B.field_eval_backward(ctx, bm, dev(sig), None, None, dev(x), 0.0, dev(w), prec)
         assert rel_l2(host(gs), gs_r) <= tol
         assert rel_l2(host(gx), gx_r) <= tol
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 129])
+@pytest.mark.parametrize("ratio", [49.0, 300.0])
+def test_far_cells_in_fp64(ctx, orc, n, ratio):
+    """Cells beyond 48 diameters only, thin ones seen along their length (the
+    far kernel's series at the end of its range) and ordinary ones, cell counts
+    around its tile of 64.  The rule it sums is exact to degree 5: off by at
+    most (0.67 / 48)^6 = 7e-12 of a cell's field, and the closed form of the
+    reference loses no more at 300 diameters."""
+    rng = np.random.default_rng(n)
+    a = rng.uniform(-1e-7, 1e-7, size=(n, 3))
+    t = rng.normal(size=(n, 3))
+    t[0] = [1.0, 0.0, 0.0]
+    t /= np.linalg.norm(t, axis=1, keepdims=True)
+    s = np.cross(t, rng.normal(size=(n, 3)))
+    s /= np.linalg.norm(s, axis=1, keepdims=True)
+    b = a + 1e-6 * t
+    c = a + 1e-6 * (rng.uniform(0.0, 0.9, size=(n, 1)) * t + rng.uniform(0.01, 0.4, size=(n, 1)) * s)
+    z = np.zeros(n)
+    m = W.Mesh(a, b, c, z.astype(np.int32), z + 1.0, z + 1.0, z, name="far")
+    sig = rng.uniform(1e-7, 2e-7, size=n)
+    d = rng.normal(size=(70, 3))
+    d[:2] = [[1.0, 0.0, 0.0], [-1.0, 0.0, 0.0]]
+    x = ratio * 1.04e-6 * d / np.linalg.norm(d, axis=1, keepdims=True)
+    E, V = B.field_eval(ctx, bind(ctx, m), dev(sig), None, None, dev(x), 0.0, B.OBEM_FP64, want_v=True)
+    Er, Vr = orc.panel_field(x, a, b, c, sig, want_v=True)
+    assert rel_l2(host(E), Er) <= 1e-11
+    assert rel_l2(host(V), Vr) <= 1e-11
