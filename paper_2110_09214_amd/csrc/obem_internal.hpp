@@ -90,6 +90,13 @@ enum MeshField {
   MF_COUNT = MF_Q4 + 9
 };
 
+// A cell in the absorption grid's lists: its index and its bounding box,
+// rounded outwards to FP32 and widened by 1e-6 of its diameter.
+struct alignas(16) GridItem {
+  float lo[3], hi[3];
+  int32_t k, pad;
+};
+
 struct obem_meshh {
   int64_t n = 0;
   int64_t n_dd = 0;
@@ -118,7 +125,7 @@ struct obem_meshh {
   int32_t grid_n[3] = {0, 0, 0};
   double grid_lo[3], grid_h[3];
   int32_t *grid_start = nullptr;   // n_cells + 1
-  int32_t *grid_items = nullptr;
+  GridItem *grid_items = nullptr;  // per grid cell, the cells whose boxes overlap it
   const double *field(int k) const { return f + (size_t)k * (size_t)n; }
 };
 

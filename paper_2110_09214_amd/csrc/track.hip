@@ -57,24 +57,32 @@ struct StepDev {
 
 struct GridDev {
   int nx, ny, nz;
-  double lo[3], h[3];
-  const int32_t *start, *items;
+  double lo[3], inv_h[3];
+  const int32_t *start;
+  const GridItem *items;
   int N;
-  const double *f;
+  const double *rec;
   const int8_t *kind;
 };
 
-// Cross section k at eps (eV): linear in the normalised lethargy of eq.
-// (leth) between log-spaced nodes, clamped to the end nodes.
-__device__ __forceinline__ double xs_at(const GasDev &g, int k, double eps) {
+// Place of eps (eV) in the tables of log-spaced nodes, by the normalised
+// lethargy of eq. (leth): node i and the fraction towards node i + 1, clamped
+// to the end nodes.  span = log(e_max / e_min).
+struct TabPos {
+  int i;
+  double fr;
+};
+__device__ __forceinline__ TabPos tab_pos(const GasDev &g, double span, double eps) {
   const int n = g.n;
-  if (!(eps > g.e_min)) return g.xs[k * n];
-  if (eps >= g.e_max) return g.xs[k * n + n - 1];
-  const double p = (double)(n - 1) * (log(eps / g.e_min) / log(g.e_max / g.e_min));
+  if (!(eps > g.e_min)) return {0, 0.0};
+  if (eps >= g.e_max) return {n - 2, 1.0};
+  const double p = (double)(n - 1) * (log(eps / g.e_min) / span);
   int i = (int)floor(p);
   if (i >= n - 1) i = n - 2;
-  const double fr = p - (double)i;
-  return g.xs[k * n + i] * (1.0 - fr) + g.xs[k * n + i + 1] * fr;
+  return {i, p - (double)i};
+}
+__device__ __forceinline__ double tab_at(const double *tab, TabPos t) {
+  return tab[t.i] * (1.0 - t.fr) + tab[t.i + 1] * t.fr;
 }
 
 // N max_b max(sigma_tot,b, sigma_tot,b+1) v(E_b+1): exact bound on each bin.
@@ -103,13 +111,20 @@ __global__ __launch_bounds__(256) void k_nu_max(GasDev g, double *out) {
 // First crossing of the chord p0 -> p1 with a cell (Moller-Trumbore, 1997),
 // smallest parameter t in (0, 1], ties to the lower cell index; the uniform
 // grid restricts the candidates to cells whose bounding boxes overlap the
-// chord's.
+// chord's.  Most cells of a grid cell's list miss the chord's own box, so the
+// list carries their boxes: 32 contiguous bytes a cell, kGridBatch cells in
+// flight, where a test reads 72 bytes after the index has arrived and does
+// some 60 dependent FP64 operations: 20,000 particles in the holes of the
+// coarse GEM cell, about 10 cells a list and 25 for the longest of a wave,
+// 572 -> 306 us a push, the collisions' own arithmetic now.  (The margin of
+// the boxes is far above the rounding of the test, so no crossing is lost.)
+constexpr int kGridBatch = 4;
 __device__ __forceinline__ void mt_test(const GridDev &G, int k, d3 o, d3 dir, double &bt, int &best) {
-  const int N = G.N;
-  const double *f = G.f;
-  const d3 a = mk3(f[(size_t)MF_AX * N + k], f[(size_t)MF_AY * N + k], f[(size_t)MF_AZ * N + k]);
-  const d3 e1 = mk3(f[(size_t)MF_BX * N + k], f[(size_t)MF_BY * N + k], f[(size_t)MF_BZ * N + k]) - a;
-  const d3 e2 = mk3(f[(size_t)MF_CX * N + k], f[(size_t)MF_CY * N + k], f[(size_t)MF_CZ * N + k]) - a;
+  double v9[10];
+  load_doubles<10>(G.rec + (size_t)CR_COUNT * k + CR_V, v9);
+  const d3 a = mk3(v9[0], v9[1], v9[2]);
+  const d3 e1 = mk3(v9[3], v9[4], v9[5]) - a;
+  const d3 e2 = mk3(v9[6], v9[7], v9[8]) - a;
   const d3 pv = cross3(dir, e2);
   const double det = dot3(e1, pv);
   if (det == 0.0) return;
@@ -137,7 +152,8 @@ __device__ int first_hit(const GridDev &G, const double *p0, const double *p1) {
   const int nn[3] = {G.nx, G.ny, G.nz};
   for (int c = 0; c < 3; ++c) {
     const double a = fmin(p0[c], p1[c]), b = fmax(p0[c], p1[c]);
-    const double ta = floor((a - G.lo[c]) / G.h[c]), tb = floor((b - G.lo[c]) / G.h[c]);
+    // widened by 1e-8 of a grid cell, above the rounding of the product
+    const double ta = floor(fma(a - G.lo[c], G.inv_h[c], -1e-8)), tb = floor(fma(b - G.lo[c], G.inv_h[c], 1e-8));
     if (tb < 0.0 || ta >= (double)nn[c]) return -1;  // chord outside every cell's box
     lo[c] = (int)fmax(ta, 0.0);
     hi[c] = (int)fmin(tb, (double)(nn[c] - 1));
@@ -147,33 +163,60 @@ __device__ int first_hit(const GridDev &G, const double *p0, const double *p1) {
     for (int k = 0; k < G.N; ++k) mt_test(G, k, o, dir, bt, best);
     return best;
   }
+  // the chord's box, rounded outwards to FP32
+  float ca[3], cb[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    ca[c] = (float)fmin(p0[c], p1[c]);
+    cb[c] = (float)fmax(p0[c], p1[c]);
+    ca[c] -= fabsf(ca[c]) * 0x1p-22f;
+    cb[c] += fabsf(cb[c]) * 0x1p-22f;
+  }
   for (int iz = lo[2]; iz <= hi[2]; ++iz)
     for (int iy = lo[1]; iy <= hi[1]; ++iy)
       for (int ix = lo[0]; ix <= hi[0]; ++ix) {
         const int cell = (iz * G.ny + iy) * G.nx + ix;
-        for (int q = G.start[cell]; q < G.start[cell + 1]; ++q) mt_test(G, G.items[q], o, dir, bt, best);
+        const int qe = G.start[cell + 1];
+        for (int q = G.start[cell]; q < qe; q += kGridBatch) {
+          float4 w[2 * kGridBatch];
+#pragma unroll
+          for (int j = 0; j < kGridBatch; ++j) {
+            const float4 *it = reinterpret_cast<const float4 *>(G.items + min(q + j, qe - 1));
+            w[2 * j] = it[0];
+            w[2 * j + 1] = it[1];
+          }
+          int k[kGridBatch];
+#pragma unroll
+          for (int j = 0; j < kGridBatch; ++j) {
+            const float4 l = w[2 * j], h = w[2 * j + 1];  // lo.xyz hi.x, hi.yz k
+            const bool meet = q + j < qe && cb[0] >= l.x && cb[1] >= l.y && cb[2] >= l.z && ca[0] <= l.w &&
+                              ca[1] <= h.x && ca[2] <= h.y;
+            k[j] = meet ? __float_as_int(h.z) : -1;
+          }
+#pragma unroll 1
+          for (;;) {  // the cells met, one at a time
+            int kk = -1;
+#pragma unroll
+            for (int j = 0; j < kGridBatch; ++j)
+              if (kk < 0 && k[j] >= 0) {
+                kk = k[j];
+                k[j] = -1;
+              }
+            if (kk < 0) break;
+            mt_test(G, kk, o, dir, bt, best);
+          }
+        }
       }
   return best;
 }
 
 __device__ __forceinline__ void iso_dir(double u2, double u3, double *d) {
   const double ct = 1.0 - 2.0 * u2, st = sqrt(fmax(0.0, 1.0 - ct * ct)), ph = 2.0 * kPi * u3;
-  d[0] = st * cos(ph);
-  d[1] = st * sin(ph);
+  double sp, cp;
+  sincos(ph, &sp, &cp);
+  d[0] = st * cp;
+  d[1] = st * sp;
   d[2] = ct;
-}
-
-// Table value at eps (eV), linear in the normalised lethargy of eq. (leth)
-// between log-spaced nodes, clamped to the end nodes (as xs_at).
-__device__ __forceinline__ double table_at(const GasDev &g, const double *tab, double eps) {
-  const int n = g.n;
-  if (!(eps > g.e_min)) return tab[0];
-  if (eps >= g.e_max) return tab[n - 1];
-  const double p = (double)(n - 1) * (log(eps / g.e_min) / log(g.e_max / g.e_min));
-  int i = (int)floor(p);
-  if (i >= n - 1) i = n - 2;
-  const double fr = p - (double)i;
-  return tab[i] * (1.0 - fr) + tab[i + 1] * fr;
 }
 
 // Unit vector at polar angle theta (cosine ct) and azimuth 2 pi u about the
@@ -191,7 +234,8 @@ __device__ __forceinline__ void rotate_about(const double *d, double ct, double 
   for (int k = 0; k < 3; ++k) e1[k] /= l;
   const double e2[3] = {d[1] * e1[2] - d[2] * e1[1], d[2] * e1[0] - d[0] * e1[2], d[0] * e1[1] - d[1] * e1[0]};
   const double st = sqrt(fmax(0.0, 1.0 - ct * ct)), ph = 2.0 * kPi * u;
-  const double cp = cos(ph), sp = sin(ph);
+  double sp, cp;
+  sincos(ph, &sp, &cp);
 #pragma unroll
   for (int k = 0; k < 3; ++k) out[k] = ct * d[k] + st * (cp * e1[k] + sp * e2[k]);
 }
@@ -231,7 +275,7 @@ __device__ __forceinline__ bool add_pair(Kids &K, const double *xe, const double
 // the collision's own uniforms; extra draws use counter word 3 = 2k + 1
 // (ionisation, Penning) and 0x80000000 | k (Penning cation).  Returns true
 // when the electron became an anion.
-__device__ bool electron_interaction(const GasDev &g, int proc, double eps, double *X, double *Vv, double u2,
+__device__ bool electron_interaction(const GasDev &g, int proc, double eps, TabPos at, double *X, double *Vv, double u2,
                                      double u3, uint64_t pid, uint32_t step, uint2 key, uint32_t k, Kids &K,
                                      int *cnt) {
   const double e_therm = 1.5 * kKb * g.temperature;
@@ -241,7 +285,7 @@ __device__ bool electron_interaction(const GasDev &g, int proc, double eps, doub
   if (proc == 0) {  // elastic, recoil loss 2 m_e/M (1 - cos theta)
     double ct;
     if (g.xi && vm > 0.0) {  // eq. (anisotrop) about the incident direction
-      const double xi = table_at(g, g.xi, eps);
+      const double xi = tab_at(g.xi, at);
       ct = 1.0 - 2.0 * u2 * (1.0 - xi) / (1.0 + xi * (1.0 - 2.0 * u2));
       const double d0[3] = {Vv[0] / vm, Vv[1] / vm, Vv[2] / vm};
       rotate_about(d0, ct, u3, dir);
@@ -395,10 +439,16 @@ __global__ __launch_bounds__(256) void k_push_mc(int n, double *X0, double *X1, 
     const uint2 key = make_uint2(p.key0, p.key1);
     Kids K = {child, p.max_ion, i, 0};
     int st = 0, hcell = -1;
-    for (int k = 0;; ++k) {
+    const double span = log(g.e_max / g.e_min);
+    double acc[3];
+    auto accelerate = [&] {
       const double m = (sp == 0) ? kMe : (sp == 1 ? g.m_cation : g.m_anion);
       const double q = (sp == 1) ? kQe : -kQe;
-      const double acc[3] = {q * Ef[0] / m, q * Ef[1] / m, q * Ef[2] / m};
+#pragma unroll
+      for (int d = 0; d < 3; ++d) acc[d] = q * Ef[d] / m;
+    };
+    accelerate();
+    for (int k = 0;; ++k) {
       const double numax = (sp == 0) ? g.nu_e : g.nu_i;
       double tau;
       uint4 w = make_uint4(0, 0, 0, 0);
@@ -443,10 +493,11 @@ __global__ __launch_bounds__(256) void k_push_mc(int n, double *X0, double *X1, 
       const double u1 = u01(w.y), u2 = u01(w.z), u3 = u01(w.w);
       if (sp == 0) {
         const double eps = 0.5 * kMe * v2 / kQe;
+        const TabPos at = tab_pos(g, span, eps);
         double nuk[5], tot = 0.0;
 #pragma unroll
         for (int kk = 0; kk < 5; ++kk) {
-          nuk[kk] = g.density * xs_at(g, kk, eps) * vm;
+          nuk[kk] = g.density * tab_at(g.xs + kk * g.n, at) * vm;
           tot += nuk[kk];
         }
         double lim = numax;
@@ -467,9 +518,10 @@ __global__ __launch_bounds__(256) void k_push_mc(int n, double *X0, double *X1, 
           continue;
         }
         cnt[C_EL + proc] += 1;
-        if (electron_interaction(g, proc, eps, X, Vv, u2, u3, pid, p.step, key, (uint32_t)k, K, cnt)) {
+        if (electron_interaction(g, proc, eps, at, X, Vv, u2, u3, pid, p.step, key, (uint32_t)k, K, cnt)) {
           sp = 2;
           ballistic = true;
+          accelerate();
         }
       } else {
         const double nui = g.density * g.ion_iso * vm, nub = g.density * g.ion_back * vm;
@@ -604,10 +656,11 @@ __global__ __launch_bounds__(256) void k_collide_step(int n, double *X0, double 
     bool changed = false;
     if (sp == 0) {
       const double eps = 0.5 * kMe * v2 / kQe;
+      const TabPos at = tab_pos(g, log(g.e_max / g.e_min), eps);
       double nuk[5], tot = 0.0;
 #pragma unroll
       for (int kk = 0; kk < 5; ++kk) {
-        nuk[kk] = g.density * xs_at(g, kk, eps) * vm;
+        nuk[kk] = g.density * tab_at(g.xs + kk * g.n, at) * vm;
         tot += nuk[kk];
       }
       if (!(u0 < -expm1(-tot * p.dt))) {
@@ -623,7 +676,7 @@ __global__ __launch_bounds__(256) void k_collide_step(int n, double *X0, double 
         }
         if (proc < 0) proc = 4;
         cnt[C_EL + proc] += 1;
-        if (electron_interaction(g, proc, eps, X, Vv, u2, u3, pid, p.step, key, 0u, K, cnt)) species[i] = 2;
+        if (electron_interaction(g, proc, eps, at, X, Vv, u2, u3, pid, p.step, key, 0u, K, cnt)) species[i] = 2;
         changed = true;
       }
     } else {
@@ -877,7 +930,9 @@ static obem_status build_grid(obem_ctx *ctx, obem_meshh *m) {
   }
   const size_t ncell = (size_t)nn[0] * nn[1] * nn[2];
   std::vector<int32_t> count(ncell + 1, 0);
-  auto range = [&](int64_t k, int lo[3], int hi[3]) {
+  auto range = [&](int64_t k, int lo[3], int hi[3], GridItem &it) {
+    it.k = (int32_t)k;
+    it.pad = 0;
     for (int c = 0; c < 3; ++c) {
       double a = INFINITY, b = -INFINITY;
       for (int vtx = 0; vtx < 3; ++vtx) {
@@ -885,6 +940,8 @@ static obem_status build_grid(obem_ctx *ctx, obem_meshh *m) {
         a = std::min(a, x);
         b = std::max(b, x);
       }
+      it.lo[c] = std::nextafter((float)(a - 1e-6 * diam[k]), -INFINITY);
+      it.hi[c] = std::nextafter((float)(b + 1e-6 * diam[k]), INFINITY);
       lo[c] = std::max(0, std::min(nn[c] - 1, (int)std::floor((a - m->grid_lo[c]) / m->grid_h[c])));
       hi[c] = std::max(0, std::min(nn[c] - 1, (int)std::floor((b - m->grid_lo[c]) / m->grid_h[c])));
     }
@@ -895,10 +952,11 @@ static obem_status build_grid(obem_ctx *ctx, obem_meshh *m) {
       for (size_t c = 0; c < ncell; ++c) count[c + 1] += count[c];
       fillp.assign(count.begin(), count.end() - 1);
     }
-    std::vector<int32_t> items(pass == 1 ? count[ncell] : 0);
+    std::vector<GridItem> items(pass == 1 ? count[ncell] : 0);
     for (int64_t k = 0; k < N; ++k) {
       int lo[3], hi[3];
-      range(k, lo, hi);
+      GridItem it;
+      range(k, lo, hi, it);
       for (int z = lo[2]; z <= hi[2]; ++z)
         for (int y = lo[1]; y <= hi[1]; ++y)
           for (int x = lo[0]; x <= hi[0]; ++x) {
@@ -906,18 +964,18 @@ static obem_status build_grid(obem_ctx *ctx, obem_meshh *m) {
             if (pass == 0)
               count[cell + 1]++;
             else
-              items[fillp[cell]++] = (int32_t)k;
+              items[fillp[cell]++] = it;
           }
     }
     if (pass == 1) {
       if (hipMalloc(&m->grid_start, sizeof(int32_t) * (ncell + 1)) != hipSuccess ||
-          hipMalloc(&m->grid_items, sizeof(int32_t) * std::max<size_t>(1, items.size())) != hipSuccess) {
+          hipMalloc(&m->grid_items, sizeof(GridItem) * std::max<size_t>(1, items.size())) != hipSuccess) {
         (void)hipGetLastError();
         return fail(ctx, OBEM_ENOMEM, "absorption grid allocation failed");
       }
       OBEM_HIP(ctx, hipMemcpy(m->grid_start, count.data(), sizeof(int32_t) * (ncell + 1), hipMemcpyHostToDevice));
       if (!items.empty())
-        OBEM_HIP(ctx, hipMemcpy(m->grid_items, items.data(), sizeof(int32_t) * items.size(), hipMemcpyHostToDevice));
+        OBEM_HIP(ctx, hipMemcpy(m->grid_items, items.data(), sizeof(GridItem) * items.size(), hipMemcpyHostToDevice));
     }
   }
   return OBEM_OK;
@@ -1200,12 +1258,12 @@ extern "C" obem_status track_step(obem_ctx *ctx, obem_meshh *mesh, obem_particle
     G.nz = mesh->grid_n[2];
     for (int c = 0; c < 3; ++c) {
       G.lo[c] = mesh->grid_lo[c];
-      G.h[c] = mesh->grid_h[c];
+      G.inv_h[c] = 1.0 / mesh->grid_h[c];
     }
     G.start = mesh->grid_start;
     G.items = mesh->grid_items;
     G.N = (int)mesh->n;
-    G.f = mesh->f;
+    G.rec = mesh->rec;
     G.kind = mesh->kind;
   }
   if (p->stepper == OBEM_NULL_COLLISION) {

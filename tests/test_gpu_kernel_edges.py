@@ -271,3 +271,34 @@ def test_far_cells_in_fp64(ctx, orc, n, ratio):
     Er, Vr = orc.panel_field(x, a, b, c, sig, want_v=True)
     assert rel_l2(host(E), Er) <= 1e-11
     assert rel_l2(host(V), Vr) <= 1e-11
+
+
+@pytest.mark.parametrize("dt", [1e-13, 3e-12, 2e-11, 2e-10])
+def test_chords_through_the_grid(ctx, orc, dt):
+    """Free flights of electrons from 0.2 um to 400 um long through the coarse
+    GEM cell (chords within one grid cell, over several, and over more than
+    the 4096 beyond which every cell is tested): who is absorbed, and in which
+    cell the charge lands, as the oracle finds it."""
+    m = W.gem_cell_mesh(W.GemGeometry(m=3, n_r=2, n_cone=2, plain_h=48e-6))
+    geo = W.GemGeometry()
+    gas = W.constant_nu_gas(0.0)
+    rng = np.random.default_rng(11)
+    n = 700
+    top = geo.t_kapton / 2 + geo.t_cu
+    x = rng.uniform(-1, 1, size=(n, 3)) * np.array([0.9 * geo.half_x, 0.9 * geo.half_y, 1.2 * top])
+    v = rng.normal(size=(n, 3))
+    v *= 2e6 / np.linalg.norm(v, axis=1, keepdims=True)
+    sp, ids = np.zeros(n, np.int8), np.arange(n, dtype=np.int64)
+    p = dict(dt=dt, step=0, seed=5, max_coll=4, max_ion_per_step=1, ion_v_cap=2e4,
+             box_lo=(-geo.half_x, -geo.half_y, -3e-3), box_hi=(geo.half_x, geo.half_y, 3e-3), soft=1e-7, r_rec=0.0,
+             capacity=n, precision=B.OBEM_FP64, resolve=0, stepper=0)
+    state, _, counts, so, _ = orc.track_step(dict(x=x, v=v, species=sp, id=ids, next_id=n), m, np.zeros(m.n), gas, p,
+                                             np.zeros(m.n, np.int64), rhs0=m.rhs)
+    parts = B.Particles(n, "cuda", dev(x), dev(v), dev(sp, torch.int8), dev(ids, torch.int64), n)
+    counts_g = torch.zeros(m.n, dtype=torch.int64, device="cuda")
+    gas_s, keep = B.gas_struct(gas, "cuda")
+    sg = B.track_step(ctx, bind(ctx, m), parts, gas_s, p, counts_g, dev(np.zeros(m.n)), dev(m.rhs))
+    assert so["absorbed"] > 0 or dt < 1e-12
+    assert sg["absorbed"] == so["absorbed"]
+    assert np.array_equal(host(counts_g), counts)
+    assert np.array_equal(host(parts.state()["id"]), state["id"])
