@@ -344,6 +344,7 @@ obem_status obem_destroy(obem_ctx *ctx) {
     (void)hipStreamDestroy(ctx->aux);
   }
   if (ctx->work_dev) (void)hipFree(ctx->work_dev);
+  if (ctx->host_words) (void)hipHostFree(ctx->host_words);
   for (auto &b : ctx->ws)
     if (b.p) (void)hipFree(b.p);
   solver_release(ctx);

@@ -152,6 +152,8 @@ struct obem_ctx {
   // the directed terms of the other calls and of the pair-once calls' n^2
   unsigned long long *work_dev = nullptr;
   int64_t work_directed = 0, work_once_n2 = 0;
+  // a tracking step's counters and totals, written by the device (pinned, lazy)
+  unsigned long long *host_words = nullptr;
   // the device address of the library's static scratch array on this
   // context's device, and while an allocation-free call runs, the arena that
   // ws_get carves the workspace slots from instead of allocating

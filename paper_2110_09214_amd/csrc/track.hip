@@ -42,7 +42,8 @@ struct GasDev {
   const double *xs;
   double thr[5];
   double density, temperature, m_gas, m_cation, m_anion, ion_iso, ion_back;
-  double nu_e, nu_i;
+  const double *nu_e;  // the electrons' bound on the device (k_step_init)
+  double nu_i;
   const double *xi;  // anisotropy of the elastic angle (eq. (anisotrop)) or NULL
   double pen_prob, pen_level;
 };
@@ -86,7 +87,7 @@ __device__ __forceinline__ double tab_at(const double *tab, TabPos t) {
 }
 
 // N max_b max(sigma_tot,b, sigma_tot,b+1) v(E_b+1): exact bound on each bin.
-__global__ __launch_bounds__(256) void k_nu_max(GasDev g, double *out) {
+__device__ __forceinline__ void nu_max(const GasDev &g, double *out) {
   __shared__ double s[256];
   double best = 0.0;
   for (int b = threadIdx.x; b + 1 < g.n; b += 256) {
@@ -439,7 +440,7 @@ __global__ __launch_bounds__(256) void k_push_mc(int n, double *X0, double *X1, 
     const uint2 key = make_uint2(p.key0, p.key1);
     Kids K = {child, p.max_ion, i, 0};
     int st = 0, hcell = -1;
-    const double span = log(g.e_max / g.e_min);
+    const double span = log(g.e_max / g.e_min), nu_e = *g.nu_e;
     double acc[3];
     auto accelerate = [&] {
       const double m = (sp == 0) ? kMe : (sp == 1 ? g.m_cation : g.m_anion);
@@ -449,7 +450,7 @@ __global__ __launch_bounds__(256) void k_push_mc(int n, double *X0, double *X1, 
     };
     accelerate();
     for (int k = 0;; ++k) {
-      const double numax = (sp == 0) ? g.nu_e : g.nu_i;
+      const double numax = (sp == 0) ? nu_e : g.nu_i;
       double tau;
       uint4 w = make_uint4(0, 0, 0, 0);
       bool last = false;
@@ -799,11 +800,21 @@ __global__ __launch_bounds__(256) void k_inc_update(int n, int k, const double *
   sigma[i] = sigma_last[i] + d;
 }
 
-__global__ __launch_bounds__(256) void k_fill_u64(int n, unsigned long long *p, unsigned long long v) {
+// What the step needs cleared, and in the last workgroup the bound on the
+// electrons' collision frequency: one launch, nothing read back.
+__global__ __launch_bounds__(256) void k_step_init(int n, unsigned long long *key, uint8_t *dead, GasDev g,
+                                                   double *nu_e, unsigned long long *counters) {
+  if (blockIdx.x == gridDim.x - 1) {
+    if (threadIdx.x < NCNT) counters[threadIdx.x] = 0;
+    nu_max(g, nu_e);
+    return;
+  }
   const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = v;
+  if (i >= n) return;
+  key[i] = ~0ull;
+  key[(size_t)n + i] = ~0ull;
+  dead[i] = 0;
 }
-
 __global__ __launch_bounds__(256) void k_fill_i8(int n, int8_t *p) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < n) p[i] = 0;
@@ -812,11 +823,6 @@ __global__ __launch_bounds__(256) void k_fill_i8(int n, int8_t *p) {
 __global__ __launch_bounds__(256) void k_fill_i32(int n, int32_t *p, int32_t v) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < n) p[i] = v;
-}
-
-__global__ __launch_bounds__(256) void k_fill_u8(int n, uint8_t *p) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = 0;
 }
 
 // Recombination (section 3.4.3): each electron proposes to its nearest cation
@@ -862,12 +868,23 @@ __global__ __launch_bounds__(256) void k_recomb_c(int n, const int8_t *sp, const
   }
 }
 
+// Per particle: 1 if it stays (low word), its children (high word).
 __global__ __launch_bounds__(256) void k_keep(int n, const uint8_t *dead, const int8_t *status, const int32_t *n_child,
-                                              int32_t *keep, int32_t *kids) {
+                                              uint64_t *kk) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
-  keep[i] = (!dead[i] && status[i] == 0) ? 1 : 0;
-  kids[i] = 2 * n_child[i];
+  const uint32_t keep = (!dead[i] && status[i] == 0) ? 1 : 0;
+  kk[i] = ((uint64_t)(uint32_t)(2 * n_child[i]) << 32) | keep;
+}
+
+// The step's counters and totals (survivors, children) to the host's words:
+// one wait instead of five copies of 4 to 112 bytes (25-45 us each), which
+// with the copies back in one launch takes a step of 500 to 20,000 charges
+// about 135 us less.
+__global__ void k_totals(int n, const uint64_t *kk, const uint64_t *pos, const unsigned long long *counters,
+                         unsigned long long *host) {
+  if (threadIdx.x < NCNT) host[threadIdx.x] = counters[threadIdx.x];
+  if (threadIdx.x == NCNT) host[NCNT] = kk[n - 1] + pos[n - 1];
 }
 
 struct SoA {
@@ -876,20 +893,22 @@ struct SoA {
   int64_t *id;
 };
 
-__global__ __launch_bounds__(256) void k_compact(int n, SoA in, const int32_t *keep, const int32_t *kpos,
-                                                 const int32_t *kids, const int32_t *cpos, const double *child,
-                                                 int max_ion, int n_surv, int take, int64_t next_id, SoA out) {
+__global__ __launch_bounds__(256) void k_compact(int n, SoA in, const uint64_t *kk, const uint64_t *pos,
+                                                 const double *child, int max_ion, int n_surv, int take,
+                                                 int64_t next_id, SoA out) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
-  if (keep[i]) {
-    const int o = kpos[i];
+  const uint64_t w = kk[i], at = pos[i];
+  if (w & 1) {
+    const int o = (int)(uint32_t)at;
 #pragma unroll
     for (int c = 0; c < 6; ++c) out.c[c][o] = in.c[c][i];
     out.sp[o] = in.sp[i];
     out.id[o] = in.id[i];
   }
-  for (int c = 0; c < kids[i]; ++c) {
-    const int k = cpos[i] + c;
+  const int kids = (int)(w >> 32), first = (int)(at >> 32);
+  for (int c = 0; c < kids; ++c) {
+    const int k = first + c;
     if (k >= take) break;
     const double *rec = child + (((size_t)i * max_ion + c / 2) * 2 + (c & 1)) * 6;
     const int o = n_surv + k;
@@ -898,6 +917,16 @@ __global__ __launch_bounds__(256) void k_compact(int n, SoA in, const int32_t *k
     out.sp[o] = (c & 1) ? 1 : 0;
     out.id[o] = next_id + k;
   }
+}
+
+// The compacted particles back into the caller's arrays.
+__global__ __launch_bounds__(256) void k_copy_back(int n, SoA from, SoA to) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+#pragma unroll
+  for (int c = 0; c < 6; ++c) to.c[c][i] = from.c[c][i];
+  to.sp[i] = from.sp[i];
+  to.id[i] = from.id[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -1063,9 +1092,8 @@ static constexpr double kPefrlLambda = -0.2123418310626054;
 static constexpr double kPefrlChi = -0.06626458266981849;
 
 static obem_status compact_step(obem_ctx *ctx, obem_particles *S, int n, int mi, const uint8_t *dead,
-                                const int8_t *status, const int32_t *nchild, const double *child, int32_t *keep,
-                                int32_t *kids, const unsigned long long *cnt_dev, obem_step_stats out,
-                                obem_step_stats *stats);
+                                const int8_t *status, const int32_t *nchild, const double *child, uint64_t *kk,
+                                const unsigned long long *cnt_dev, obem_step_stats out, obem_step_stats *stats);
 
 extern "C" obem_status track_step(obem_ctx *ctx, obem_meshh *mesh, obem_particles *S, const obem_gas *gas,
                                   const obem_step_params *p, int64_t *dd_counts, double *sigma,
@@ -1192,7 +1220,8 @@ extern "C" obem_status track_step(obem_ctx *ctx, obem_meshh *mesh, obem_particle
   int32_t *nn = (int32_t *)ws_get(ctx, WS_MISC1, sizeof(int32_t) * nz * 4 + 64);
   int8_t *status = (int8_t *)ws_get(ctx, WS_STATUS, nz + 64);
   if (!E || !nn || !status) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
-  int32_t *keep = nn + nz, *kids = nn + 2 * nz, *hitv = nn + 3 * nz;
+  int32_t *hitv = nn + nz;
+  uint64_t *kk = (uint64_t *)(nn + 2 * nz);
   // 2. field at every particle (cells or map + all other particles) and nearest partner
   st = step_field(ctx, mesh, sigma, p->map ? &gmap : nullptr, S, n, p, nullptr, nullptr, E, nn);
   if (st) return st;
@@ -1202,19 +1231,6 @@ extern "C" obem_status track_step(obem_ctx *ctx, obem_meshh *mesh, obem_particle
   unsigned long long *key = (unsigned long long *)ws_get(ctx, WS_MISC2, sizeof(unsigned long long) * 2 * nz);
   uint8_t *dead = (uint8_t *)ws_get(ctx, WS_MISC6, nz + 64);
   if (!key || !dead) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
-  hipLaunchKernelGGL(k_fill_u64, dim3(nbt(2 * n)), dim3(256), 0, ctx->stream, 2 * n, key, ~0ull);
-  hipLaunchKernelGGL(k_fill_u8, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, dead);
-  const double r2 = p->r_rec * p->r_rec;
-  {
-  OBEM_PROF(ctx, "recombine");
-  hipLaunchKernelGGL(k_recomb_a, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, S->species, nn, S->x, S->y, S->z, r2, key);
-  hipLaunchKernelGGL(k_recomb_b, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, S->species, nn, S->x, S->y, S->z, r2,
-                     S->id, key, key + nz);
-  hipLaunchKernelGGL(k_recomb_c, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, S->species, nn, S->x, S->y, S->z, r2,
-                     S->id, key + nz, dead);
-  }
-  OBEM_HIP(ctx, hipGetLastError());
-  // 4. push + null-collision MC + absorption
   GasDev g;
   g.n = gas->n_nodes;
   g.e_min = gas->e_min;
@@ -1234,12 +1250,20 @@ extern "C" obem_status track_step(obem_ctx *ctx, obem_meshh *mesh, obem_particle
   double *nu_dev = (double *)ws_get(ctx, WS_SOLVE2 + 0, 64);
   unsigned long long *cnt_dev = (unsigned long long *)ws_get(ctx, WS_SOLVE1 + 0, 256);
   if (!nu_dev || !cnt_dev) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
-  hipLaunchKernelGGL(k_nu_max, dim3(1), dim3(256), 0, ctx->stream, g, nu_dev);
-  hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(256), 0, ctx->stream, NCNT, cnt_dev, 0ull);
-  OBEM_HIP(ctx, hipGetLastError());
-  OBEM_HIP(ctx, hipMemcpyAsync(&g.nu_e, nu_dev, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-  OBEM_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  g.nu_e = nu_dev;
   g.nu_i = gas->density * (gas->ion_xs_iso + gas->ion_xs_back) * p->ion_v_cap;
+  hipLaunchKernelGGL(k_step_init, dim3(nbt(n) + 1), dim3(256), 0, ctx->stream, n, key, dead, g, nu_dev, cnt_dev);
+  const double r2 = p->r_rec * p->r_rec;
+  {
+  OBEM_PROF(ctx, "recombine");
+  hipLaunchKernelGGL(k_recomb_a, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, S->species, nn, S->x, S->y, S->z, r2, key);
+  hipLaunchKernelGGL(k_recomb_b, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, S->species, nn, S->x, S->y, S->z, r2,
+                     S->id, key, key + nz);
+  hipLaunchKernelGGL(k_recomb_c, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, S->species, nn, S->x, S->y, S->z, r2,
+                     S->id, key + nz, dead);
+  }
+  OBEM_HIP(ctx, hipGetLastError());
+  // 4. push + null-collision MC + absorption
   StepDev sd;
   sd.dt = p->dt;
   sd.step = p->step;
@@ -1277,7 +1301,7 @@ extern "C" obem_status track_step(obem_ctx *ctx, obem_meshh *mesh, obem_particle
                          dd_counts, cnt_dev);
     }
     OBEM_HIP(ctx, hipGetLastError());
-    return compact_step(ctx, S, n, mi, dead, status, nchild, child, keep, kids, cnt_dev, out, stats);
+    return compact_step(ctx, S, n, mi, dead, status, nchild, child, kk, cnt_dev, out, stats);
   }
   hipLaunchKernelGGL(k_fill_i8, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, status);
   hipLaunchKernelGGL(k_fill_i32, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, hitv, -1);
@@ -1317,37 +1341,36 @@ extern "C" obem_status track_step(obem_ctx *ctx, obem_meshh *mesh, obem_particle
                        S->vz, S->species, S->id, dead, g, sd, status, nchild, child, cnt_dev);
   }
   OBEM_HIP(ctx, hipGetLastError());
-  return compact_step(ctx, S, n, mi, dead, status, nchild, child, keep, kids, cnt_dev, out, stats);
+  return compact_step(ctx, S, n, mi, dead, status, nchild, child, kk, cnt_dev, out, stats);
 }
 
 // 5. compaction: survivors in id order, then children in parent order; the
 // step's statistics.
 static obem_status compact_step(obem_ctx *ctx, obem_particles *S, int n, int mi, const uint8_t *dead,
-                                const int8_t *status, const int32_t *nchild, const double *child, int32_t *keep,
-                                int32_t *kids, const unsigned long long *cnt_dev, obem_step_stats out,
-                                obem_step_stats *stats) {
+                                const int8_t *status, const int32_t *nchild, const double *child, uint64_t *kk,
+                                const unsigned long long *cnt_dev, obem_step_stats out, obem_step_stats *stats) {
   const size_t nz = (size_t)n;
-  hipLaunchKernelGGL(k_keep, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, dead, status, nchild, keep, kids);
-  int32_t *kpos = (int32_t *)ws_get(ctx, WS_KEYS0, sizeof(int32_t) * nz);
-  int32_t *cpos = (int32_t *)ws_get(ctx, WS_KEYS1, sizeof(int32_t) * nz);
-  if (!kpos || !cpos) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
-  size_t tb = 0, tb2 = 0;
-  OBEM_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tb, keep, kpos, n, ctx->stream));
-  OBEM_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tb2, kids, cpos, n, ctx->stream));
-  void *tmp = ws_get(ctx, WS_SORT_TMP, std::max(tb, tb2) + 256);
+  if (!ctx->host_words &&
+      hipHostMalloc((void **)&ctx->host_words, sizeof(unsigned long long) * (NCNT + 1), hipHostMallocDefault) !=
+          hipSuccess) {
+    (void)hipGetLastError();
+    ctx->host_words = nullptr;
+    return fail(ctx, OBEM_ENOMEM, "pinned allocation failed");
+  }
+  hipLaunchKernelGGL(k_keep, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, dead, status, nchild, kk);
+  uint64_t *pos = (uint64_t *)ws_get(ctx, WS_KEYS0, sizeof(uint64_t) * nz);
+  if (!pos) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
+  size_t tb = 0;
+  OBEM_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tb, kk, pos, n, ctx->stream));
+  void *tmp = ws_get(ctx, WS_SORT_TMP, tb + 256);
   if (!tmp) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
-  OBEM_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(tmp, tb, keep, kpos, n, ctx->stream));
-  OBEM_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(tmp, tb2, kids, cpos, n, ctx->stream));
-  int32_t tail[4];
-  OBEM_HIP(ctx, hipMemcpyAsync(&tail[0], kpos + n - 1, 4, hipMemcpyDeviceToHost, ctx->stream));
-  OBEM_HIP(ctx, hipMemcpyAsync(&tail[1], keep + n - 1, 4, hipMemcpyDeviceToHost, ctx->stream));
-  OBEM_HIP(ctx, hipMemcpyAsync(&tail[2], cpos + n - 1, 4, hipMemcpyDeviceToHost, ctx->stream));
-  OBEM_HIP(ctx, hipMemcpyAsync(&tail[3], kids + n - 1, 4, hipMemcpyDeviceToHost, ctx->stream));
-  unsigned long long hc[NCNT];
-  OBEM_HIP(ctx, hipMemcpyAsync(hc, cnt_dev, sizeof(hc), hipMemcpyDeviceToHost, ctx->stream));
+  OBEM_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(tmp, tb, kk, pos, n, ctx->stream));
+  unsigned long long *hc = ctx->host_words;
+  hipLaunchKernelGGL(k_totals, dim3(1), dim3(64), 0, ctx->stream, n, kk, pos, cnt_dev, hc);
+  OBEM_HIP(ctx, hipGetLastError());
   OBEM_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  const int64_t n_surv = (int64_t)tail[0] + tail[1];
-  const int64_t n_new = (int64_t)tail[2] + tail[3];
+  const int64_t n_surv = (int64_t)(uint32_t)hc[NCNT];
+  const int64_t n_new = (int64_t)(hc[NCNT] >> 32);
   const int64_t take = std::min<int64_t>(n_new, S->capacity - n_surv);
   // output buffers
   const size_t cap = (size_t)(n_surv + take);
@@ -1365,13 +1388,10 @@ static obem_status compact_step(obem_ctx *ctx, obem_particles *S, int n, int mi,
   o.sp = (int8_t *)(ob + 7 * cap);
   if (cap > 0) {
     OBEM_PROF(ctx, "compact");
-    hipLaunchKernelGGL(k_compact, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, in, keep, kpos, kids, cpos, child, mi,
-                       (int)n_surv, (int)take, S->next_id, o);
+    hipLaunchKernelGGL(k_compact, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, in, kk, pos, child, mi, (int)n_surv,
+                       (int)take, S->next_id, o);
+    hipLaunchKernelGGL(k_copy_back, dim3(nbt((int)cap)), dim3(256), 0, ctx->stream, (int)cap, o, in);
     OBEM_HIP(ctx, hipGetLastError());
-    for (int c = 0; c < 6; ++c)
-      OBEM_HIP(ctx, hipMemcpyAsync(ic[c], o.c[c], sizeof(double) * cap, hipMemcpyDeviceToDevice, ctx->stream));
-    OBEM_HIP(ctx, hipMemcpyAsync(S->id, o.id, sizeof(int64_t) * cap, hipMemcpyDeviceToDevice, ctx->stream));
-    OBEM_HIP(ctx, hipMemcpyAsync(S->species, o.sp, cap, hipMemcpyDeviceToDevice, ctx->stream));
   }
   OBEM_HIP(ctx, hipStreamSynchronize(ctx->stream));
   // recombined count: n - survivors - absorbed - left (children not counted)
