@@ -813,9 +813,10 @@ __global__ __launch_bounds__(kThreads) void k_panel_fp64(int n_t, const double *
 // FP64 closed-form zone of both modes (MIXED: R < 3 D by the far kernel's FP32
 // test on the same recentred values; else R < 48 D by its FP64 test), added
 // to the far kernel's partial sums of the same cell range (gridDim.y splits
-// the cells as there; one writer per entry, stream order).  One wave per
-// workgroup: the zone's work is uneven over targets and cells, and single
-// waves spread it over the chip.  The wave bounds its 64 targets by a sphere
+// the cells as there; one writer per entry, stream order).  A workgroup has 64
+// targets and WAVES waves, each with its share of every tile's cells: the
+// zone's work is uneven over targets and cells, and a wave whose targets are
+// close to a whole tile runs 64 batches one after the other.  A wave bounds its 64 targets by a sphere
 // and visits the 64-cell tiles whose zone sphere (centre, max_k |c_k -
 // centre| + zone D_k, slightly inflated) it meets; in a tile, lane k tests
 // cell k once against the sphere, and the flagged cells take the per-lane
@@ -827,20 +828,34 @@ __global__ __launch_bounds__(kThreads) void k_panel_fp64(int n_t, const double *
 // results in queue order (deterministic).  Bound by
 // the closed form's FP64 operations.  Measured against the closed form of
 // every flagged cell for the whole wave: mixed, 97 points and 4,096 cells 84
-// -> 34 us, 200,003 points and 40,776 cells 1346 -> 475 us; FP64, 50,000
+// -> 34 us (14 us with four waves), 200,003 points and 40,776 cells 1346 -> 475 us; FP64, 50,000
 // points and 40,776 cells 5.65 -> 2.87 ms.  kDenseLanes 8 to 32 differ by 1 %.
 constexpr int kDenseLanes = 32;
+// Four waves a workgroup up to this many workgroups (64 targets x splits), one
+// beyond, where the chip is full with single waves and four repeat the tests
+// of the tiles.  One -> four waves, calls: mixed, 128 workgroups 109 -> 89 us,
+// 19,000 (20,000 charges in the holes) 1.66 -> 1.58 ms, but 23,400 (a fine
+// plate) 535 -> 567 us, 60,000 2.79 -> 2.94 ms, 200,000 8.4 -> 9.0 ms; FP64
+// (more pairs a test) 4,096 250 -> 212 us, 8,000 2.55 -> 1.85 ms, 50,000 10.1 ->
+// 9.9 ms, but 78,000 4.31 -> 4.43 ms, 200,000 13.8 -> 14.4 ms.
+constexpr int kCloseFew = 20480, kCloseFewFp64 = 61440;
 
-template <bool WANT_V, bool MIXED>
-__global__ __launch_bounds__(64) void k_panel_close(int n_t, const double *__restrict__ xs, int N,
-                                                    const double *__restrict__ f, const double *__restrict__ rec,
-                                                    const double *__restrict__ sigma,
-                                                    const double *__restrict__ tiles, int cchunk, double *part) {
+template <bool WANT_V, bool MIXED, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_panel_close(int n_t, const double *__restrict__ xs, int N,
+                                                            const double *__restrict__ f,
+                                                            const double *__restrict__ rec,
+                                                            const double *__restrict__ sigma,
+                                                            const double *__restrict__ tiles, int cchunk,
+                                                            double *part) {
   constexpr int NC = WANT_V ? 4 : 3;
-  __shared__ double X[3][64];
-  __shared__ double R[NC][64];
-  __shared__ int qk[128], ql[128];
-  const int lane = threadIdx.x;
+  __shared__ double Xs[WAVES][3][64];
+  __shared__ double Rs[WAVES][NC][64];
+  __shared__ int qks[WAVES][128], qls[WAVES][128];
+  const int lane = threadIdx.x & 63, wave = WAVES == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  auto &X = Xs[wave];
+  auto &R = Rs[wave];
+  auto &qk = qks[wave];
+  auto &ql = qls[wave];
   const int i = blockIdx.x * 64 + lane;
   const bool active = i < n_t;
   const int ii = active ? i : n_t - 1;
@@ -918,6 +933,7 @@ __global__ __launch_bounds__(64) void k_panel_close(int n_t, const double *__res
       }
     }
     uint64_t m = __ballot(flag);
+    if (WAVES == 4) m &= 0x1111111111111111ull << wave;  // this wave's share of the tile
     for (;;) {
       for (; m && qn < 64; m &= m - 1ull) {
         const int k = __builtin_amdgcn_readfirstlane(__builtin_ctzll(m));
@@ -970,8 +986,8 @@ __global__ __launch_bounds__(64) void k_panel_close(int n_t, const double *__res
       const int n = t < te ? (qn >= 64 ? 64 : 0) : min(qn, 64);
       if (n == 0) break;
       // the first n queued pairs, one per lane; then every lane adds its own
-      // (one wave: the barriers only order the LDS accesses)
-      __syncthreads();
+      // (within the wave: the fences only order the LDS accesses)
+      wave_lds_fence();
       if (lane < n) {
         const int k = qk[lane], l = ql[lane];
         d3 E;
@@ -983,7 +999,7 @@ __global__ __launch_bounds__(64) void k_panel_close(int n_t, const double *__res
         R[2][lane] = sg * E.z;
         if (WANT_V) R[NC - 1][lane] = sg * V;
       }
-      __syncthreads();
+      wave_lds_fence();
       for (; mine; mine &= mine - 1ull) {
         const int j = __builtin_ctzll(mine);
         ex += R[0][j];
@@ -999,11 +1015,27 @@ __global__ __launch_bounds__(64) void k_panel_close(int n_t, const double *__res
         k2 = qk[64 + lane];
         l2 = ql[64 + lane];
       }
-      __syncthreads();
+      wave_lds_fence();
       if (lane < qn) {
         qk[lane] = k2;
         ql[lane] = l2;
       }
+    }
+  }
+  if (WAVES > 1) {  // the waves' sums, in their order
+    wave_lds_fence();
+    R[0][lane] = ex;
+    R[1][lane] = ey;
+    R[2][lane] = ez;
+    if (WANT_V) R[NC - 1][lane] = ev;
+    __syncthreads();
+    if (wave != 0) return;
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) {
+      ex += Rs[w][0][lane];
+      ey += Rs[w][1][lane];
+      ez += Rs[w][2][lane];
+      if (WANT_V) ev += Rs[w][NC - 1][lane];
     }
   }
   if (active) {
@@ -1091,13 +1123,25 @@ obem_status launch_panel_field(obem_ctx *ctx, const obem_meshh *m, const double 
   // the near kernel of split y adds the closed-form pairs of the same cell
   // range into the same slot (one writer per entry, after the far kernel),
   // then the slots are added in split order
-#define PANEL_CLOSE(V, M, T)                                                                                     \
-  hipLaunchKernelGGL((k_panel_close<V, M>), dim3((n_t + 63) / 64, ns), dim3(64), 0, ctx->stream, n_t, to.xs, N, m->f, \
-                     m->rec, sigma, T, cchunk, part)
+#define PANEL_CLOSE(V, M, T)                                                                              \
+  if (few)                                                                                                \
+    hipLaunchKernelGGL((k_panel_close<V, M, 4>), dim3(bw, ns), dim3(256), 0, ctx->stream, n_t, to.xs, N, m->f, \
+                       m->rec, sigma, T, cchunk, part);                                                    \
+  else                                                                                                    \
+    hipLaunchKernelGGL((k_panel_close<V, M, 1>), dim3(bw, ns), dim3(64), 0, ctx->stream, n_t, to.xs, N, m->f, \
+                       m->rec, sigma, T, cchunk, part)
+  const int bw = (n_t + 63) / 64;
+  const bool few = (int64_t)bw * ns <= (prec == OBEM_MIXED ? kCloseFew : kCloseFewFp64);
   if (prec == OBEM_MIXED) {
-    if (want_v) PANEL_CLOSE(true, true, m->tiles); else PANEL_CLOSE(false, true, m->tiles);
+    if (want_v) {
+      PANEL_CLOSE(true, true, m->tiles);
+    } else {
+      PANEL_CLOSE(false, true, m->tiles);
+    }
+  } else if (want_v) {
+    PANEL_CLOSE(true, false, m->tiles48);
   } else {
-    if (want_v) PANEL_CLOSE(true, false, m->tiles48); else PANEL_CLOSE(false, false, m->tiles48);
+    PANEL_CLOSE(false, false, m->tiles48);
   }
 #undef PANEL_CLOSE
 #undef PANEL_FAR
