@@ -230,25 +230,56 @@ void launch_tile_boxes(obem_ctx *ctx, int n, const double *src, double *box) {
   if (n > 0) hipLaunchKernelGGL(k_tile_boxes, dim3(nblk(n)), dim3(256), 0, ctx->stream, n, src, box);
 }
 
-// Small sets, one workgroup each and two of them side by side: box, keys,
-// sort and (GATHER) copies in one launch instead of five to ten, each of which
-// costs its latency.  T threads of ITEMS points, stable block radix sort in
-// LDS.  Source copy and target order of 64 points took about 65 us before and
-// take 6, of 1,000 points 16, of 4,096 points 35; above 256 points the copies
-// are faster in a launch of their own (4,096: 51 us with them), above 4,096
-// the launches of order_large.
-constexpr int kSmallOrder = 4096;
+// Up to 256 points, one workgroup a set and two of them side by side: box,
+// keys, stable radix sort in LDS and copies in one launch instead of five to
+// ten, each of which costs its latency (64 points 65 -> 6 us).
+constexpr int kTinyOrder = 256;
 
-template <int T, int ITEMS, bool GATHER>
-__global__ __launch_bounds__(T) void k_order_small(OrderPair jobs) {
-  using Sort = hipcub::BlockRadixSort<uint32_t, T, ITEMS, int32_t>;
+__global__ __launch_bounds__(kTinyOrder) void k_order_tiny(OrderPair jobs) {
+  using Sort = hipcub::BlockRadixSort<uint32_t, kTinyOrder, 1, int32_t>;
   __shared__ typename Sort::TempStorage tmp;
-  __shared__ int32_t order[T * ITEMS];
-  __shared__ double red[6 * (T / 64)];
+  __shared__ double red[6 * (kTinyOrder / 64)];
   const OrderJob &J = jobs.job[blockIdx.x];
   const int n = J.n, t = threadIdx.x;
   double box[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
-  for (int i = t; i < n; i += T) {
+  if (t < n) {
+    box[0] = box[3] = J.x[t];
+    box[1] = box[4] = J.y[t];
+    box[2] = box[5] = J.z[t];
+  }
+  block_box<kTinyOrder>(box, red);
+  // padding keys sort behind every point (equal keys keep their order)
+  uint32_t key[1] = {t < n ? order_key(J, t, box, box + 3) : 0xffffffffu};
+  int32_t idx[1] = {t};
+  Sort(tmp).Sort(key, idx, 0, (J.q || J.species) ? 32 : 30);
+  double v[3] = {0.0, 0.0, 0.0};
+  if (t < n) {
+    J.perm[t] = idx[0];
+    order_gather(J, t, idx[0], v);
+  }
+  __syncthreads();  // red is consumed
+  if (J.tbox) tile_box(v, t < n, t, red, J.tbox);
+}
+
+// Small sets: a point's place is the number of keys before its own, counted
+// against all of them.  n^2 comparisons are less than the passes of a sort
+// while a launch of 16 points a workgroup does not fill the chip: every
+// workgroup holds all keys, four a thread, and counts by ballots.
+// Every workgroup of the keys' launch reduces the whole box itself.  A call
+// with 4,096 charges in place of one workgroup's radix sort in LDS 212 -> 198
+// us, against the launches of order_large with 4,097 charges 128 -> 111, with
+// 8,000 130 -> 115, but with 16,000 134 -> 147 us.
+constexpr int kSmallOrder = 8192;
+constexpr int kRankPoints = 16;
+
+__global__ __launch_bounds__(1024) void k_order_key_small(OrderPair jobs, uint32_t *k0, uint32_t *k1) {
+  __shared__ double red[6 * 16];
+  const OrderJob &J = jobs.job[blockIdx.y];
+  const int n = J.n, t = threadIdx.x;
+  if ((int)blockIdx.x * 1024 >= n) return;  // workgroup-uniform
+  double box[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll 4
+  for (int i = t; i < n; i += 1024) {
     const double v[3] = {J.x[i], J.y[i], J.z[i]};
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -256,36 +287,54 @@ __global__ __launch_bounds__(T) void k_order_small(OrderPair jobs) {
       box[3 + c] = fmax(box[3 + c], v[c]);
     }
   }
-  block_box<T>(box, red);
-  // padding keys sort behind every point (equal keys keep their order)
-  uint32_t key[ITEMS];
-  int32_t idx[ITEMS];
+  block_box<1024>(box, red);
+  const int i = blockIdx.x * 1024 + t;
+  if (i < n) (blockIdx.y ? k1 : k0)[i] = order_key(J, i, box, box + 3);
+}
+
+__global__ __launch_bounds__(1024) void k_order_rank(OrderPair jobs, const uint32_t *__restrict__ k0,
+                                                     const uint32_t *__restrict__ k1) {
+  __shared__ int cnt[16][kRankPoints];
+  const OrderJob &J = jobs.job[blockIdx.y];
+  const uint32_t *__restrict__ keys = blockIdx.y ? k1 : k0;
+  const int n = J.n, t = threadIdx.x, first = blockIdx.x * kRankPoints;
+  if (first >= n) return;  // workgroup-uniform
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  uint32_t own[kRankPoints];
+  int c[kRankPoints];
 #pragma unroll
-  for (int u = 0; u < ITEMS; ++u) {
-    const int i = t * ITEMS + u;
-    idx[u] = i;
-    key[u] = i < n ? order_key(J, i, box, box + 3) : 0xffffffffu;
+  for (int p = 0; p < kRankPoints; ++p) {
+    own[p] = keys[min(first + p, n - 1)];
+    c[p] = 0;
   }
-  Sort(tmp).Sort(key, idx, 0, (J.q || J.species) ? 32 : 30);
-  if (!GATHER) {
+  for (int base = 0; base < n; base += 4096) {
+    uint32_t k[4];
+    const int j0 = base + 4 * t, w0 = base + 256 * wave;
 #pragma unroll
-    for (int u = 0; u < ITEMS; ++u)
-      if (t * ITEMS + u < n) J.perm[t * ITEMS + u] = idx[u];
-    return;
+    for (int u = 0; u < 4; ++u) k[u] = j0 + u < n ? keys[j0 + u] : 0xffffffffu;
+    // equal keys keep their order: those of a wave's 256 points are all
+    // before, all behind or around the workgroup's points
+    auto count = [&](auto before) {
+#pragma unroll
+      for (int p = 0; p < kRankPoints; ++p)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) c[p] += __popcll(__ballot(before(k[u], own[p], j0 + u < first + p)));
+    };
+    if (w0 + 256 <= first)
+      count([](uint32_t a, uint32_t b, bool) { return a <= b; });
+    else if (w0 > first)
+      count([](uint32_t a, uint32_t b, bool) { return a < b; });
+    else
+      count([](uint32_t a, uint32_t b, bool l) { return a < b || (a == b && l); });
   }
+  if ((t & 63) == 0)
 #pragma unroll
-  for (int u = 0; u < ITEMS; ++u) order[t * ITEMS + u] = idx[u];
-  for (int i0 = 0; i0 < n; i0 += T) {
-    __syncthreads();  // order is written, the previous round's red consumed
-    const int i = i0 + t;
-    double v[3] = {0.0, 0.0, 0.0};
-    if (i < n) {
-      const int j = order[i];
-      J.perm[i] = j;
-      order_gather(J, i, j, v);
-    }
-    if (J.tbox)
-      tile_box(v, i < n, t & 255, red + 24 * (t >> 8), i / 256 * 256 < n ? J.tbox + 6 * (size_t)(i / 256) : nullptr);
+    for (int p = 0; p < kRankPoints; ++p) cnt[wave][p] = c[p];
+  __syncthreads();
+  if (t < kRankPoints && first + t < n) {
+    int r = 0;
+    for (int w = 0; w < 16; ++w) r += cnt[w][t];
+    J.perm[r] = first + t;
   }
 }
 
@@ -330,13 +379,14 @@ obem_status order_points(obem_ctx *ctx, const OrderJob &a, const OrderJob &b) {
   }
   if (ns) {
     const int m = std::max(small.job[0].n, small.job[1].n);
-    if (m <= 256) {
-      hipLaunchKernelGGL((k_order_small<256, 1, true>), dim3(ns), dim3(256), 0, ctx->stream, small);
+    if (m <= kTinyOrder) {
+      hipLaunchKernelGGL(k_order_tiny, dim3(ns), dim3(kTinyOrder), 0, ctx->stream, small);
     } else {
-      if (m <= 1024)
-        hipLaunchKernelGGL((k_order_small<1024, 1, false>), dim3(ns), dim3(1024), 0, ctx->stream, small);
-      else
-        hipLaunchKernelGGL((k_order_small<1024, 4, false>), dim3(ns), dim3(1024), 0, ctx->stream, small);
+      uint32_t *k0 = (uint32_t *)ws_get(ctx, WS_KEYS0, sizeof(uint32_t) * small.job[0].n);
+      uint32_t *k1 = ns > 1 ? (uint32_t *)ws_get(ctx, WS_KEYS1, sizeof(uint32_t) * small.job[1].n) : nullptr;
+      if (!k0 || (ns > 1 && !k1)) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
+      hipLaunchKernelGGL(k_order_key_small, dim3(nblk(m, 1024), ns), dim3(1024), 0, ctx->stream, small, k0, k1);
+      hipLaunchKernelGGL(k_order_rank, dim3(nblk(m, kRankPoints), ns), dim3(1024), 0, ctx->stream, small, k0, k1);
       hipLaunchKernelGGL(k_order_gather, dim3(nblk(m), ns), dim3(256), 0, ctx->stream, small);
     }
     OBEM_HIP(ctx, hipGetLastError());

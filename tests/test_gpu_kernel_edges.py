@@ -151,8 +151,8 @@ def test_point_layouts(ctx):
 @pytest.mark.parametrize("n", [1, 2, 127, 128, 129, 1024, 1025, 4095, 4096, 4097, 5000])
 @pytest.mark.parametrize("kind", ["spread", "same_cell", "line"])
 def test_orderings(ctx, orc, n, kind):
-    """Source copy and target order around the sizes of the one-workgroup
-    sort (128, 1,024 threads, 4,096): many points in one cell of the curve's
+    """Source copy and target order of small and larger sets (around 128,
+    1,024 and 4,096 points): many points in one cell of the curve's
     grid (ties keep the caller's order), on a line, charges of both signs and
     zero, through the field with separate targets, against the oracle, and
     the same bit for bit in a second call."""
@@ -308,3 +308,30 @@ def test_chords_through_the_grid(ctx, orc, dt):
     assert sg["absorbed"] == so["absorbed"]
     assert np.array_equal(host(counts_g), counts)
     assert np.array_equal(host(parts.state()["id"]), state["id"])
+
+
+@pytest.mark.parametrize("n", [256, 257, 271, 4096, 4097, 8191, 8192, 8193])
+@pytest.mark.parametrize("kind", ["spread", "same_cell", "line"])
+def test_counted_places(ctx, orc, n, kind):
+    """Orderings around the sizes of the counted places (above 256 points, 16 a
+    workgroup, 4,096 keys a pass, up to 8,192), distinct and equal keys.  A
+    point lost or taken twice changes the potential of equal charges by 1 / n
+    of it; FP32 terms are off by at most 17 ulps and a tile's 256 sums by 256:
+    2e-5 of the sum of magnitudes (for a potential of one sign, of itself)."""
+    rng = np.random.default_rng(n)
+    x = rng.uniform(size=(n, 3)) * 1e-4
+    if kind == "same_cell":
+        x[n // 3:] = x[0] + 1e-9 * rng.uniform(size=(n - n // 3, 3))
+    elif kind == "line":
+        x[:, 1:] = 2e-5
+    q = np.full(n, W.E_CHARGE)
+    xt = rng.uniform(size=(n, 3)) * 1e-4
+    ref, vref = orc.pair_field(xt, x, q, 1e-6, want_v=True)
+    for prec, tol in ((B.OBEM_FP64, 1e-12), (B.OBEM_MIXED, 2e-5)):
+        E, V = B.field_eval(ctx, None, None, dev(x), dev(q), dev(xt), 1e-6, prec, want_v=True)
+        assert (np.abs(host(V) - vref) / vref).max() <= tol
+        # the signs' classes, both jobs of one size, and what the coordinates are worth
+        s = np.where(np.arange(n) % 3 == 0, -W.E_CHARGE, W.E_CHARGE)
+        _, v2 = orc.pair_field(xt, x, s, 1e-6, want_v=True)
+        _, V2 = B.field_eval(ctx, None, None, dev(x), dev(s), dev(xt), 1e-6, prec, want_v=True)
+        assert (np.abs(host(V2) - v2) / vref).max() <= tol
