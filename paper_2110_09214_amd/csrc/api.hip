@@ -608,6 +608,11 @@ static obem_status field_eval_impl(obem_ctx *ctx, const obem_meshh *mesh, const 
   // the pair-once evaluation adds to the accumulator; otherwise the partial
   // sums of cells and charges are added and scattered in one pass
   Slots cells, pairs;
+  if (mesh && n_src > 0 && !once && side_by_side(ctx, n_tgt, mesh->n, n_src)) {
+    st = launch_cells_and_charges(ctx, mesh, sigma, so, to, soft, precision, tis, want_v, acc, &cells, &pairs);
+    if (st) return st;
+    return launch_finish(ctx, to, cells, pairs, kKe, Ex, Ey, Ez, want_v ? V : nullptr);
+  }
   if (mesh)
     st = launch_panel_field(ctx, mesh, sigma, to, precision, want_v, acc, once ? nullptr : &cells);
   else if (once)

@@ -525,16 +525,15 @@ __device__ __forceinline__ void neumaier(float &s, float &c, float v) {
   s = t;
 }
 
+// Target tile bx and split by of the cells into ranges of cchunk; split y writes
+// its sums to part + 4 n_t y (part = acc when there is one split).
 template <bool WANT_V>
-// gridDim.y splits the cells into ranges of cchunk; split y writes its sums
-// to part + 4 n_t y (part = acc when there is one split).
-__global__ __launch_bounds__(kThreads) void k_panel_mixed(int n_t, const double *__restrict__ xs, int N,
-                                                          const double *__restrict__ f,
-                                                          const double *__restrict__ sigma, int cchunk,
-                                                          double *part) {
+__device__ __forceinline__ void panel_mixed(int bx, int by, int n_t, const double *__restrict__ xs, int N,
+                                            const double *__restrict__ f, const double *__restrict__ sigma,
+                                            int cchunk, double *part) {
   __shared__ PanelCell T[kPT];
   const int tid = threadIdx.x;
-  const int i0 = blockIdx.x * kThreads;
+  const int i0 = bx * kThreads;
   const int i = i0 + tid;
   const bool active = i < n_t;
   const double c0 = xs[i0], c1 = xs[(size_t)n_t + i0], c2 = xs[2 * (size_t)n_t + i0];
@@ -563,7 +562,7 @@ __global__ __launch_bounds__(kThreads) void k_panel_mixed(int n_t, const double 
     rw *= 1.0001f;
   }
   float hx = 0.f, hy = 0.f, hz = 0.f, hv = 0.f, lx = 0.f, ly = 0.f, lz = 0.f, lv = 0.f;
-  const int kb = blockIdx.y * cchunk, ke = min(N, kb + cchunk);
+  const int kb = by * cchunk, ke = min(N, kb + cchunk);
   for (int k0 = kb; k0 < ke; k0 += kPT) {
     const int cnt = min(kPT, ke - k0);
     __syncthreads();
@@ -745,12 +744,19 @@ __global__ __launch_bounds__(kThreads) void k_panel_mixed(int n_t, const double 
     if (WANT_V) neumaier(hv, lv, pv);
   }
   if (active) {
-    double *acc = part + (size_t)blockIdx.y * 4 * n_t;
+    double *acc = part + (size_t)by * 4 * n_t;
     acc[i] = (double)hx + (double)lx;
     acc[(size_t)n_t + i] = (double)hy + (double)ly;
     acc[2 * (size_t)n_t + i] = (double)hz + (double)lz;
     acc[3 * (size_t)n_t + i] = WANT_V ? (double)hv + (double)lv : 0.0;
   }
+}
+
+template <bool WANT_V>
+__global__ __launch_bounds__(kThreads) void k_panel_mixed(int n_t, const double *__restrict__ xs, int N,
+                                                          const double *__restrict__ f,
+                                                          const double *__restrict__ sigma, int cchunk, double *part) {
+  panel_mixed<WANT_V>(blockIdx.x, blockIdx.y, n_t, xs, N, f, sigma, cchunk, part);
 }
 
 // FP64 mode: closed form up to 48 diameters (k_panel_close), FP64
@@ -776,20 +782,18 @@ struct alignas(16) CellF64 {
 };
 
 template <bool WANT_V>
-__global__ __launch_bounds__(kThreads) void k_panel_fp64(int n_t, const double *__restrict__ xs, int N,
-                                                         const double *__restrict__ f,
-                                                         const double *__restrict__ rec,
-                                                         const double *__restrict__ sigma, int cchunk,
-                                                         double *part) {
+__device__ __forceinline__ void panel_fp64(int bx, int by, int n_t, const double *__restrict__ xs, int N,
+                                           const double *__restrict__ f, const double *__restrict__ rec,
+                                           const double *__restrict__ sigma, int cchunk, double *part) {
   __shared__ CellF64 T[kPF];
   constexpr double kTa = 1.0 - 3.0 * Rule7::a, kTb = 1.0 - 3.0 * Rule7::b;
   const int tid = threadIdx.x;
-  const int i = blockIdx.x * kThreads + tid;
+  const int i = bx * kThreads + tid;
   const bool active = i < n_t;
   const int ii = active ? i : 0;
   const double x0 = xs[ii], x1 = xs[(size_t)n_t + ii], x2 = xs[2 * (size_t)n_t + ii];
   double ex = 0.0, ey = 0.0, ez = 0.0, ev = 0.0;
-  const int kb = blockIdx.y * cchunk, ke = min(N, kb + cchunk);
+  const int kb = by * cchunk, ke = min(N, kb + cchunk);
   for (int k0 = kb; k0 < ke; k0 += kPF) {
     const int cnt = min(kPF, ke - k0);
     __syncthreads();
@@ -852,12 +856,19 @@ __global__ __launch_bounds__(kThreads) void k_panel_fp64(int n_t, const double *
     }
   }
   if (active) {
-    double *acc = part + (size_t)blockIdx.y * 4 * n_t;
+    double *acc = part + (size_t)by * 4 * n_t;
     acc[i] = ex;
     acc[(size_t)n_t + i] = ey;
     acc[2 * (size_t)n_t + i] = ez;
     acc[3 * (size_t)n_t + i] = ev;
   }
+}
+
+template <bool WANT_V>
+__global__ __launch_bounds__(kThreads) void k_panel_fp64(int n_t, const double *__restrict__ xs, int N,
+                                                         const double *__restrict__ f, const double *__restrict__ rec,
+                                                         const double *__restrict__ sigma, int cchunk, double *part) {
+  panel_fp64<WANT_V>(blockIdx.x, blockIdx.y, n_t, xs, N, f, rec, sigma, cchunk, part);
 }
 
 // FP64 closed-form zone of both modes (MIXED: R < 3 D by the far kernel's FP32
@@ -1142,12 +1153,12 @@ obem_status launch_finish(obem_ctx *ctx, const TargetOrder &to, const Slots &cel
   return OBEM_OK;
 }
 
-obem_status launch_panel_field(obem_ctx *ctx, const obem_meshh *m, const double *sigma, const TargetOrder &to,
-                               obem_precision prec, bool want_v, double *acc, Slots *slots) {
-  const int n_t = to.n;
-  if (slots) *slots = Slots{acc, 0};
-  if (n_t == 0) return OBEM_OK;
-  const int N = (int)m->n;
+// Splits of the cells for n_t targets, and where the sums go.
+struct PanelPlan {
+  int bt, ns, cchunk;
+  double *part;
+};
+static obem_status panel_plan(obem_ctx *ctx, int n_t, int N, double *acc, PanelPlan *P) {
   const int bt = nblk(n_t);
   // cell ranges of >= 64 cells (a multiple of both LDS tiles), about
   // kSplitWorkgroups workgroups in all
@@ -1161,27 +1172,25 @@ obem_status launch_panel_field(obem_ctx *ctx, const obem_meshh *m, const double 
     part = (double *)ws_get(ctx, WS_PANEL, sizeof(double) * 4 * (size_t)n_t * ns);
     if (!part) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
   }
-  dim3 gsplit(bt, ns), block(kThreads);
-  OBEM_PROF(ctx, "panel");
-#define PANEL_FAR(K, V, ...) \
-  hipLaunchKernelGGL(K<V>, gsplit, block, 0, ctx->stream, n_t, to.xs, N, m->f, __VA_ARGS__ sigma, cchunk, part)
-  if (prec == OBEM_MIXED) {
-    if (want_v) PANEL_FAR(k_panel_mixed, true, ); else PANEL_FAR(k_panel_mixed, false, );
-  } else {
-    if (want_v) PANEL_FAR(k_panel_fp64, true, m->rec, ); else PANEL_FAR(k_panel_fp64, false, m->rec, );
-  }
-  // the near kernel of split y adds the closed-form pairs of the same cell
-  // range into the same slot (one writer per entry, after the far kernel),
-  // then the slots are added in split order
+  *P = PanelPlan{bt, ns, cchunk, part};
+  return OBEM_OK;
+}
+
+// The near kernel of split y adds the closed-form pairs of the same cell range
+// into the same slot (one writer per entry, after the far kernel); the slots
+// are added in split order.
+static void launch_panel_close(obem_ctx *ctx, const obem_meshh *m, const double *sigma, const TargetOrder &to,
+                               obem_precision prec, bool want_v, const PanelPlan &P) {
+  const int n_t = to.n, N = (int)m->n;
 #define PANEL_CLOSE(V, M, T)                                                                              \
   if (few)                                                                                                \
-    hipLaunchKernelGGL((k_panel_close<V, M, 4>), dim3(bw, ns), dim3(256), 0, ctx->stream, n_t, to.xs, N, m->f, \
-                       m->rec, sigma, T, cchunk, part);                                                    \
+    hipLaunchKernelGGL((k_panel_close<V, M, 4>), dim3(bw, P.ns), dim3(256), 0, ctx->stream, n_t, to.xs, N, m->f, \
+                       m->rec, sigma, T, P.cchunk, P.part);                                                    \
   else                                                                                                    \
-    hipLaunchKernelGGL((k_panel_close<V, M, 1>), dim3(bw, ns), dim3(64), 0, ctx->stream, n_t, to.xs, N, m->f, \
-                       m->rec, sigma, T, cchunk, part)
+    hipLaunchKernelGGL((k_panel_close<V, M, 1>), dim3(bw, P.ns), dim3(64), 0, ctx->stream, n_t, to.xs, N, m->f, \
+                       m->rec, sigma, T, P.cchunk, P.part)
   const int bw = (n_t + 63) / 64;
-  const bool few = (int64_t)bw * ns <= (prec == OBEM_MIXED ? kCloseFew : kCloseFewFp64);
+  const bool few = (int64_t)bw * P.ns <= (prec == OBEM_MIXED ? kCloseFew : kCloseFewFp64);
   if (prec == OBEM_MIXED) {
     if (want_v) {
       PANEL_CLOSE(true, true, m->tiles);
@@ -1194,11 +1203,32 @@ obem_status launch_panel_field(obem_ctx *ctx, const obem_meshh *m, const double 
     PANEL_CLOSE(false, false, m->tiles48);
   }
 #undef PANEL_CLOSE
+}
+
+obem_status launch_panel_field(obem_ctx *ctx, const obem_meshh *m, const double *sigma, const TargetOrder &to,
+                               obem_precision prec, bool want_v, double *acc, Slots *slots) {
+  const int n_t = to.n;
+  if (slots) *slots = Slots{acc, 0};
+  if (n_t == 0) return OBEM_OK;
+  const int N = (int)m->n;
+  PanelPlan P;
+  const obem_status st = panel_plan(ctx, n_t, N, acc, &P);
+  if (st) return st;
+  dim3 gsplit(P.bt, P.ns), block(kThreads);
+  OBEM_PROF(ctx, "panel");
+#define PANEL_FAR(K, V, ...) \
+  hipLaunchKernelGGL(K<V>, gsplit, block, 0, ctx->stream, n_t, to.xs, N, m->f, __VA_ARGS__ sigma, P.cchunk, P.part)
+  if (prec == OBEM_MIXED) {
+    if (want_v) PANEL_FAR(k_panel_mixed, true, ); else PANEL_FAR(k_panel_mixed, false, );
+  } else {
+    if (want_v) PANEL_FAR(k_panel_fp64, true, m->rec, ); else PANEL_FAR(k_panel_fp64, false, m->rec, );
+  }
 #undef PANEL_FAR
+  launch_panel_close(ctx, m, sigma, to, prec, want_v, P);
   if (slots)
-    *slots = Slots{part, ns};
-  else if (ns > 1)
-    launch_slot_sum(ctx, n_t, 4, Slots{part, ns}, false, acc);
+    *slots = Slots{P.part, P.ns};
+  else if (P.ns > 1)
+    launch_slot_sum(ctx, n_t, 4, Slots{P.part, P.ns}, false, acc);
   OBEM_HIP(ctx, hipGetLastError());
   return OBEM_OK;
 }
@@ -1341,19 +1371,14 @@ __global__ __launch_bounds__(256) void k_tile_mask(int ntile, int wpr, int sym_t
 }
 
 template <bool WANT_V, bool NN, int EXCL>
-__global__ __launch_bounds__(kThreads, 7) void k_pair_mixed(int n_t, const double *__restrict__ xs,
-                                                         const int32_t *__restrict__ perm, int n_s,
-                                                         const double *__restrict__ sx,
-                                                         const double *__restrict__ sy,
-                                                         const double *__restrict__ sz,
-                                                         const double *__restrict__ sq,
-                                                         const int8_t *__restrict__ species,
-                                                         const int8_t *__restrict__ species_s, float soft2,
-                                                         int chunk, double *part, float *nn_d2p,
-                                                         int32_t *nn_ip, const double *__restrict__ tbox,
-                                                         float nn_cut2, const int32_t *__restrict__ self_map,
-                                                         int sym_tiles, double nn_cut2d,
-                                                         const uint32_t *__restrict__ dmask, int dwpr) {
+__device__ __forceinline__ void pair_mixed(int bx, int n_t, const double *__restrict__ xs,
+                                           const int32_t *__restrict__ perm, int n_s, const double *__restrict__ sx,
+                                           const double *__restrict__ sy, const double *__restrict__ sz,
+                                           const double *__restrict__ sq, const int8_t *__restrict__ species,
+                                           const int8_t *__restrict__ species_s, float soft2, int chunk, double *part,
+                                           float *nn_d2p, int32_t *nn_ip, const double *__restrict__ tbox,
+                                           float nn_cut2, const int32_t *__restrict__ self_map, int sym_tiles,
+                                           double nn_cut2d, const uint32_t *__restrict__ dmask, int dwpr) {
   constexpr bool kFar = (EXCL == 0) && !WANT_V;  // expanded far tiles allowed
   __shared__ float4 S[kThreads];
   __shared__ float4 SL[kThreads];
@@ -1366,7 +1391,7 @@ __global__ __launch_bounds__(kThreads, 7) void k_pair_mixed(int n_t, const doubl
   // tile lie in one chunk, so the busy workgroups are spread evenly over the
   // launch instead of coming in one block per chunk
   const int nsplit = (n_s + chunk - 1) / chunk;
-  const int tt = (int)blockIdx.x / nsplit, split = (int)blockIdx.x % nsplit;
+  const int tt = (int)bx / nsplit, split = (int)bx % nsplit;
   const int tid = threadIdx.x;
   const int i0 = tt * kThreads;
   const int i = i0 + tid;
@@ -1551,6 +1576,24 @@ __global__ __launch_bounds__(kThreads, 7) void k_pair_mixed(int n_t, const doubl
       nn_ip[(size_t)split * n_t + i] = bidx;
     }
   }
+}
+
+template <bool WANT_V, bool NN, int EXCL>
+__global__ __launch_bounds__(kThreads, 7) void k_pair_mixed(int n_t, const double *__restrict__ xs,
+                                                            const int32_t *__restrict__ perm, int n_s,
+                                                            const double *__restrict__ sx,
+                                                            const double *__restrict__ sy,
+                                                            const double *__restrict__ sz,
+                                                            const double *__restrict__ sq,
+                                                            const int8_t *__restrict__ species,
+                                                            const int8_t *__restrict__ species_s, float soft2,
+                                                            int chunk, double *part, float *nn_d2p, int32_t *nn_ip,
+                                                            const double *__restrict__ tbox, float nn_cut2,
+                                                            const int32_t *__restrict__ self_map, int sym_tiles,
+                                                            double nn_cut2d, const uint32_t *__restrict__ dmask,
+                                                            int dwpr) {
+  pair_mixed<WANT_V, NN, EXCL>(blockIdx.x, n_t, xs, perm, n_s, sx, sy, sz, sq, species, species_s, soft2, chunk, part, nn_d2p, nn_ip,
+             tbox, nn_cut2, self_map, sym_tiles, nn_cut2d, dmask, dwpr);
 }
 
 // ---------------------------------------------------------------------------
@@ -2029,27 +2072,23 @@ __global__ __launch_bounds__(256) void k_sym_reduce(int n, int sbsz, int ns, int
 }
 
 template <bool WANT_V, bool NN, int EXCL>
-__global__ __launch_bounds__(kThreads) void k_pair_fp64(int n_t, const double *__restrict__ xs,
-                                                        const int32_t *__restrict__ perm, int n_s,
-                                                        const double *__restrict__ sx,
-                                                        const double *__restrict__ sy,
-                                                        const double *__restrict__ sz,
-                                                        const double *__restrict__ sq,
-                                                        const int8_t *__restrict__ species,
-                                                        const int8_t *__restrict__ species_s, double soft2,
-                                                        int chunk, double *part, double *nn_d2p,
-                                                        int32_t *nn_ip, const int32_t *__restrict__ self_map) {
+__device__ __forceinline__ void pair_fp64(int bx, int by, int n_t, const double *__restrict__ xs,
+                                          const int32_t *__restrict__ perm, int n_s, const double *__restrict__ sx,
+                                          const double *__restrict__ sy, const double *__restrict__ sz,
+                                          const double *__restrict__ sq, const int8_t *__restrict__ species,
+                                          const int8_t *__restrict__ species_s, double soft2, int chunk, double *part,
+                                          double *nn_d2p, int32_t *nn_ip, const int32_t *__restrict__ self_map) {
   __shared__ double4 S[kThreads];
   __shared__ int K[kThreads];
   const int tid = threadIdx.x;
-  const int i = blockIdx.x * kThreads + tid;
+  const int i = bx * kThreads + tid;
   const bool active = i < n_t;
   const int ii = active ? i : 0;
   const double x0 = xs[ii], x1 = xs[(size_t)n_t + ii], x2 = xs[2 * (size_t)n_t + ii];
   int want = -2;
   if (NN && active) want = want_key(species[perm[i]]);
   const int self = active ? (self_map ? self_map[perm[i]] : perm[i]) : -1;
-  const int jb = blockIdx.y * chunk;
+  const int jb = by * chunk;
   const int je = min(n_s, jb + chunk);
   double ex = 0.0, ey = 0.0, ez = 0.0, ev = 0.0;
   double best = INFINITY;
@@ -2086,16 +2125,29 @@ __global__ __launch_bounds__(kThreads) void k_pair_fp64(int n_t, const double *_
     }
   }
   if (active) {
-    const size_t o = (size_t)blockIdx.y * 4 * n_t;
+    const size_t o = (size_t)by * 4 * n_t;
     part[o + i] = ex;
     part[o + (size_t)n_t + i] = ey;
     part[o + 2 * (size_t)n_t + i] = ez;
     part[o + 3 * (size_t)n_t + i] = ev;
     if (NN) {
-      nn_d2p[(size_t)blockIdx.y * n_t + i] = best;
-      nn_ip[(size_t)blockIdx.y * n_t + i] = bidx;
+      nn_d2p[(size_t)by * n_t + i] = best;
+      nn_ip[(size_t)by * n_t + i] = bidx;
     }
   }
+}
+
+template <bool WANT_V, bool NN, int EXCL>
+__global__ __launch_bounds__(kThreads) void k_pair_fp64(int n_t, const double *__restrict__ xs,
+                                                        const int32_t *__restrict__ perm, int n_s,
+                                                        const double *__restrict__ sx, const double *__restrict__ sy,
+                                                        const double *__restrict__ sz, const double *__restrict__ sq,
+                                                        const int8_t *__restrict__ species,
+                                                        const int8_t *__restrict__ species_s, double soft2, int chunk,
+                                                        double *part, double *nn_d2p, int32_t *nn_ip,
+                                                        const int32_t *__restrict__ self_map) {
+  pair_fp64<WANT_V, NN, EXCL>(blockIdx.x, blockIdx.y, n_t, xs, perm, n_s, sx, sy, sz, sq, species, species_s, soft2, chunk, part,
+            nn_d2p, nn_ip, self_map);
 }
 
 // Nearest partner over the source chunks: smallest distance, ties to the
@@ -2167,6 +2219,63 @@ static int sym_resident(obem_ctx *ctx, bool nn) {
   return cache;
 }
 
+// Splits of the sources for n_t targets, and where the sums go.
+struct PairPlan {
+  int nsplit, chunk;
+  double *part;
+};
+static obem_status pair_plan(obem_ctx *ctx, int n_t, int n_s, PairPlan *P) {
+  const int bt = nblk(n_t);
+  // about 128k workgroups (64 rounds of the 2048 resident ones), so that the
+  // last workgroups to start are short and the chip drains quickly at the
+  // end; chunks of at least one tile, of two where these fill the chip
+  int nsplit = (kSplitWorkgroups + bt - 1) / bt;
+  nsplit = std::max(1, std::min(nsplit, (n_s + kThreads - 1) / kThreads));
+  if ((int64_t)bt * nsplit > kFewWorkgroups) nsplit = std::max(1, std::min(nsplit, (n_s + 511) / 512));
+  nsplit = std::min(nsplit, max_slots(bt));
+  int chunk = (n_s + nsplit - 1) / nsplit;
+  chunk = (chunk + kThreads - 1) / kThreads * kThreads;
+  nsplit = (n_s + chunk - 1) / chunk;
+  double *part = (double *)ws_get(ctx, WS_PART, sizeof(double) * 4 * (size_t)n_t * nsplit);
+  if (!part) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
+  *P = PairPlan{nsplit, chunk, part};
+  return OBEM_OK;
+}
+
+// soft == 0: drop zero-distance terms (1: the self term and coincident
+// points); soft > 0 with targets = sources: only the potential needs the self
+// term removed (2; its field term is exactly 0).
+static int excluded(double soft, bool tgt_is_src, bool want_v) {
+  if (!(soft > 0.0)) return 1;
+  return tgt_is_src && want_v ? 2 : 0;
+}
+
+// Cells beyond the close zone and charges in one launch: workgroups below nc
+// take a target tile and a range of cells, the others a target tile and a
+// range of charges, each as its own kernel does.
+template <bool FP64, bool WANT_V, int EXCL>
+__global__ __launch_bounds__(kThreads) void k_cells_and_charges(
+    int nc, int bt, int n_t, const double *__restrict__ xs, int N, const double *__restrict__ f,
+    const double *__restrict__ rec, const double *__restrict__ sigma, int cchunk, double *cpart,
+    const int32_t *__restrict__ perm, int n_s, const double *__restrict__ sx, const double *__restrict__ sy,
+    const double *__restrict__ sz, const double *__restrict__ sq, double soft2, int chunk, double *ppart,
+    const double *__restrict__ tbox, float cut2, double cut2d, const int32_t *__restrict__ self_map) {
+  const int b = blockIdx.x, p = b - nc;
+  if (FP64) {
+    if (b < nc)
+      panel_fp64<WANT_V>(b % bt, b / bt, n_t, xs, N, f, rec, sigma, cchunk, cpart);
+    else
+      pair_fp64<WANT_V, false, EXCL>(p % bt, p / bt, n_t, xs, perm, n_s, sx, sy, sz, sq, nullptr, nullptr, soft2,
+                                     chunk, ppart, nullptr, nullptr, self_map);
+  } else {
+    if (b < nc)
+      panel_mixed<WANT_V>(b % bt, b / bt, n_t, xs, N, f, sigma, cchunk, cpart);
+    else
+      pair_mixed<WANT_V, false, EXCL>(p, n_t, xs, perm, n_s, sx, sy, sz, sq, nullptr, nullptr, (float)soft2, chunk,
+                                      ppart, nullptr, nullptr, tbox, cut2, self_map, 0, cut2d, nullptr, 0);
+  }
+}
+
 obem_status launch_pair_field(obem_ctx *ctx, int64_t n_src, const double *sx, const double *sy, const double *sz,
                               const double *sq, const TargetOrder &to, double soft, obem_precision prec,
                               bool tgt_is_src, bool want_v, const int8_t *species, const int8_t *species_s,
@@ -2180,17 +2289,11 @@ obem_status launch_pair_field(obem_ctx *ctx, int64_t n_src, const double *sx, co
   if (once && !(tgt_is_src && n_s == n_t && tbox && pair_once_applies(n_t, prec, soft, want_v)))
     return fail(ctx, OBEM_EINVAL, "pair-once evaluation needs targets = sources in one order");
   const int bt = nblk(n_t);
-  // about 128k workgroups (64 rounds of the 2048 resident ones), so that the
-  // last workgroups to start are short and the chip drains quickly at the
-  // end; chunks of at least one tile, of two where these fill the chip
-  int nsplit = (kSplitWorkgroups + bt - 1) / bt;
-  nsplit = std::max(1, std::min(nsplit, (n_s + kThreads - 1) / kThreads));
-  if ((int64_t)bt * nsplit > kFewWorkgroups) nsplit = std::max(1, std::min(nsplit, (n_s + 511) / 512));
-  nsplit = std::min(nsplit, max_slots(bt));
-  int chunk = (n_s + nsplit - 1) / nsplit;
-  chunk = (chunk + kThreads - 1) / kThreads * kThreads;
-  nsplit = (n_s + chunk - 1) / chunk;
-  double *part = (double *)ws_get(ctx, WS_PART, sizeof(double) * 4 * (size_t)n_t * nsplit);
+  PairPlan P;
+  obem_status pst = pair_plan(ctx, n_t, n_s, &P);
+  if (pst) return pst;
+  const int nsplit = P.nsplit, chunk = P.chunk;
+  double *part = P.part;
   const bool nn = nn_idx != nullptr;
   void *nnd = nullptr;
   int32_t *nni = nullptr;
@@ -2199,15 +2302,7 @@ obem_status launch_pair_field(obem_ctx *ctx, int64_t n_src, const double *sx, co
     nni = (int32_t *)ws_get(ctx, WS_MISC7, sizeof(int32_t) * (size_t)n_t * nsplit);
     if (!nnd || !nni) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
   }
-  if (!part) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
-  // soft == 0: drop zero-distance terms (the self term and coincident
-  // points); soft > 0 with targets = sources: only the potential needs the
-  // self term removed (its field term is exactly 0).
-  int excl = 0;
-  if (!(soft > 0.0))
-    excl = 1;
-  else if (tgt_is_src && want_v)
-    excl = 2;
+  const int excl = excluded(soft, tgt_is_src, want_v);
   dim3 grid(bt, nsplit);
   // cut with a margin for the FP32 box coordinates (a larger cut only costs time)
   const double nn_cut2d = tbox ? std::pow(nn_cut * (1.0 + 1e-4) + 1e-9, 2) : INFINITY;
@@ -2296,6 +2391,59 @@ obem_status launch_pair_field(obem_ctx *ctx, int64_t n_src, const double *sx, co
       if (st) return st;
     }
   }
+  return OBEM_OK;
+}
+
+// Side by side where the two launches together have at most this many
+// workgroups (target tiles x splits): alone, each leaves part of the chip idle
+// or ends with a part of it idle.  Apart -> side by side, calls: 97 points,
+// 4,096 cells and 1,000 charges (68 workgroups) 88 -> 68 us, 4,096 charges
+// between plates in FP64 198 -> 188 us, 20,011 points, 40,776 cells and 200,003
+// charges (10,112) 2.55 -> 2.42 ms; 25,000 workgroups 1 % faster, but 30,000 in
+// FP64 9.5 -> 9.75 ms and 100,000 0.4 % slower (both kernels take the larger
+// register count).
+constexpr int64_t kSideBySide = 12288;
+
+bool side_by_side(const obem_ctx *ctx, int64_t n_t, int64_t N, int64_t n_s) {
+  const int bt = nblk(n_t), slots = max_slots(bt);
+  const int64_t w = std::min<int64_t>(slots, (N + 63) / 64) + std::min<int64_t>(slots, (n_s + kThreads - 1) / kThreads);
+  return !ctx->prof && bt * w <= kSideBySide;  // profiles time the two apart
+}
+
+obem_status launch_cells_and_charges(obem_ctx *ctx, const obem_meshh *m, const double *sigma, const SourceOrder &so,
+                                     const TargetOrder &to, double soft, obem_precision prec, bool tgt_is_src,
+                                     bool want_v, double *acc, Slots *cells, Slots *charges) {
+  const int n_t = to.n, N = (int)m->n, n_s = (int)so.n;
+  PanelPlan C;
+  PairPlan P;
+  obem_status st = panel_plan(ctx, n_t, N, acc, &C);
+  if (!st) st = pair_plan(ctx, n_t, n_s, &P);
+  if (st) return st;
+  const int excl = excluded(soft, tgt_is_src, want_v);
+  // no partner search: the cut of its tiles is that of launch_pair_field at 0
+  const double cut2d = so.tbox ? 1e-18 : INFINITY;
+  const int nc = C.bt * C.ns, np = C.bt * P.nsplit;
+  const double soft2 = prec == OBEM_MIXED ? (double)(float)(soft * soft) : soft * soft;
+#define BOTH(F, V, Z)                                                                                               \
+  if ((prec == OBEM_FP64) == F && want_v == V && excl == Z)                                                         \
+  hipLaunchKernelGGL((k_cells_and_charges<F, V, Z>), dim3(nc + np), dim3(kThreads), 0, ctx->stream, nc, C.bt, n_t,  \
+                     to.xs, N, m->f, m->rec, sigma, C.cchunk, C.part, to.perm, n_s, so.x, so.y, so.z, so.q, soft2,  \
+                     P.chunk, P.part, so.tbox, (float)cut2d, cut2d, tgt_is_src ? so.inv : nullptr)
+  BOTH(false, false, 0);
+  BOTH(false, false, 1);
+  BOTH(false, true, 0);
+  BOTH(false, true, 1);
+  BOTH(false, true, 2);
+  BOTH(true, false, 0);
+  BOTH(true, false, 1);
+  BOTH(true, true, 0);
+  BOTH(true, true, 1);
+  BOTH(true, true, 2);
+#undef BOTH
+  launch_panel_close(ctx, m, sigma, to, prec, want_v, C);
+  *cells = Slots{C.part, C.ns};
+  *charges = Slots{P.part, P.nsplit};
+  OBEM_HIP(ctx, hipGetLastError());
   return OBEM_OK;
 }
 

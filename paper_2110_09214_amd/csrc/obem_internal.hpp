@@ -332,6 +332,13 @@ struct SourceOrder {
   const int32_t *inv = nullptr;
   const int32_t *perm = nullptr;  // ordered position -> caller index
 };
+
+// Both for few targets, the far cells and the charges in one launch, sums left
+// in slots.
+bool side_by_side(const obem_ctx *ctx, int64_t n_t, int64_t N, int64_t n_s);
+obem_status launch_cells_and_charges(obem_ctx *ctx, const obem_meshh *m, const double *sigma, const SourceOrder &so,
+                                     const TargetOrder &to, double soft, obem_precision prec, bool tgt_is_src,
+                                     bool want_v, double *acc, Slots *cells, Slots *charges);
 obem_status order_sources(obem_ctx *ctx, int64_t n, const double *sx, const double *sy, const double *sz,
                           const double *sq, bool want_inv, SourceOrder *out);
 // Both orderings of a field call with separate target order.

@@ -335,3 +335,28 @@ def test_counted_places(ctx, orc, n, kind):
         _, v2 = orc.pair_field(xt, x, s, 1e-6, want_v=True)
         _, V2 = B.field_eval(ctx, None, None, dev(x), dev(s), dev(xt), 1e-6, prec, want_v=True)
         assert (np.abs(host(V2) - v2) / vref).max() <= tol
+
+
+@pytest.mark.parametrize("n", [1, 255, 257])
+@pytest.mark.parametrize("soft", [0.0, 1e-7])
+@pytest.mark.parametrize("same", [False, True])
+def test_cells_and_charges_side_by_side(ctx, orc, n, soft, same):
+    """Cells and charges in one launch: with and without softening, targets =
+    sources or not, with and without the potential, remainders of the target
+    tile, against the oracle (tolerances of the field tests)."""
+    m = W.parallel_plate_mesh(n=7)
+    lo, hi = np.array([m.a.min(0), m.a.max(0)])
+    rng = np.random.default_rng(n)
+    x = lo + (hi - lo) * rng.uniform(0.2, 0.8, size=(n, 3))
+    xs, q = (x, W.E_CHARGE * rng.choice([-1.0, 1.0], size=n)) if same else (
+        lo + (hi - lo) * rng.uniform(0.2, 0.8, size=(300, 3)), W.E_CHARGE * rng.choice([-1.0, 1.0], size=300))
+    sig = 1e-9 * (1.0 + rng.uniform(size=m.n))
+    Er, Vr = orc.panel_field(x, m.a, m.b, m.c, sig, want_v=True)
+    Ep, Vp = orc.pair_field(x, xs, q, soft, tgt_is_src=same, want_v=True)
+    bm = bind(ctx, m)
+    for prec, tol in ((B.OBEM_FP64, 1e-12), (B.OBEM_MIXED, 1e-5)):
+        E, V = B.field_eval(ctx, bm, dev(sig), dev(xs), dev(q), dev(x), soft, prec, tgt_is_src=same, want_v=True)
+        assert rel_l2(host(E), Er + Ep) <= tol
+        assert rel_l2(host(V), Vr + Vp) <= tol
+        E = B.field_eval(ctx, bm, dev(sig), dev(xs), dev(q), dev(x), soft, prec, tgt_is_src=same)
+        assert rel_l2(host(E), Er + Ep) <= tol
