@@ -10,9 +10,9 @@
 // recentred on the first centroid of their 256), the lanes hold charges,
 // gridDim.y chunks of charges with per-chunk partial sums reduced in chunk
 // order.  Precision regimes as in the field: mixed = FP32 7-point rule
-// within 8 diameters, 6-point rule within 40, 3-point rule beyond (far
-// kernel, charges ordered by
-// charge sign, then Hilbert, so the charge comes out of the pair loop), FP64
+// within 6 diameters, 6-point rule within 16, 4-point rule within 40, 3-point
+// rule beyond (far kernel, charges ordered by charge sign, then Hilbert, so the
+// charge comes out of the pair loop), FP64
 // closed form within 3 diameters (near kernel, its own partial slots);
 // FP64 = closed form within 48 diameters, FP64 7-point rule beyond.
 #include <algorithm>
@@ -42,8 +42,8 @@ __device__ __forceinline__ void infl_closed(const double *__restrict__ rec, int 
 // charges in blocks of 1024, 4 per thread (one from each 256-charge tile of
 // the block, so a wave's lanes hold 64 consecutive, spatially close charges).
 // Per cell the rule is chosen per wave over those close charges (7 points
-// within 8 D, 6 within 40 D, 3 beyond; pairs within 3 D are left to the near
-// kernel), and
+// within 6 D, 6 within 16 D, 4 within 40 D, 3 beyond; pairs within 3 D are left
+// to the near kernel), and
 // each thread adds q (IV, IE) of its charges into 8 x 4 FP32 sums.  The sums
 // of a block are reduced over the 256 threads through LDS in fixed order and
 // in FP64 (8 partial sums of 32 threads each, then the 8 in order) and

@@ -27,13 +27,13 @@ constexpr double kKe = 1.0 / (4.0 * kPi * kEps0);
 // Far-field regimes of the cell field (ratio of target distance from the
 // cell centroid to the cell diameter D):
 //   mixed: R < 3 D   -> FP64 closed form
-//          R < 8 D   -> FP32 7-point degree-5 rule
-//          R < 40 D  -> FP32 6-point degree-4 rule
+//          R < 6 D   -> FP32 7-point degree-5 rule
+//          R < 16 D  -> FP32 6-point degree-4 rule
+//          R < 40 D  -> FP32 4-point degree-3 rule
 //          else      -> FP32 3-point degree-2 rule
 //   fp64:  R < 48 D  -> FP64 closed form, else FP64 7-point rule
 constexpr double kNearMixed = 3.0;
 constexpr double kFar3Mixed = 40.0;  // 3-point rule from here on (mixed)
-constexpr double kMid6Mixed = 8.0;   // 6-point rule from here to kFar3Mixed (mixed)
 // Zones of the mixed cell field (forward kernel): the cheapest rule whose
 // truncation error stays below the FP32 rounding floor (about 2e-7): 7
 // points from 3 D, 6 from kFwd6 D, 4 from kFwd4 D, 3 from kFar3Mixed D.
