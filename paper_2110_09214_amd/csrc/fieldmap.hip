@@ -44,8 +44,16 @@ __global__ __launch_bounds__(256) void k_map_pack(int64_t M, const double *__res
 obem_status map_pack(obem_ctx *ctx, int64_t n, MapDev *g) {
   const int64_t M = (int64_t)g->nx * g->ny * g->nz;
   if (n < kPackPoints || n < M / 8) return OBEM_OK;
+  // The plain map needs no workspace: a captured call takes it (it must not
+  // allocate, and its graph may outlive the buffer), and so does a call that
+  // cannot have the buffer.
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return OBEM_OK;
+  }
   double *nodes = (double *)ws_get(ctx, WS_MAPNODES, sizeof(double) * 3 * (size_t)M);
-  if (!nodes) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
+  if (!nodes) return OBEM_OK;
   hipLaunchKernelGGL(k_map_pack, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, ctx->stream, M, g->ex, g->ey, g->ez,
                      nodes);
   OBEM_HIP(ctx, hipGetLastError());
