@@ -38,95 +38,6 @@ __device__ __forceinline__ void neum(float &s, float &c, float v) {
   s = t;
 }
 
-// FP64 closed-form Jacobian of a unit-density cell contracted with w:
-//   gtw = G^T w = sum_e (m_e . w) grad f_e + (n . w) grad Omega
-// and ie_w = w . IE.  P[k] = vertex k minus the target.  With f = log(a / b)
-// (edge_f) and C = 2 L / (a b),
-//   grad f_e = C (Pm/Rm + Pp/Rp),   grad Omega = sum_e (t_e x Pm) C (1/Rm + 1/Rp),
-// sums of terms of one sign in the far range: at 24-48 D the relative error
-// is 4.3e-14 (rms against 128 bits) where differences of reciprocals had
-// 1.2e-12.
-__device__ __forceinline__ void cell_grad_closed(const double *__restrict__ rec, d3 x, d3 w, d3 &gtw, double &ie_w) {
-  CellSeen s = cell_seen(rec, x);
-  const double nw = dot3(s.n, w);
-  ie_w = nw * solid_angle(s.num, s.den);
-  gtw = mk3(0, 0, 0);
-  d3 gO = mk3(0, 0, 0);
-#pragma unroll 1
-  for (int e = 0; e < 3; ++e) {
-    double d[8];
-    load_doubles<8>(rec + CR_EDGE + CR_EDGE_SIZE * e, d);
-    const double L = d[0];
-    const d3 t = mk3(d[1], d[2], d[3]);
-    double b;
-    const double f = edge_f(s.P[0], s.R[0], s.R[1], t, L, &b);
-    const double C = 2.0 * L * rcp_f64((s.R[0] + s.R[1] + L) * b);
-    const double im = rcp_f64(s.R[0]), ip = rcp_f64(s.R[1]);
-    const double mw = dot3(mk3(d[4], d[5], d[6]), w);
-    ie_w = fma(mw, f, ie_w);
-    gtw = gtw + (s.P[0] * im + s.P[1] * ip) * (C * mw);
-    gO = gO + cross3(t, s.P[0]) * (C * (im + ip));
-    rotate3(s);
-  }
-  gtw = gtw + gO * nw;
-}
-
-// The same for x at least kMidForm diameters from the centroid (see
-// cell_mid_form): with t = L / S, C = 2 t / (S (1 - t^2)); two reciprocals
-// for the seven quotients.
-__device__ __forceinline__ void cell_grad_mid(const double *__restrict__ rec, d3 x, d3 w, d3 &gtw, double &ie_w) {
-  double d[14];
-  load_doubles<14>(rec, d);
-  d3 P[3];
-  double R[3], iR[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    P[k] = mk3(d[3 * k], d[3 * k + 1], d[3 * k + 2]) - x;
-    R[k] = sqrt_rcp_f64(dot3(P[k], P[k]), iR[k]);
-  }
-  const d3 n = mk3(d[9], d[10], d[11]);
-  const double num = -d[12] * dot3(P[0], n);
-  const double den = fma(R[0] * R[1], R[2],
-                         fma(dot3(P[0], P[1]), R[2], fma(dot3(P[0], P[2]), R[1], dot3(P[1], P[2]) * R[0])));
-  const double S0 = R[0] + R[1], S1 = R[1] + R[2], S2 = R[2] + R[0];
-  const double p01 = S0 * S1, p23 = S2 * den, r = rcp_f64(p01 * p23);
-  const double r01 = r * p23, r23 = r * p01;
-  auto quot = [](double a, double b, double rb) {
-    const double q = a * rb;
-    return fma(fma(-b, q, a), rb, q);
-  };
-  const double z = quot(num, den, r23 * S2), zz = z * z;
-  const double nw = dot3(n, w);
-  ie_w = nw * (2.0 * fma(z * zz, atan_tail(zz), z));
-  const double S[3] = {S0, S1, S2}, iS[3] = {r01 * S1, r01 * S0, r23 * den};
-  double t[3], o[3];
-  d3 et[3], em[3];
-#pragma unroll
-  for (int e = 0; e < 3; ++e) {
-    double c[8];
-    load_doubles<8>(rec + CR_EDGE + CR_EDGE_SIZE * e, c);
-    t[e] = quot(c[0], S[e], iS[e]);
-    o[e] = fma(-t[e], t[e], 1.0);
-    et[e] = mk3(c[1], c[2], c[3]);
-    em[e] = mk3(c[4], c[5], c[6]);
-  }
-  const double o01 = o[0] * o[1], ro = rcp_f64(o01 * o[2]), rq = ro * o[2];
-  const double io[3] = {rq * o[1], rq * o[0], ro * o01};
-  gtw = mk3(0, 0, 0);
-  d3 gO = mk3(0, 0, 0);
-#pragma unroll
-  for (int e = 0; e < 3; ++e) {
-    const int e1 = (e + 1) % 3;
-    const double t2 = t[e] + t[e], tt = t[e] * t[e];
-    const double C = t2 * iS[e] * io[e];
-    const double mw = dot3(em[e], w);
-    ie_w = fma(mw, fma(t2 * tt, atanh_tail<true>(tt), t2), ie_w);
-    gtw = gtw + (P[e] * iR[e] + P[e1] * iR[e1]) * (C * mw);
-    gO = gO + cross3(et[e], P[e]) * (C * (iR[e] + iR[e1]));
-  }
-  gtw = gtw + gO * nw;
-}
-
 // ---------------------------------------------------------------------------
 // Cell adjoint, mixed precision (regimes as in the forward kernels).  The far
 // kernel takes the pairs beyond 3 D with the FP32 rules (7 points up to 6 D,

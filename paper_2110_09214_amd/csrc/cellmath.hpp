@@ -74,9 +74,13 @@ __device__ __forceinline__ double rsqrt_f64(double x) {
 // a polynomial's constants to vector registers instead (one more instruction
 // per term, and the registers).
 __device__ __forceinline__ double fma_k(double a, double b, double k) {
+#ifdef __HIP_DEVICE_COMPILE__
   double r;
   asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(k));
   return r;
+#else
+  return fma(a, b, k);
+#endif
 }
 // (atanh(s) - s) / s^3 on s^2 = z <= 0.0297 and (WIDE) z <= 0.075, and
 // (atan(t) - t) / t^3 on t^2 = u <= 1/16: minimax polynomials, relative error
@@ -135,36 +139,61 @@ __device__ __forceinline__ double inv_sqrt_f64(double x) {
 // b = S - L,
 //   f = log(a / b),
 // as e ln 2 + 2 atanh(s), s = (a 2^-e - b) / (a 2^-e + b), |s| <= 0.172, the
-// atanh by a degree-15 polynomial: one
-// quotient and one polynomial for every target, where log1p of one of four
-// quotients (by the position of the target's foot) ran up to four times in a
-// wave.  s is formed from S and L, exact in the small difference far from the
-// edge (e = 0: s = L / S).  Close to the edge (b < S / 5) b cancels and comes
-// from the distances to the edge's line instead, with l = t . P and
-// R0 = |t x P|:  b = 2 (R0^2 + lm lp + Rm Rp) / a, where for a foot inside the
-// edge (lm lp < 0) Rm Rp + lm lp = R0^2 (R0^2 + lm^2 + lp^2) / (Rm Rp - lm lp).
-// On the edge itself b = 0 and f is infinite.  b_out: b, for the gradient.
-__device__ __forceinline__ double edge_f(d3 Pm, double Rm, double Rp, d3 t, double L, double *b_out) {
-  const double S = Rm + Rp, a = S + L;
-  double b = S - L;
-  const bool close = b < 0.2 * S;
+// atanh by a degree-15 polynomial: one polynomial for every target, where
+// log1p of one of four quotients (by the position of the target's foot) ran up
+// to four times in a wave.  s is formed from S and L, exact in the small
+// difference far from the edge (e = 0: s = L / S).
+// Close to the edge b cancels, and a / b is 1 + q with the quotient of terms
+// of one sign instead (l = t . P, R0 = |t x P|; the mirrored one where lm + lp
+// < 0):
+//   q = L (S + lm + lp) / (S (Rm + lm))             for lm >= 0,
+//       L (S + lm + lp) (Rm - lm) / (S R0^2)        for a foot inside the edge,
+// s = (q 2^-e - (1 - 2^-e)) / (q 2^-e + (1 + 2^-e)).  Close is L > 0.45 S:
+// there both forms round equally.  (With 0.667 the field's error at 0.3 to 0.7
+// diameters was 10 to 20 % above that of log1p with the quotient everywhere,
+// with 0.45 it is at most that everywhere; 0.4: the gradient 3 % above it.)
+// On the edge itself q and f are infinite.
+// C_out: C = 2 L / (a b), for the gradient, from a b / 2 = Rm Rp + Pm . Pp, or
+// where x sees the edge under more than a right angle (its foot is inside, lm
+// lp < 0), R0^2 (R0^2 + lm^2 + lp^2 + u) / u with u = Rm Rp - lm lp.
+__device__ __forceinline__ double edge_f(d3 Pm, d3 Pp, double Rm, double Rp, d3 t, double L, double *C_out) {
+  const double S = Rm + Rp;
+  const bool close = L > 0.45 * S;
+  double q = 0.0, B = S, ratio = (S + L) * __builtin_amdgcn_rcp(S - L);
+  const double dp = C_out ? dot3(Pm, Pp) : 0.0;
+  double cn = L, cd = fma(Rm, Rp, dp);
   if (close) {
     const d3 c = cross3(t, Pm);
-    const double R2 = dot3(c, c), lm = dot3(t, Pm), lp = lm + L, p = lm * lp, mm = Rm * Rp;
-    double w = mm + p;
-    if (p < 0.0) w = div_f64(R2 * (R2 + fma(lm, lm, lp * lp)), mm - p);
-    b = div_f64(2.0 * (R2 + w), a);
+    const double R2 = dot3(c, c);
+    double lm = dot3(t, Pm), lp = lm + L, r1 = Rm;
+    if (dp < 0.0) {
+      const double u = fma(Rm, Rp, -(lm * lp));
+      cn = L * u;
+      cd = R2 * (R2 + fma(lm, lm, lp * lp) + u);
+    }
+    if (lp + lm < 0.0) {
+      const double l = lm;
+      lm = -lp;
+      lp = -l;
+      r1 = Rp;
+    }
+    const double n = L * (S + (lp + lm));
+    B = S * (lm < 0.0 ? R2 : r1 + lm);
+    q = div_f64(lm < 0.0 ? n * (r1 - lm) : n, B);
+    ratio = 1.0 + q;
   }
+  if (C_out) *C_out = div_f64(cn, cd);
   // e = round(log2(a / b)), from the estimate of the ratio
-  const int e = __builtin_amdgcn_frexp_exp(a * __builtin_amdgcn_rcp(b) * 1.4142135623730951) - 1;
+  const int e = __builtin_amdgcn_frexp_exp(ratio * 1.4142135623730951) - 1;
   const double k = __builtin_amdgcn_ldexp(1.0, -e);
-  const double num = close ? fma(a, k, -b) : fma(-S, 1.0 - k, L * (1.0 + k));
-  const double den = close ? fma(a, k, b) : fma(S, 1.0 + k, -L * (1.0 - k));
+  const double num = close ? fma(q, k, k - 1.0) : fma(-S, 1.0 - k, L * (1.0 + k));
+  const double den = close ? fma(q, k, k + 1.0) : fma(S, 1.0 + k, -L * (1.0 - k));
   const double s = div_f64(num, den), z = s * s;
-  const double s2 = s + s;
-  const double f = fma((double)e, 0.69314718055994530942, fma(s2 * z, atanh_tail<false>(z), s2));
-  if (b_out) *b_out = b;
-  return b == 0.0 ? (double)INFINITY : f;
+  const double s2 = s + s, tail = s2 * z * atanh_tail<false>(z);
+  // e ln 2 in two parts, the first a product without rounding
+  const double h = (double)e * 0x1.62e42fefap-1, f = h + s2;
+  const double r = (h - f) + s2 + fma((double)e, 0x1.cf79abc9e3b39p-40, tail);
+  return B == 0.0 ? (double)INFINITY : f + r;
 }
 
 // Large angles, rare: kept out of line, since the library's constants
@@ -239,9 +268,10 @@ __device__ __forceinline__ void rotate3(CellSeen &s) {
 // the plane gets Omega = 0 (the principal value of the normal field).  Bound
 // by FP64 operations; the edges run in a loop, each loading its own data,
 // since unrolled they take over 200 registers and two waves per SIMD.
-// Against 128-bit arithmetic the relative error of IE is 3.2e-15 (rms) at
-// 1.5-3 D and 4.5e-14 at 24-48 D (3.4e-15 and 5.6e-14 for the log1p form it
-// replaces).
+// Against 128-bit arithmetic the relative error of IE (root mean square of the
+// 99 % smallest) is 6.0e-16 at 0.3-0.45 D, 8.2e-16 at 0.45-0.7 D, 2.4e-15 at
+// 1.5-2.5 D and 4.1e-14 at 24-48 D (6.0e-16, 8.3e-16, 2.7e-15 and 4.8e-14 for
+// log1p and atan2 of quotients without cancellation).
 template <bool WANT_V>
 __device__ __forceinline__ void cell_closed_form(const double *__restrict__ rec, d3 x, d3 &IE, double &IV) {
   CellSeen s = cell_seen(rec, x);
@@ -252,7 +282,7 @@ __device__ __forceinline__ void cell_closed_form(const double *__restrict__ rec,
   for (int e = 0; e < 3; ++e) {
     double d[8];
     load_doubles<8>(rec + CR_EDGE + CR_EDGE_SIZE * e, d);
-    const double f = edge_f(s.P[0], s.R[0], s.R[1], mk3(d[1], d[2], d[3]), d[0], nullptr);
+    const double f = edge_f(s.P[0], s.P[1], s.R[0], s.R[1], mk3(d[1], d[2], d[3]), d[0], nullptr);
     const d3 m = mk3(d[4], d[5], d[6]);
     IE = IE + m * f;
     if (WANT_V) IV = fma(dot3(m, s.P[0]), f, IV);
@@ -290,6 +320,94 @@ __device__ __forceinline__ void cell_mid_form(const double *__restrict__ rec, d3
     IE = IE + m * f;
     if (WANT_V) IV = fma(dot3(m, s.P[e]), f, IV);
   }
+}
+
+// FP64 closed-form Jacobian of a unit-density cell contracted with w:
+//   gtw = G^T w = sum_e (m_e . w) grad f_e + (n . w) grad Omega
+// and ie_w = w . IE.  P[k] = vertex k minus the target.  With f = log(a / b)
+// (edge_f) and C = 2 L / (a b),
+//   grad f_e = C (Pm/Rm + Pp/Rp),   grad Omega = sum_e (t_e x Pm) C (1/Rm + 1/Rp),
+// sums of terms of one sign in the far range: at 24-48 D the relative error
+// against 128 bits is 2.9e-14 where differences of reciprocals had 9.7e-13, at
+// 0.45-0.7 D 6.8e-16 and 9.1e-16.
+__device__ __forceinline__ void cell_grad_closed(const double *__restrict__ rec, d3 x, d3 w, d3 &gtw, double &ie_w) {
+  CellSeen s = cell_seen(rec, x);
+  const double nw = dot3(s.n, w);
+  ie_w = nw * solid_angle(s.num, s.den);
+  gtw = mk3(0, 0, 0);
+  d3 gO = mk3(0, 0, 0);
+#pragma unroll 1
+  for (int e = 0; e < 3; ++e) {
+    double d[8];
+    load_doubles<8>(rec + CR_EDGE + CR_EDGE_SIZE * e, d);
+    const double L = d[0];
+    const d3 t = mk3(d[1], d[2], d[3]);
+    double C;
+    const double f = edge_f(s.P[0], s.P[1], s.R[0], s.R[1], t, L, &C);
+    const double im = rcp_f64(s.R[0]), ip = rcp_f64(s.R[1]);
+    const double mw = dot3(mk3(d[4], d[5], d[6]), w);
+    ie_w = fma(mw, f, ie_w);
+    gtw = gtw + (s.P[0] * im + s.P[1] * ip) * (C * mw);
+    gO = gO + cross3(t, s.P[0]) * (C * (im + ip));
+    rotate3(s);
+  }
+  gtw = gtw + gO * nw;
+}
+
+// The same for x at least kMidForm diameters from the centroid (see
+// cell_mid_form): with t = L / S, C = 2 t / (S (1 - t^2)); two reciprocals
+// for the seven quotients.
+__device__ __forceinline__ void cell_grad_mid(const double *__restrict__ rec, d3 x, d3 w, d3 &gtw, double &ie_w) {
+  double d[14];
+  load_doubles<14>(rec, d);
+  d3 P[3];
+  double R[3], iR[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    P[k] = mk3(d[3 * k], d[3 * k + 1], d[3 * k + 2]) - x;
+    R[k] = sqrt_rcp_f64(dot3(P[k], P[k]), iR[k]);
+  }
+  const d3 n = mk3(d[9], d[10], d[11]);
+  const double num = -d[12] * dot3(P[0], n);
+  const double den = fma(R[0] * R[1], R[2],
+                         fma(dot3(P[0], P[1]), R[2], fma(dot3(P[0], P[2]), R[1], dot3(P[1], P[2]) * R[0])));
+  const double S0 = R[0] + R[1], S1 = R[1] + R[2], S2 = R[2] + R[0];
+  const double p01 = S0 * S1, p23 = S2 * den, r = rcp_f64(p01 * p23);
+  const double r01 = r * p23, r23 = r * p01;
+  auto quot = [](double a, double b, double rb) {
+    const double q = a * rb;
+    return fma(fma(-b, q, a), rb, q);
+  };
+  const double z = quot(num, den, r23 * S2), zz = z * z;
+  const double nw = dot3(n, w);
+  ie_w = nw * (2.0 * fma(z * zz, atan_tail(zz), z));
+  const double S[3] = {S0, S1, S2}, iS[3] = {r01 * S1, r01 * S0, r23 * den};
+  double t[3], o[3];
+  d3 et[3], em[3];
+#pragma unroll
+  for (int e = 0; e < 3; ++e) {
+    double c[8];
+    load_doubles<8>(rec + CR_EDGE + CR_EDGE_SIZE * e, c);
+    t[e] = quot(c[0], S[e], iS[e]);
+    o[e] = fma(-t[e], t[e], 1.0);
+    et[e] = mk3(c[1], c[2], c[3]);
+    em[e] = mk3(c[4], c[5], c[6]);
+  }
+  const double o01 = o[0] * o[1], ro = rcp_f64(o01 * o[2]), rq = ro * o[2];
+  const double io[3] = {rq * o[1], rq * o[0], ro * o01};
+  gtw = mk3(0, 0, 0);
+  d3 gO = mk3(0, 0, 0);
+#pragma unroll
+  for (int e = 0; e < 3; ++e) {
+    const int e1 = (e + 1) % 3;
+    const double t2 = t[e] + t[e], tt = t[e] * t[e];
+    const double C = t2 * iS[e] * io[e];
+    const double mw = dot3(em[e], w);
+    ie_w = fma(mw, fma(t2 * tt, atanh_tail<true>(tt), t2), ie_w);
+    gtw = gtw + (P[e] * iR[e] + P[e1] * iR[e1]) * (C * mw);
+    gO = gO + cross3(et[e], P[e]) * (C * (iR[e] + iR[e1]));
+  }
+  gtw = gtw + gO * nw;
 }
 
 // Symmetric quadrature rules on the triangle, barycentric weights
