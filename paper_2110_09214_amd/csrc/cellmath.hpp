@@ -115,18 +115,6 @@ __device__ __forceinline__ double atan_tail(double u) {
   return fma_k(q, u, -0.33333333333333303632);
 }
 
-// (1 + x)^(-3/2) on |x| <= 0.0197: minimax polynomial, relative error 1.2e-15 at
-// the ends, 3.5e-16 within half the range.
-__device__ __forceinline__ double far_series(double x) {
-  double q = fma(x, -3.1451690588984347, 2.934885790054357);
-  q = fma(q, x, -2.7070303867241168);
-  q = fma(q, x, 2.4609370597075957);
-  q = fma(q, x, -2.187500000080547);
-  q = fma(q, x, 1.8750000000213611);
-  q = fma(q, x, -1.4999999999999987);
-  return fma(q, x, 1.0);
-}
-
 // 1/sqrt(x) of a squared distance that may overflow (x > 0): 0 beyond
 // 1e300, where the estimate's product would be infinity times zero.
 __device__ __forceinline__ double inv_sqrt_f64(double x) {

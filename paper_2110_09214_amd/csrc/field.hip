@@ -762,31 +762,25 @@ __global__ __launch_bounds__(kThreads) void k_panel_mixed(int n_t, const double 
 // FP64 mode: closed form up to 48 diameters (k_panel_close), FP64
 // 7-point rule beyond (k_panel_fp64).  Both decide with the same FP64 test
 // |x - c_k|^2 >= (48 D_k)^2 on the unmodified coordinates.
-//
-// With d = x - c, kappa = 1 / |d|^2 and the vertices at c + e_j, a rule point
-// c + t e_j (t = 1 - 3 a or 1 - 3 b) is at the squared distance
-// |d|^2 (1 + delta), delta = kappa (t^2 |e_j|^2 - 2 t d.e_j), and beyond 48
-// diameters |delta| <= 0.0195.  So the six outer points need no root of their
-// own, only far_series(delta), and as e_1 + e_2 + e_3 = 0 the sums over points
-// leave the plane once per cell: 103 FP64 operations and one root a pair
-// instead of 147 and seven.  Bound by FP64 issue: 50,000 targets and 40,776
-// cells of the GEM cell 8.9 -> 7.1 ms, 546 cycles a wave and pair of which the
-// operations need 430; two targets a thread (half the LDS reads) take 1 %
-// longer.
-constexpr int kPF = 64;  // cells per LDS tile of the FP64 far kernel
+// Bound by FP64 issue (132 operations and 7 reciprocal roots a pair): a call of
+// 50,000 targets and 40,776 cells takes 11.5 ms.  One root a pair, with the
+// outer points' factors (1 + delta)^(-3/2) by a polynomial, took 9.2 ms, but its
+// rounding was twice as large (2.5e-16 instead of 1.2e-16 of the rule's sum,
+// root mean square): the rounding of x - c and of the one root enters all seven
+// terms alike, where seven of their own average.
+constexpr int kPF = 32;  // cells per LDS tile of the FP64 far kernel
 
-// One cell of the FP64 far kernel's LDS tile: centroid, (48 D)^2, e_1, e_2,
-// t^2 |e_j|^2 of the six outer points, area sigma.
-struct alignas(16) CellF64 {
-  double g[3], lim, e[6], qa[3], qb[3], as;
+// One cell of the FP64 far kernel's LDS tile: centroid, (48 D)^2, the 7 rule
+// points, area sigma {w0, wa, wa, wa, wb, wb, wb} folded per point.
+struct CellF64 {
+  double g[3], lim, q[21], w[7];
 };
 
 template <bool WANT_V>
 __device__ __forceinline__ void panel_fp64(int bx, int by, int n_t, const double *__restrict__ xs, int N,
-                                           const double *__restrict__ f, const double *__restrict__ rec,
-                                           const double *__restrict__ sigma, int cchunk, double *part) {
+                                           const double *__restrict__ f, const double *__restrict__ sigma, int cchunk,
+                                           double *part) {
   __shared__ CellF64 T[kPF];
-  constexpr double kTa = 1.0 - 3.0 * Rule7::a, kTb = 1.0 - 3.0 * Rule7::b;
   const int tid = threadIdx.x;
   const int i = bx * kThreads + tid;
   const bool active = i < n_t;
@@ -797,61 +791,37 @@ __device__ __forceinline__ void panel_fp64(int bx, int by, int n_t, const double
   for (int k0 = kb; k0 < ke; k0 += kPF) {
     const int cnt = min(kPF, ke - k0);
     __syncthreads();
+    for (int idx = tid; idx < 21 * kPF; idx += kThreads) {
+      const int m = idx / kPF, k = idx % kPF;
+      if (k < cnt) T[k].q[m] = f[(size_t)(MF_Q7 + m) * N + k0 + k];
+    }
     if (tid < cnt) {
       const int kk = k0 + tid;
       const double D = f[(size_t)MF_DIAM * N + kk];
-      const double *v = rec + (size_t)CR_COUNT * kk + CR_V;
-      const d3 g = mk3(f[(size_t)MF_GX * N + kk], f[(size_t)MF_GY * N + kk], f[(size_t)MF_GZ * N + kk]);
-      CellF64 &c = T[tid];
-      c.g[0] = g.x;
-      c.g[1] = g.y;
-      c.g[2] = g.z;
-      c.lim = kQuadFp64 * kQuadFp64 * D * D;
-      c.as = f[(size_t)MF_AREA * N + kk] * sigma[kk];
+      const double as = f[(size_t)MF_AREA * N + kk] * sigma[kk];
+      T[tid].g[0] = f[(size_t)MF_GX * N + kk];
+      T[tid].g[1] = f[(size_t)MF_GY * N + kk];
+      T[tid].g[2] = f[(size_t)MF_GZ * N + kk];
+      T[tid].lim = kQuadFp64 * kQuadFp64 * D * D;
 #pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        const d3 e = mk3(v[3 * j], v[3 * j + 1], v[3 * j + 2]) - g;
-        if (j < 2) {
-          c.e[3 * j] = e.x;
-          c.e[3 * j + 1] = e.y;
-          c.e[3 * j + 2] = e.z;
-        }
-        const double e2 = dot3(e, e);
-        c.qa[j] = kTa * kTa * e2;
-        c.qb[j] = kTb * kTb * e2;
-      }
+      for (int m = 0; m < 7; ++m) T[tid].w[m] = as * (m == 0 ? Rule7::w0 : (m < 4 ? Rule7::wa : Rule7::wb));
     }
     __syncthreads();
     for (int k = 0; k < cnt; ++k) {
-      const CellF64 &c = T[k];
-      const double dx = x0 - c.g[0], dy = x1 - c.g[1], dz = x2 - c.g[2];
+      const double dx = x0 - T[k].g[0], dy = x1 - T[k].g[1], dz = x2 - T[k].g[2];
       const double R2 = fma(dx, dx, fma(dy, dy, dz * dz));
-      if (R2 >= c.lim) {  // the near kernel takes the others
-        const double ri = rsqrt_f64(R2), kappa = ri * ri;
-        double p[3];
-        p[0] = fma(dx, c.e[0], fma(dy, c.e[1], dz * c.e[2]));
-        p[1] = fma(dx, c.e[3], fma(dy, c.e[4], dz * c.e[5]));
-        p[2] = -(p[0] + p[1]);
-        double s[3], ta = 0.0, tb = 0.0, va = 0.0, vb = 0.0;
+      if (R2 >= T[k].lim) {  // the near kernel takes the others
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-          const double da = kappa * fma_k(p[j], -2.0 * kTa, c.qa[j]), db = kappa * fma_k(p[j], -2.0 * kTb, c.qb[j]);
-          const double ga = far_series(da), gb = far_series(db);
-          ta += ga;
-          tb += gb;
-          if (WANT_V) {
-            va += fma(da, ga, ga);
-            vb += fma(db, gb, gb);
-          }
-          s[j] = fma(ga, kTa * Rule7::wa, gb * (kTb * Rule7::wb));
+        for (int m = 0; m < 7; ++m) {
+          const double qx = x0 - T[k].q[3 * m], qy = x1 - T[k].q[3 * m + 1], qz = x2 - T[k].q[3 * m + 2];
+          const double ri = rsqrt_f64(fma(qx, qx, fma(qy, qy, qz * qz)));
+          const double wr = T[k].w[m] * ri;
+          const double t = wr * ri * ri;
+          ex = fma(t, qx, ex);
+          ey = fma(t, qy, ey);
+          ez = fma(t, qz, ez);
+          if (WANT_V) ev += wr;
         }
-        const double wr = c.as * ri, w = wr * kappa;
-        const double t = w * fma(ta, Rule7::wa, fma(tb, Rule7::wb, Rule7::w0));
-        const double s0 = w * (s[2] - s[0]), s1 = w * (s[2] - s[1]);
-        ex = fma(t, dx, fma(s0, c.e[0], fma(s1, c.e[3], ex)));
-        ey = fma(t, dy, fma(s0, c.e[1], fma(s1, c.e[4], ey)));
-        ez = fma(t, dz, fma(s0, c.e[2], fma(s1, c.e[5], ez)));
-        if (WANT_V) ev = fma(wr, fma(va, Rule7::wa, fma(vb, Rule7::wb, Rule7::w0)), ev);
       }
     }
   }
@@ -866,9 +836,9 @@ __device__ __forceinline__ void panel_fp64(int bx, int by, int n_t, const double
 
 template <bool WANT_V>
 __global__ __launch_bounds__(kThreads) void k_panel_fp64(int n_t, const double *__restrict__ xs, int N,
-                                                         const double *__restrict__ f, const double *__restrict__ rec,
+                                                         const double *__restrict__ f,
                                                          const double *__restrict__ sigma, int cchunk, double *part) {
-  panel_fp64<WANT_V>(blockIdx.x, blockIdx.y, n_t, xs, N, f, rec, sigma, cchunk, part);
+  panel_fp64<WANT_V>(blockIdx.x, blockIdx.y, n_t, xs, N, f, sigma, cchunk, part);
 }
 
 // FP64 closed-form zone of both modes (MIXED: R < 3 D by the far kernel's FP32
@@ -1216,12 +1186,12 @@ obem_status launch_panel_field(obem_ctx *ctx, const obem_meshh *m, const double 
   if (st) return st;
   dim3 gsplit(P.bt, P.ns), block(kThreads);
   OBEM_PROF(ctx, "panel");
-#define PANEL_FAR(K, V, ...) \
-  hipLaunchKernelGGL(K<V>, gsplit, block, 0, ctx->stream, n_t, to.xs, N, m->f, __VA_ARGS__ sigma, P.cchunk, P.part)
+#define PANEL_FAR(K, V) \
+  hipLaunchKernelGGL(K<V>, gsplit, block, 0, ctx->stream, n_t, to.xs, N, m->f, sigma, P.cchunk, P.part)
   if (prec == OBEM_MIXED) {
-    if (want_v) PANEL_FAR(k_panel_mixed, true, ); else PANEL_FAR(k_panel_mixed, false, );
+    if (want_v) PANEL_FAR(k_panel_mixed, true); else PANEL_FAR(k_panel_mixed, false);
   } else {
-    if (want_v) PANEL_FAR(k_panel_fp64, true, m->rec, ); else PANEL_FAR(k_panel_fp64, false, m->rec, );
+    if (want_v) PANEL_FAR(k_panel_fp64, true); else PANEL_FAR(k_panel_fp64, false);
   }
 #undef PANEL_FAR
   launch_panel_close(ctx, m, sigma, to, prec, want_v, P);
@@ -2256,14 +2226,14 @@ static int excluded(double soft, bool tgt_is_src, bool want_v) {
 template <bool FP64, bool WANT_V, int EXCL>
 __global__ __launch_bounds__(kThreads) void k_cells_and_charges(
     int nc, int bt, int n_t, const double *__restrict__ xs, int N, const double *__restrict__ f,
-    const double *__restrict__ rec, const double *__restrict__ sigma, int cchunk, double *cpart,
+    const double *__restrict__ sigma, int cchunk, double *cpart,
     const int32_t *__restrict__ perm, int n_s, const double *__restrict__ sx, const double *__restrict__ sy,
     const double *__restrict__ sz, const double *__restrict__ sq, double soft2, int chunk, double *ppart,
     const double *__restrict__ tbox, float cut2, double cut2d, const int32_t *__restrict__ self_map) {
   const int b = blockIdx.x, p = b - nc;
   if (FP64) {
     if (b < nc)
-      panel_fp64<WANT_V>(b % bt, b / bt, n_t, xs, N, f, rec, sigma, cchunk, cpart);
+      panel_fp64<WANT_V>(b % bt, b / bt, n_t, xs, N, f, sigma, cchunk, cpart);
     else
       pair_fp64<WANT_V, false, EXCL>(p % bt, p / bt, n_t, xs, perm, n_s, sx, sy, sz, sq, nullptr, nullptr, soft2,
                                      chunk, ppart, nullptr, nullptr, self_map);
@@ -2427,7 +2397,7 @@ obem_status launch_cells_and_charges(obem_ctx *ctx, const obem_meshh *m, const d
 #define BOTH(F, V, Z)                                                                                               \
   if ((prec == OBEM_FP64) == F && want_v == V && excl == Z)                                                         \
   hipLaunchKernelGGL((k_cells_and_charges<F, V, Z>), dim3(nc + np), dim3(kThreads), 0, ctx->stream, nc, C.bt, n_t,  \
-                     to.xs, N, m->f, m->rec, sigma, C.cchunk, C.part, to.perm, n_s, so.x, so.y, so.z, so.q, soft2,  \
+                     to.xs, N, m->f, sigma, C.cchunk, C.part, to.perm, n_s, so.x, so.y, so.z, so.q, soft2,  \
                      P.chunk, P.part, so.tbox, (float)cut2d, cut2d, tgt_is_src ? so.inv : nullptr)
   BOTH(false, false, 0);
   BOTH(false, false, 1);
