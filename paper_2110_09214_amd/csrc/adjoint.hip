@@ -624,7 +624,7 @@ __global__ __launch_bounds__(kT) void k_panel_bwd_fp64(int n_t, const double *__
             const double ex = x.x - f[(size_t)(MF_Q7 + 3 * q) * N + kk];
             const double ey = x.y - f[(size_t)(MF_Q7 + 3 * q + 1) * N + kk];
             const double ez = x.z - f[(size_t)(MF_Q7 + 3 * q + 2) * N + kk];
-            const double ri = rsqrt_f64(fma(ex, ex, fma(ey, ey, ez * ez)));
+            const double ri = inv_sqrt_f64(fma(ex, ex, fma(ey, ey, ez * ez)));
             const double ri2 = ri * ri;
             const double a3 = aw * ri * ri2;
             const double dw = ex * w.x + ey * w.y + ez * w.z;

@@ -66,7 +66,7 @@ __global__ __launch_bounds__(256) void k_bem_assemble(int N, const double *__res
           const double qx = x0 - f[(size_t)(MF_Q7 + 3 * q) * N + j];
           const double qy = x1 - f[(size_t)(MF_Q7 + 3 * q + 1) * N + j];
           const double qz = x2 - f[(size_t)(MF_Q7 + 3 * q + 2) * N + j];
-          const double ri = rsqrt_f64(fma(qx, qx, fma(qy, qy, qz * qz)));
+          const double ri = inv_sqrt_f64(fma(qx, qx, fma(qy, qy, qz * qz)));
           const double wr = w * ri;
           iv += wr;
           const double s = wr * ri * ri;

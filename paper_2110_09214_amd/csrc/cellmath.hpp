@@ -115,11 +115,11 @@ __device__ __forceinline__ double atan_tail(double u) {
   return fma_k(q, u, -0.33333333333333303632);
 }
 
-// 1/sqrt(x) of a squared distance that may overflow (x > 0): 0 beyond
-// 1e300, where the estimate's product would be infinity times zero.
+// 1/sqrt(x) of a squared distance that may overflow (x > 0): 0 for an infinite
+// one, where the estimate's product would be infinity times zero.
 __device__ __forceinline__ double inv_sqrt_f64(double x) {
   const double r = rsqrt_f64(x);
-  return x > 1e300 ? 0.0 : r;
+  return x == (double)INFINITY ? 0.0 : r;
 }
 
 // Line integral of 1/|x - r'| along an edge of length L whose endpoints, seen

@@ -496,7 +496,7 @@ __global__ __launch_bounds__(kTI) void k_influence_fp64(int N, const double *__r
               const double w = qa * ((m == 0) ? Rule7::w0 : (m < 4 ? Rule7::wa : Rule7::wb));
               const double ax = p.x - f[(size_t)(MF_Q7 + 3 * m) * N + kk], ay = p.y - f[(size_t)(MF_Q7 + 3 * m + 1) * N + kk],
                            az = p.z - f[(size_t)(MF_Q7 + 3 * m + 2) * N + kk];
-              const double ri = rsqrt_f64(fma(ax, ax, fma(ay, ay, az * az)));
+              const double ri = inv_sqrt_f64(fma(ax, ax, fma(ay, ay, az * az)));
               const double wr = w * ri;
               const double s = wr * ri * ri;
               acc[c][0] += wr;

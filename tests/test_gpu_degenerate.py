@@ -88,3 +88,27 @@ def test_track_step_without_particles(ctx, orc):
     rhs[dd] += W.E_CHARGE * np.array([5, -2, 7]) / area[dd]
     sig_o, _ = orc.bem_solve(m, rhs)
     assert np.abs(host(sig) - sig_o).max() <= 1e-10 * np.abs(sig_o).max()
+
+
+def test_fp64_at_distances_whose_square_overflows(ctx, orc):
+    """FP64: a charge 1e160 m away adds nothing to the influence, a target there
+    nothing to the adjoint of the others (the squared distance is infinite, its
+    inverse root 0), and the potential at 1e152 m, whose square is still finite,
+    is k q / r."""
+    m = W.parallel_plate_mesh(n=4)
+    bm = bind(ctx, m)
+    x, q = W.parallel_plate_electrons(70, seed=1)
+    far, qf = np.append(x, [[1e160, 0.0, 0.0]], 0), np.append(q, q[:1])
+    ref = orc.influence(m, m.rhs, x, q)[0]
+    out = host(B.bem_influence(ctx, bm, dev(m.rhs), dev(far), dev(qf), B.OBEM_FP64))
+    assert np.abs(out - ref).max() <= 1e-11 * np.abs(ref - m.rhs).max() + 4e-16 * np.abs(m.rhs).max()
+    rng = np.random.default_rng(1)
+    sig, w = 1e-6 * rng.normal(size=m.n), rng.normal(size=(71, 3))
+    gs, gx, _ = B.field_eval_backward(ctx, bm, dev(sig), None, None, dev(x), 0.0, dev(w[:70]), B.OBEM_FP64)
+    gs2, gx2, _ = B.field_eval_backward(ctx, bm, dev(sig), None, None, dev(far), 0.0, dev(w), B.OBEM_FP64)
+    assert rel_l2(host(gs2), host(gs)) <= 1e-13
+    assert rel_l2(host(gx2)[:70], host(gx)) <= 1e-13 and not host(gx2)[70].any()
+    p = np.array([[1e152, 0.0, 0.0], [0.0, 3e150, 1e153]])
+    _, V = B.field_eval(ctx, None, None, dev(x), dev(q), dev(p), 0.0, B.OBEM_FP64, want_v=True)
+    v = B.obem_constants()["k_e"] * q.sum() / np.linalg.norm(p / 1e152, axis=1) / 1e152
+    assert np.abs(host(V) / v - 1.0).max() <= 1e-14
