@@ -255,11 +255,15 @@ def bem_solve_charges_adjoint(ctx: Context, mesh: BoundMesh, g_sigma, g_rhs=None
 
 
 def _soa(x):
-    """The three coordinate arrays of x (n, 3): rows of one transposed copy
-    (one launch; a copy per coordinate is three).  97 probe points near 1,000
-    charges: 166 -> 156 us, 1,000,000 points of a map 254 -> 223 us."""
+    """The three coordinate arrays of x (n, 3): columns that are contiguous
+    (slices of a structure of arrays) as they are, others as the rows of one
+    transposed copy (one launch; a copy per coordinate is three).  97 probe
+    points near 1,000 charges: 166 -> 156 us, 1,000,000 points of a map 254 ->
+    223 us."""
     if x.shape[1] < 3:
         raise IndexError(f"points need 3 coordinates, got {x.shape[1]}")
+    if x.stride(0) == 1 or x.shape[0] <= 1:
+        return [x[:, k].contiguous() for k in range(3)]
     return list(x[:, :3].transpose(0, 1).contiguous())
 
 
