@@ -1135,6 +1135,14 @@ extern "C" obem_status track_step(obem_ctx *ctx, obem_meshh *mesh, obem_particle
   obem_status st;
   const int n = (int)S->n_live;
   obem_step_stats out = {};
+  // pinned words of the totals: before anything of the state has changed
+  if (n > 0 && !ctx->host_words &&
+      hipHostMalloc((void **)&ctx->host_words, sizeof(unsigned long long) * (NCNT + 1), hipHostMallocDefault) !=
+          hipSuccess) {
+    (void)hipGetLastError();
+    ctx->host_words = nullptr;
+    return fail(ctx, OBEM_ENOMEM, "pinned allocation failed");
+  }
   // 1. charging-up right-hand side and re-solve
   if (mesh && p->resolve) {
     const int N = (int)mesh->n;
@@ -1350,13 +1358,6 @@ static obem_status compact_step(obem_ctx *ctx, obem_particles *S, int n, int mi,
                                 const int8_t *status, const int32_t *nchild, const double *child, uint64_t *kk,
                                 const unsigned long long *cnt_dev, obem_step_stats out, obem_step_stats *stats) {
   const size_t nz = (size_t)n;
-  if (!ctx->host_words &&
-      hipHostMalloc((void **)&ctx->host_words, sizeof(unsigned long long) * (NCNT + 1), hipHostMallocDefault) !=
-          hipSuccess) {
-    (void)hipGetLastError();
-    ctx->host_words = nullptr;
-    return fail(ctx, OBEM_ENOMEM, "pinned allocation failed");
-  }
   hipLaunchKernelGGL(k_keep, dim3(nbt(n)), dim3(256), 0, ctx->stream, n, dead, status, nchild, kk);
   uint64_t *pos = (uint64_t *)ws_get(ctx, WS_KEYS0, sizeof(uint64_t) * nz);
   if (!pos) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
