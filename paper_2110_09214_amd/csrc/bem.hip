@@ -379,6 +379,92 @@ static obem_status residual(obem_ctx *ctx, const obem_meshh *m, const double *x,
   return OBEM_OK;
 }
 
+// The vector u_i = 1 + frac(i g), g the golden ratio's fraction: no wrong row or
+// column of an inverse leaves it as it is.
+__device__ __forceinline__ double probe_value(int i) {
+  const double t = 0.6180339887498949 * (double)i;
+  return 1.0 + (t - floor(t));
+}
+__global__ __launch_bounds__(256) void k_probe(int N, double *u) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < N) u[i] = probe_value(i);
+}
+// Largest |x_i - u_i| (infinite where x is not a number); one workgroup.
+__global__ __launch_bounds__(256) void k_probe_error(int N, const double *__restrict__ x, double *out) {
+  __shared__ double s[256];
+  double m = 0.0;
+  for (int i = threadIdx.x; i < N; i += 256) {
+    const double d = fabs(x[i] - probe_value(i));
+    m = d == d ? fmax(m, d) : (double)INFINITY;
+  }
+  s[threadIdx.x] = m;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if (threadIdx.x < w) s[threadIdx.x] = fmax(s[threadIdx.x], s[threadIdx.x + w]);
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) out[0] = s[0];
+}
+
+// out = B in (added to out when add) for one of the mesh's matrices.
+static obem_status matrix_apply(obem_ctx *ctx, int N, const double *B, const double *in, double *out, bool add) {
+  const int nch = n_chunks(N);
+  const int chunk = (N + nch - 1) / nch;
+  double *hi = (double *)ws_get(ctx, WS_SOLVE1, sizeof(double) * (size_t)nch * N);
+  if (!hi) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
+  hipLaunchKernelGGL(k_rows_chunk<2>, dim3(nb(N), nch), dim3(256), 0, ctx->stream, N, B, in, chunk, hi, nullptr);
+  hipLaunchKernelGGL(k_rows_final, dim3(nfin(N)), dim3(kFin), 0, ctx->stream, N, nch, hi, add ? 1 : 0, out);
+  OBEM_HIP(ctx, hipGetLastError());
+  return OBEM_OK;
+}
+
+// Largest error of inverse times (A u) against u.
+static obem_status inverse_error(obem_ctx *ctx, obem_meshh *m, double *err) {
+  const int N = (int)m->n;
+  double *w = (double *)ws_get(ctx, WS_MISC5, sizeof(double) * (2 * (size_t)N + 1));
+  if (!w) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
+  hipLaunchKernelGGL(k_probe, dim3(nb(N)), dim3(256), 0, ctx->stream, N, w);
+  obem_status st = matrix_apply(ctx, N, m->A, w, w + N, false);
+  if (!st) st = matrix_apply(ctx, N, m->LU, w + N, w, false);
+  if (st) return st;
+  hipLaunchKernelGGL(k_probe_error, dim3(1), dim3(256), 0, ctx->stream, N, w, w + 2 * (size_t)N);
+  OBEM_HIP(ctx, hipGetLastError());
+  OBEM_HIP(ctx, hipMemcpyAsync(err, w + 2 * (size_t)N, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+  OBEM_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  return OBEM_OK;
+}
+
+// The inverse from LU factors of A in m->LU: solves L U X = P I into a third
+// buffer, then keeps X and releases the factors.
+static obem_status inverse_by_solve(obem_ctx *ctx, obem_meshh *m, rocblas_handle h) {
+  const int N = (int)m->n;
+  double *X = nullptr;
+  if (hipMalloc(&X, sizeof(double) * (size_t)N * N) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(ctx, OBEM_ENOMEM, "cannot allocate the %d x %d inverse", N, N);
+  }
+  hipLaunchKernelGGL(k_identity, dim3(nb(N), std::min(N, 65535)), dim3(256), 0, ctx->stream, N, X);
+  rocblas_status rs;
+  {
+    OBEM_PROF(ctx, "lu");
+    rs = large_matrix(N) ? rocsolver_dgetrs_64(h, rocblas_operation_none, N, N, m->LU, N, m->ipiv64, X, N)
+                         : rocsolver_dgetrs(h, rocblas_operation_none, N, N, m->LU, N, m->ipiv, X, N);
+  }
+  const hipError_t e = hipStreamSynchronize(ctx->stream);
+  if (rs != rocblas_status_success || e != hipSuccess) {
+    (void)hipFree(X);
+    OBEM_HIP(ctx, e);
+    return fail(ctx, OBEM_EDEVICE, "rocsolver_dgetrs failed");
+  }
+  (void)hipFree(m->LU);
+  m->LU = X;
+  return OBEM_OK;
+}
+
+// An inverse is made again from the factors if its error (inverse_error, about
+// the condition's share of 1e-16 for a right one) is above this.
+constexpr double kInverseError = 1e-6;
+
 obem_status bem_factor(obem_ctx *ctx, obem_meshh *m) {
   if (m->factored) return OBEM_OK;
   const int N = (int)m->n;
@@ -454,26 +540,9 @@ obem_status bem_factor(obem_ctx *ctx, obem_meshh *m) {
   // inverse to re-solve cheaply whenever voltages or free charges change):
   // every later solve is one bandwidth-bound matrix-vector product, refined
   // against the stored A.
-  if (large) {
-    // no 64-bit in-place inverse: solve L U X = P I into a third buffer,
-    // then keep X and release the factors
-    double *X = nullptr;
-    if (hipMalloc(&X, bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      return fail(ctx, OBEM_ENOMEM, "cannot allocate the %d x %d inverse", N, N);
-    }
-    hipLaunchKernelGGL(k_identity, dim3(nb(N), std::min(N, 65535)), dim3(256), 0, ctx->stream, N, X);
-    OBEM_HIP(ctx, hipGetLastError());
-    {
-      OBEM_PROF(ctx, "lu");
-      if (rocsolver_dgetrs_64(h, rocblas_operation_none, N, N, m->LU, N, m->ipiv64, X, N) != rocblas_status_success) {
-        (void)hipFree(X);
-        return fail(ctx, OBEM_EDEVICE, "rocsolver_dgetrs failed");
-      }
-    }
-    OBEM_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    (void)hipFree(m->LU);
-    m->LU = X;
+  if (large) {  // no 64-bit in-place inverse
+    st = inverse_by_solve(ctx, m, h);
+    if (st) return st;
   } else {
     {
       OBEM_PROF(ctx, "lu");
@@ -484,6 +553,19 @@ obem_status bem_factor(obem_ctx *ctx, obem_meshh *m) {
     OBEM_HIP(ctx, hipMemcpyAsync(&i32, m->info, sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream));
     OBEM_HIP(ctx, hipStreamSynchronize(ctx->stream));
     if (i32 != 0) return fail(ctx, OBEM_ESINGULAR, "inversion failed at U(%d,%d)", i32, i32);
+    // the library's in-place inverse is wrong at some sizes (255 and 511
+    // cells of well-conditioned plates); the factors are right
+    double err = 0.0;
+    st = inverse_error(ctx, m, &err);
+    if (st) return st;
+    if (!(err <= kInverseError)) {
+      OBEM_HIP(ctx, hipMemcpyAsync(m->LU, m->A, bytes, hipMemcpyDeviceToDevice, ctx->stream));
+      OBEM_PROF(ctx, "lu");
+      if (rocsolver_dgetrf(h, N, N, m->LU, N, m->ipiv, m->info) != rocblas_status_success)
+        return fail(ctx, OBEM_EDEVICE, "rocsolver_dgetrf failed");
+      st = inverse_by_solve(ctx, m, h);
+      if (st) return st;
+    }
   }
   m->factored = true;
   return OBEM_OK;
@@ -494,16 +576,7 @@ obem_status bem_factor(obem_ctx *ctx, obem_meshh *m) {
 // transposed one the library's.
 static obem_status inv_apply(obem_ctx *ctx, obem_meshh *m, const double *in, double *out, bool trans, bool add) {
   const int N = (int)m->n;
-  if (!trans) {
-    const int nch = n_chunks(N);
-    const int chunk = (N + nch - 1) / nch;
-    double *hi = (double *)ws_get(ctx, WS_SOLVE1, sizeof(double) * (size_t)nch * N);
-    if (!hi) return fail(ctx, OBEM_ENOMEM, "workspace allocation failed");
-    hipLaunchKernelGGL(k_rows_chunk<2>, dim3(nb(N), nch), dim3(256), 0, ctx->stream, N, m->LU, in, chunk, hi, nullptr);
-    hipLaunchKernelGGL(k_rows_final, dim3(nfin(N)), dim3(kFin), 0, ctx->stream, N, nch, hi, add ? 1 : 0, out);
-    OBEM_HIP(ctx, hipGetLastError());
-    return OBEM_OK;
-  }
+  if (!trans) return matrix_apply(ctx, N, m->LU, in, out, add);
   rocblas_handle h;
   obem_status st = handle(ctx, &h);
   if (st) return st;
