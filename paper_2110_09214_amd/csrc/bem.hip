@@ -1,6 +1,7 @@
 // Collocation system of eq. (matrixBEM) on the GPU: FP64 assembly from the
 // analytic cell integrals, LU with partial pivoting (rocSOLVER getrf), the
-// inverse formed from the factors (getri), and solves as one matrix-vector
+// inverse formed from the factors (getri, checked against A; getrs where that
+// is wrong or the matrix needs 64-bit indices), and solves as one matrix-vector
 // product followed by iterative refinement driven by a compensated FP64
 // residual against the stored A.
 //
@@ -96,9 +97,9 @@ __device__ __forceinline__ void two_sum(double a, double b, double &s, double &e
 // j = jb + kCols k + u keep that many loads of a thread in flight (a wave
 // reads 512 contiguous bytes of each column), combined in fixed order at the
 // end; about kRowsWorkgroups workgroups, all resident at once, cover the HBM
-// latency also for matrices of few rows.  At 7,464 cells (445 MB) a product
-// takes 78 us (5.8 TB/s); the library gemv, whose grid is one workgroup per 64
-// rows, took 418 us (1.07 TB/s).
+// latency also for matrices of few rows.  At 7,568 cells (458 MB) a product
+// takes 78 us (5.9 TB/s); the library gemv, whose grid is one workgroup per 64
+// rows, took 422 us (1.09 TB/s).
 constexpr int kCols = 8;
 constexpr int kRowsWorkgroups = 1024;
 

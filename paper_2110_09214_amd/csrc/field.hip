@@ -2003,7 +2003,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_pair_sym_split(int n, const dou
 // Whether a launch of ns dcnt items takes the cut form: an item in parts adds
 // 2.6 us to the launch, a launch of whole items takes about 600 us up to a
 // quarter of the resident workgroups, so the line lies at 7/32 of them (224
-// of 1024).  Whole calls with 7,464 cells: 5,001 charges 880 -> 360 us, 20,001
+// of 1024).  Whole calls with 7,568 cells: 5,001 charges 880 -> 360 us, 20,001
 // 1237 -> 810 us, 40,001 (200 items) 1643 -> 1549 us; at 47,001 (253 items) the
 // parts took 1821 us against 1790.
 static bool sym_in_parts(int ns, int dcnt, int resident) { return (int64_t)ns * dcnt <= (int64_t)resident * 7 / 32; }
@@ -2368,10 +2368,11 @@ obem_status launch_pair_field(obem_ctx *ctx, int64_t n_src, const double *sx, co
 // workgroups (target tiles x splits): alone, each leaves part of the chip idle
 // or ends with a part of it idle.  Apart -> side by side, calls: 97 points,
 // 4,096 cells and 1,000 charges (68 workgroups) 88 -> 68 us, 4,096 charges
-// between plates in FP64 198 -> 188 us, 20,011 points, 40,776 cells and 200,003
-// charges (10,112) 2.55 -> 2.42 ms; 25,000 workgroups 1 % faster, but 30,000 in
-// FP64 9.5 -> 9.75 ms and 100,000 0.4 % slower (both kernels take the larger
-// register count).
+// between plates in FP64 209 -> 200 us, 20,011 points, 40,776 cells and 200,003
+// charges (10,112) 2.55 -> 2.42 ms.  Beyond the line mixed precision gains 1 % at
+// 25,000 workgroups and loses 0.4 % at 100,000 (both kernels take the larger
+// register count); FP64, 16,384 charges, gains 4 % on both sides of it (20,000
+// points 5.50 -> 5.28 ms, 30,000 7.95 -> 7.67) and 2 % at 30,000 workgroups.
 constexpr int64_t kSideBySide = 12288;
 
 bool side_by_side(const obem_ctx *ctx, int64_t n_t, int64_t N, int64_t n_s) {

@@ -43,11 +43,12 @@ __device__ __forceinline__ void infl_closed(const double *__restrict__ rec, int 
 // the block, so a wave's lanes hold 64 consecutive, spatially close charges).
 // Per cell the rule is chosen per wave over those close charges (7 points
 // within 6 D, 6 within 16 D, 4 within 40 D, 3 beyond; pairs within 3 D are left
-// to the near kernel), and
-// each thread adds q (IV, IE) of its charges into 8 x 4 FP32 sums.  The sums
-// of a block are reduced over the 256 threads through LDS in fixed order and
-// in FP64 (8 partial sums of 32 threads each, then the 8 in order) and
-// accumulated in FP64 by 32 threads, one per (cell, component).
+// to the near kernel), and each thread sums q (IV, IE) of its 4 charges in FP32.
+// The order of additions after that, which fixes the result's bits: every four
+// cells a wave writes its lanes' sums to 16 rows of LDS (cell, component); lane
+// l adds 16 lanes' entries of row l / 4, from 16 (l mod 4) on, in FP64 to its
+// sum over the blocks; at the end the four lanes of a row are added pairwise
+// (shuffles by 1 and 2) and the four waves in order through LDS.
 constexpr int kCB = 8;   // cells per workgroup
 constexpr int kCS = 4;   // charges per thread and block
 constexpr int kUP = 64 + 4;  // row pitch of a wave's sums (floats)
