@@ -762,12 +762,13 @@ __global__ __launch_bounds__(kThreads) void k_panel_mixed(int n_t, const double 
 // FP64 mode: closed form up to 48 diameters (k_panel_close), FP64
 // 7-point rule beyond (k_panel_fp64).  Both decide with the same FP64 test
 // |x - c_k|^2 >= (48 D_k)^2 on the unmodified coordinates.
-// Bound by FP64 issue (132 operations and 7 reciprocal roots a pair): a call of
-// 50,000 targets and 40,776 cells takes 11.5 ms.  One root a pair, with the
-// outer points' factors (1 + delta)^(-3/2) by a polynomial, took 9.2 ms, but its
-// rounding was twice as large (2.5e-16 instead of 1.2e-16 of the rule's sum,
-// root mean square): the rounding of x - c and of the one root enters all seven
-// terms alike, where seven of their own average.
+// Bound by FP64 issue (132 operations and 7 reciprocal roots a pair): 50,000
+// targets and 40,776 cells of the GEM cell take 9.2 ms, with two Newton steps a
+// root 10.5.  One root a pair, with the outer points' factors
+// (1 + delta)^(-3/2) by a polynomial, took 7.1 ms, but its rounding was twice as
+// large (2.5e-16 instead of 1.2e-16 of the rule's sum, root mean square): the
+// rounding of x - c and of the one root enters all seven terms alike, where
+// seven of their own average.
 constexpr int kPF = 32;  // cells per LDS tile of the FP64 far kernel
 
 // One cell of the FP64 far kernel's LDS tile: centroid, (48 D)^2, the 7 rule
