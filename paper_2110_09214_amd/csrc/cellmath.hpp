@@ -137,9 +137,10 @@ __device__ __forceinline__ double inv_sqrt_f64(double x) {
 //   q = L (S + lm + lp) / (S (Rm + lm))             for lm >= 0,
 //       L (S + lm + lp) (Rm - lm) / (S R0^2)        for a foot inside the edge,
 // s = (q 2^-e - (1 - 2^-e)) / (q 2^-e + (1 + 2^-e)).  Close is L > 0.45 S:
-// there both forms round equally.  (With 0.667 the field's error at 0.3 to 0.7
-// diameters was 10 to 20 % above that of log1p with the quotient everywhere,
-// with 0.45 it is at most that everywhere; 0.4: the gradient 3 % above it.)
+// there both forms round equally.  (With 0.667 and b from the edge's distance the
+// field's error at 0.1 to 0.7 diameters was 12 to 18 % above that of log1p with
+// the quotient everywhere; with 0.45 it is at most that at every distance, with
+// 0.5 up to 1 % above it at 0.45 to 0.7 diameters.)
 // On the edge itself q and f are infinite.
 // C_out: C = 2 L / (a b), for the gradient, from a b / 2 = Rm Rp + Pm . Pp, or
 // where x sees the edge under more than a right angle (its foot is inside, lm

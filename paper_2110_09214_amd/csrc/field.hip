@@ -868,8 +868,9 @@ constexpr int kDenseLanes = 32;
 // of the tiles.  One -> four waves, calls: mixed, 128 workgroups 109 -> 89 us,
 // 19,000 (20,000 charges in the holes) 1.66 -> 1.58 ms, but 23,400 (a fine
 // plate) 535 -> 567 us, 60,000 2.79 -> 2.94 ms, 200,000 8.4 -> 9.0 ms; FP64
-// (more pairs a test) 4,096 250 -> 212 us, 8,000 2.55 -> 1.85 ms, 50,000 10.1 ->
-// 9.9 ms, but 78,000 4.31 -> 4.43 ms, 200,000 13.8 -> 14.4 ms.
+// (more pairs a test) 4,096 233 -> 198 us, 8,000 3.00 -> 2.25 ms, 50,000 11.9 ->
+// 11.6 ms, but 78,000 (the coarse GEM cell) 3.47 -> 3.63 ms, 200,000 8.6 -> 9.1
+// ms; plates of 800 cells lose 2 % at 10,000 already and 7 % at 41,000.
 constexpr int kCloseFew = 20480, kCloseFewFp64 = 61440;
 
 template <bool WANT_V, bool MIXED, int WAVES>
